@@ -54,8 +54,8 @@ struct SurArgs {
   float F, lo, hi, xs_mul, xs_add;  // xs = x * xs_mul + xs_add
   uint32_t cr_threshold, gen, key_lo, key_hi;
   // composition
-  const float* O;    // [n][D]
-  const float* Rt;   // [n][D][D], Rt[c][j][i] = R[c][i][j]
+  const float* O;    // [n][comp_width(D)], K-permuted (comp_pos)
+  const float* Rf;   // [n][comp_frags(D)][4], MFMA fragment order
   const float* bias; // [n]
   int n;
   float inv2s2;      // 1 / (2 sigma^2)
@@ -91,103 +91,217 @@ struct SurArgs {
   unsigned long long* accepted;
 };
 
-constexpr int kEvalRows = 8;
-constexpr int kEvalThreads = 128;
+// ---------------------------------------------------------------------------
+// Composition objective of a tile of kEvalRows rows (pointers in rowp), one
+// workgroup.  Wave (h, cg), h in {0, 1}, takes the components cg, cg + G,
+// ... and of each the 64-column groups h, h + 2, ... of Z = (X - O[c]) R[c]^T
+// as FP32 16x16x4 MFMA blocks; G = blockDim / 128 waves share a column half.
+//   - A operand: the tile's rows lie in LDS, K-permuted (comp_pos) so that a
+//     lane's values of four K-steps are one 16-byte read; y = x - o is formed
+//     on the way to the MFMA, so components need no barrier between them.
+//   - B operand: R[c] in fragment order, one 16-byte load per lane and K-step
+//     for four column blocks, requested four K-steps (512 clocks of MFMA)
+//     ahead; the last group's empty column blocks are skipped.
+// An FP32 MFMA is a chain of fused multiply-adds in K order, and every sum
+// is formed in one fixed tree: a column's value accumulates over the columns
+// i, i + 128, ... in order, the 64 columns of a half add pairwise 32, 16, 8,
+// 4, 2, 1 apart, then half 0 + half 1 (the squared distance likewise over
+// coordinates), so f does not depend on the tile's position or on G.
+// Bound: FP32 MFMA rate (2 n D^2 FLOPs per row; 30 x 512 rows, D = 100,
+// n = 8: 17 us of matrix time with 112 of 128 columns computed) next to the
+// objective's ~25 VALU instructions per output.  16 rows per workgroup and
+// the components dealt to four wave pairs leave every SIMD 4 resident waves
+// at this size, so one wave's sines run under another's MFMAs.
+constexpr int kEvalRows = 16;
+constexpr int kEvalMaxThreads = 512;
 constexpr int kMaxComp = 64;
 
-// ---------------------------------------------------------------------------
-// Composition objective of up to kEvalRows rows (pointers in rowp), one
-// workgroup of kEvalThreads threads.  Per component: y = x - O[c] into LDS
-// with ||y||^2, z = R[c] y with one thread per output coordinate reading
-// the transposed rotation (coalesced), g = sum z^2 + sin^2(3z); partial
-// sums reduced in a fixed order.  Then the normalised weights.
+// Threads of a workgroup: one wave pair per component up to four.
+__host__ __device__ constexpr int comp_threads(int n) {
+  return n >= 4 ? 512 : n >= 2 ? 256 : 128;
+}
+
+// Coordinates of a row in LDS (and of a shift): rounded up to 16, and
+// within each 16 coordinate k = 4 s + q at 4 q + s.
+__host__ __device__ constexpr int comp_width(int D) { return (D + 15) / 16 * 16; }
+__host__ __device__ __forceinline__ int comp_pos(int k) {
+  return (k & ~15) | ((k & 3) << 2) | ((k >> 2) & 3);
+}
+
+// 16-byte fragments per component: 64-column groups x K-steps x lanes.
+__host__ __device__ constexpr size_t comp_frags(int D) {
+  return (size_t)((D + 63) / 64) * (comp_width(D) / 4) * 64;
+}
+
+__host__ __device__ constexpr size_t comp_lds_floats(int D, int n) {
+  return (size_t)kEvalRows * (comp_width(D) + 4)  // rows
+         + (size_t)4 * n * kEvalRows              // partial distances, sums
+         + kEvalRows;                             // values
+}
+
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+
+// z[b] (16 rows x 16 columns each, NB valid column blocks) of one component
+// and 64-column group: xp, op the lane's rows and shift (position 4 (l / 16)
+// of each 16), rf its fragments, nsteps K-steps.
+template <int NB>
+__device__ __forceinline__ void comp_group(const float* xp, const float* op,
+                                           const float4* rf, int nsteps,
+                                           floatx4 (&z)[4]) {
+  float4 nx[4];
+#pragma unroll
+  for (int u = 0; u < 4; ++u) nx[u] = rf[u * 64];
+#pragma unroll
+  for (int b = 0; b < NB; ++b) z[b] = floatx4{0.f, 0.f, 0.f, 0.f};
+  const int full = nsteps / 4, tail = nsteps % 4;
+  for (int g = 0; g < full; ++g) {
+    float4 cu[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) cu[u] = nx[u];
+    const float4 xv = ld4(xp + 16 * g), ov = ld4(op + 16 * g);
+    if (4 * (g + 1) < nsteps) {
+#pragma unroll
+      for (int u = 0; u < 4; ++u) nx[u] = rf[(4 * (g + 1) + u) * 64];
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const float y = get(xv, u) - get(ov, u);
+#pragma unroll
+      for (int b = 0; b < NB; ++b)
+        z[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(y, get(cu[u], b), z[b], 0,
+                                                    0, 0);
+    }
+  }
+  if (tail) {
+    const float4 xv = ld4(xp + 16 * full), ov = ld4(op + 16 * full);
+#pragma unroll
+    for (int u = 0; u < 3; ++u) {
+      if (u >= tail) break;
+      const float y = get(xv, u) - get(ov, u);
+#pragma unroll
+      for (int b = 0; b < NB; ++b)
+        z[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(y, get(nx[u], b), z[b], 0,
+                                                    0, 0);
+    }
+  }
+}
+
 __device__ void comp_eval_rows(const SurArgs& a, const float* const* rowp,
                                int nv, float* sm, float* fout) {
-  const int tid = (int)threadIdx.x, lane = tid % 64, wave = tid / 64;
-  constexpr int kWaves = kEvalThreads / 64;
-  const int D = a.D;
-  float* xs = sm;                          // [rows][D]
-  float* ys = xs + kEvalRows * D;          // [rows][D]
-  float* dk = ys + kEvalRows * D;          // [n][rows]
-  float* gk = dk + kMaxComp * kEvalRows;   // [n][rows]
-  float* red = gk + kMaxComp * kEvalRows;  // [2][rows][waves]
-  for (int t = tid; t < kEvalRows * D; t += kEvalThreads) {
-    const int r = t / D, j = t - r * D;
-    xs[t] = r < nv ? rowp[r][j] : 0.f;
+  const int tid = (int)threadIdx.x, nthr = (int)blockDim.x;
+  const int lane = tid % 64, li = lane % 16, lq = lane / 16;
+  const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
+  const int h = wave & 1, cg = wave >> 1, G = nthr / 128;
+  const int D = a.D, W = comp_width(D), sx = W + 4, n = a.n;
+  const int nsteps = (D + 3) / 4, ngrp = (D + 63) / 64;
+  float* xs = sm;                          // [rows][sx]
+  float* dk = xs + kEvalRows * sx;         // [n][half][rows]
+  float* gk = dk + 2 * n * kEvalRows;      // [n][half][rows]
+  for (int t = tid; t < kEvalRows * W; t += nthr) {
+    const int r = t / W, j = t - r * W;
+    xs[r * sx + comp_pos(j)] = r < nv && j < D ? rowp[r][j] : 0.f;
   }
   __syncthreads();
-  for (int c = 0; c < a.n; ++c) {
-    const float* o = a.O + (size_t)c * D;
-    const float* rt = a.Rt + (size_t)c * D * D;
-    float dpart[kEvalRows], gpart[kEvalRows];
+  const float* xp = xs + li * sx + 4 * lq;
+  for (int c = cg; c < n; c += G) {
+    const float* op = a.O + (size_t)c * W + 4 * lq;
+    // squared distance over this half's coordinates
+    float dq[16];
 #pragma unroll
-    for (int r = 0; r < kEvalRows; ++r) dpart[r] = gpart[r] = 0.f;
-    for (int j = tid; j < D; j += kEvalThreads) {
-      const float oj = o[j];
+    for (int u = 0; u < 16; ++u) dq[u] = 0.f;
+    for (int g0 = 4 * h; 16 * g0 < W; g0 += 8) {
 #pragma unroll
-      for (int r = 0; r < kEvalRows; ++r) {
-        const float y = xs[r * D + j] - oj;
-        ys[r * D + j] = y;
-        dpart[r] = fmaf(y, y, dpart[r]);
+      for (int g = 0; g < 4; ++g) {
+        if (16 * (g0 + g) >= W) break;
+        const float4 xv = ld4(xp + 16 * (g0 + g)), ov = ld4(op + 16 * (g0 + g));
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const float y = get(xv, u) - get(ov, u);
+          dq[4 * g + u] = fmaf(y, y, dq[4 * g + u]);
+        }
       }
     }
-    __syncthreads();
-    for (int i = tid; i < D; i += kEvalThreads) {
-      float z[kEvalRows];
 #pragma unroll
-      for (int r = 0; r < kEvalRows; ++r) z[r] = 0.f;
-      for (int j = 0; j < D; ++j) {
-        const float rv = rt[(size_t)j * D + i];
+    for (int m = 8; m >= 1; m >>= 1)
 #pragma unroll
-        for (int r = 0; r < kEvalRows; ++r) z[r] = fmaf(rv, ys[r * D + j], z[r]);
+      for (int u = 0; u < m; ++u) dq[u] += dq[u + m];
+    dq[0] += __shfl_xor(dq[0], 32, 64);
+    dq[0] += __shfl_xor(dq[0], 16, 64);
+    if (lq == 0) dk[(2 * c + h) * kEvalRows + li] = dq[0];
+    // the lane's columns li + 16 b of each group, rows 4 lq + r
+    floatx4 part[4];
+#pragma unroll
+    for (int b = 0; b < 4; ++b) part[b] = floatx4{0.f, 0.f, 0.f, 0.f};
+    for (int g = h; g < ngrp; g += 2) {
+      const float4* rf = reinterpret_cast<const float4*>(a.Rf) +
+                         (size_t)c * comp_frags(D) +
+                         (size_t)g * (W / 4) * 64 + lane;
+      const int nb = min(4, (D - 64 * g + 15) / 16);
+      floatx4 z[4];
+      if (nb == 4) comp_group<4>(xp, op, rf, nsteps, z);
+      else if (nb == 3) comp_group<3>(xp, op, rf, nsteps, z);
+      else if (nb == 2) comp_group<2>(xp, op, rf, nsteps, z);
+      else comp_group<1>(xp, op, rf, nsteps, z);
+#pragma unroll
+      for (int b = 0; b < 4; ++b) {
+        if (b >= nb) break;
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          part[b][r] += fmaf(z[b][r], z[b][r], sin_squared(3.0f * z[b][r]));
       }
-#pragma unroll
-      for (int r = 0; r < kEvalRows; ++r)
-        gpart[r] += fmaf(z[r], z[r], sin_squared(3.0f * z[r]));
     }
+    float v[4];
 #pragma unroll
-    for (int r = 0; r < kEvalRows; ++r) {
-      const float ds = group_sum<64>(dpart[r]);
-      const float gs = group_sum<64>(gpart[r]);
-      if (lane == 0) {
-        red[(0 * kEvalRows + r) * kWaves + wave] = ds;
-        red[(1 * kEvalRows + r) * kWaves + wave] = gs;
-      }
-    }
-    __syncthreads();
-    if (tid < 2 * kEvalRows) {
-      float s = 0.f;
-#pragma unroll
-      for (int w = 0; w < kWaves; ++w) s += red[tid * kWaves + w];
-      const int q = tid / kEvalRows, r = tid % kEvalRows;
-      (q == 0 ? dk : gk)[c * kEvalRows + r] = s;
-    }
-    __syncthreads();
+    for (int r = 0; r < 4; ++r)
+      v[r] = (part[0][r] + part[2][r]) + (part[1][r] + part[3][r]);
+    // 16 columns of four rows: two reduce-scatter steps, then two exchanges
+    const bool u8 = (lane & 8) != 0, u4 = (lane & 4) != 0;
+    const float v0 = (u8 ? v[2] : v[0]) + __shfl_xor(u8 ? v[0] : v[2], 8, 64);
+    const float v1 = (u8 ? v[3] : v[1]) + __shfl_xor(u8 ? v[1] : v[3], 8, 64);
+    float s = (u4 ? v1 : v0) + __shfl_xor(u4 ? v0 : v1, 4, 64);
+    s += __shfl_xor(s, 2, 64);
+    s += __shfl_xor(s, 1, 64);
+    if ((lane & 3) == 0)
+      gk[(2 * c + h) * kEvalRows + 4 * lq + (u8 ? 2 : 0) + (u4 ? 1 : 0)] = s;
   }
+  __syncthreads();
+  // the halves' sums; then every weight's exponential, in parallel
+  for (int t = tid; t < n * kEvalRows; t += nthr) {
+    const int at = (t / kEvalRows) * 2 * kEvalRows + t % kEvalRows;
+    dk[at] += dk[at + kEvalRows];
+    gk[at] += gk[at + kEvalRows];
+  }
+  __syncthreads();
   if (tid < kEvalRows) {
     float dmin = INFINITY;
-    for (int c = 0; c < a.n; ++c) dmin = fminf(dmin, dk[c * kEvalRows + tid]);
+    for (int c = 0; c < n; ++c)
+      dmin = fminf(dmin, dk[2 * c * kEvalRows + tid]);
+    fout[tid] = dmin;
+  }
+  __syncthreads();
+  for (int t = tid; t < n * kEvalRows; t += nthr) {
+    const int r = t % kEvalRows, at = (t / kEvalRows) * 2 * kEvalRows + r;
+    dk[at] = expf(-(dk[at] - fout[r]) * a.inv2s2);
+    gk[at] += a.bias[t / kEvalRows];
+  }
+  __syncthreads();
+  if (tid < kEvalRows) {
     float wsum = 0.f, f = 0.f;
-    for (int c = 0; c < a.n; ++c) {
-      const float w = expf(-(dk[c * kEvalRows + tid] - dmin) * a.inv2s2);
+    for (int c = 0; c < n; ++c) {
+      const float w = dk[2 * c * kEvalRows + tid];
       wsum += w;
-      f = fmaf(w, gk[c * kEvalRows + tid] + a.bias[c], f);
+      f = fmaf(w, gk[2 * c * kEvalRows + tid], f);
     }
     fout[tid] = f / wsum;
   }
   __syncthreads();
 }
 
-__host__ __device__ constexpr size_t comp_lds_floats(int D) {
-  return (size_t)2 * kEvalRows * D + (size_t)2 * kMaxComp * kEvalRows +
-         (size_t)2 * kEvalRows * (kEvalThreads / 64) + kEvalRows;
-}
-
 // f of rows X (row r at X + r * ldx).
-__global__ __launch_bounds__(kEvalThreads) void k_comp_eval(SurArgs a,
-                                                            const float* X,
-                                                            int n, int ldx,
-                                                            float* f) {
+__global__ __launch_bounds__(kEvalMaxThreads) void k_comp_eval(SurArgs a,
+                                                               const float* X,
+                                                               int n, int ldx,
+                                                               float* f) {
   extern __shared__ __align__(16) float sm[];
   __shared__ const float* rowp[kEvalRows];
   const int row0 = (int)blockIdx.x * kEvalRows;
@@ -195,7 +309,7 @@ __global__ __launch_bounds__(kEvalThreads) void k_comp_eval(SurArgs a,
   if ((int)threadIdx.x < kEvalRows)
     rowp[threadIdx.x] = X + (size_t)(row0 + min((int)threadIdx.x, nv - 1)) * ldx;
   __syncthreads();
-  float* fout = sm + comp_lds_floats(a.D) - kEvalRows;
+  float* fout = sm + comp_lds_floats(a.D, a.n) - kEvalRows;
   comp_eval_rows(a, rowp, nv, sm, fout);
   if ((int)threadIdx.x < nv) f[row0 + threadIdx.x] = fout[threadIdx.x];
 }
@@ -589,7 +703,7 @@ __global__ __launch_bounds__(512) void k_mlp_infer_res(SurArgs a, const float* X
 // ---------------------------------------------------------------------------
 // Choice, true evaluation, selection, next generation, archive insert:
 // kEvalRows targets per workgroup.
-__global__ __launch_bounds__(kEvalThreads) void k_sur_select(SurArgs a) {
+__global__ __launch_bounds__(kEvalMaxThreads) void k_sur_select(SurArgs a) {
   extern __shared__ __align__(16) float sm[];
   __shared__ const float* rowp[kEvalRows];
   __shared__ int acc_s[kEvalRows];
@@ -615,7 +729,7 @@ __global__ __launch_bounds__(kEvalThreads) void k_sur_select(SurArgs a) {
     if (tid < nv) a.choice[t] = best;
   }
   __syncthreads();
-  float* fout = sm + comp_lds_floats(a.D) - kEvalRows;
+  float* fout = sm + comp_lds_floats(a.D, a.n) - kEvalRows;
   comp_eval_rows(a, rowp, nv, sm, fout);
   if (tid < nv) {
     const int i = i0 + tid;
@@ -633,7 +747,7 @@ __global__ __launch_bounds__(kEvalThreads) void k_sur_select(SurArgs a) {
   }
   __syncthreads();
   const int nq = (a.D + 3) / 4;
-  for (int t2 = tid; t2 < nv * nq; t2 += kEvalThreads) {
+  for (int t2 = tid; t2 < nv * nq; t2 += (int)blockDim.x) {
     const int r = t2 / nq, q = t2 - r * nq;
     const int i = i0 + r;
     const size_t t = (size_t)run * a.NP + i;
@@ -740,7 +854,6 @@ __global__ __launch_bounds__(256) void k_model_prep(SurArgs a) {
 // C(4 (l / 16) + r, l % 16)), so that a minibatch of 128 rows of 30 runs
 // already spreads over 240 workgroups.
 constexpr int kTrainRows = 16;
-typedef float floatx4 __attribute__((ext_vector_type(4)));
 
 __host__ __device__ constexpr size_t train_lds_floats(int Dp, int H) {
   return (size_t)kTrainRows * (Dp + 1) + (size_t)3 * kTrainRows * (H + 1) +
@@ -1227,20 +1340,28 @@ __global__ __launch_bounds__(256) void k_sur_best(SurArgs a) {
   if ((threadIdx.x % 64) == 0) atomicMin(&a.best_key[run], best);
 }
 
-// Transposed rotations Rt[c][j][i] = R[c][i][j] and shifts.
+// Shifts K-permuted and zero-padded; rotations in the B-operand order of
+// 16x16x4 MFMA blocks: fragment (c, group g, K-step s, lane l) holds
+// R[c][64 g + 16 b + l % 16][4 s + l / 16], b = 0..3, zero outside D x D.
 __global__ __launch_bounds__(256) void k_comp_prep(const float* O,
                                                    const float* R, int ldr,
                                                    int n, int D, float* Op,
-                                                   float* Rt) {
-  const size_t per = (size_t)D * D;
+                                                   float* Rf) {
+  const int W = comp_width(D);
+  const size_t per = comp_frags(D) * 4;
   const size_t total = (size_t)n * per;
-  for (size_t t = (size_t)blockIdx.x * 256 + threadIdx.x; t < total;
-       t += (size_t)gridDim.x * 256) {
+  const size_t t0 = (size_t)blockIdx.x * 256 + threadIdx.x;
+  for (size_t t = t0; t < total; t += (size_t)gridDim.x * 256) {
     const int c = (int)(t / per);
     const size_t e = t - (size_t)c * per;
-    const int j = (int)(e / D), i = (int)(e - (size_t)j * D);
-    Rt[t] = R[((size_t)c * D + i) * ldr + j];
-    if (j == 0) Op[(size_t)c * D + i] = O[(size_t)c * D + i];
+    const int b = (int)(e % 4), l = (int)(e / 4 % 64);
+    const int s = (int)(e / 256 % (W / 4)), g = (int)(e / 256 / (W / 4));
+    const int i = 64 * g + 16 * b + l % 16, j = 4 * s + l / 16;
+    Rf[t] = i < D && j < D ? R[((size_t)c * D + i) * ldr + j] : 0.f;
+  }
+  for (size_t t = t0; t < (size_t)n * W; t += (size_t)gridDim.x * 256) {
+    const int c = (int)(t / W), k = (int)(t - (size_t)c * W);
+    Op[(size_t)c * W + comp_pos(k)] = k < D ? O[(size_t)c * D + k] : 0.f;
   }
 }
 
@@ -1262,7 +1383,7 @@ int64_t model_size(int D, int H) {
 }
 
 struct SLayout {
-  size_t best, acc, O, Rt, bias, cand, pred, choice, theta, m, v, w1f, w2f,
+  size_t best, acc, O, Rf, bias, cand, pred, choice, theta, m, v, w1f, w2f,
       w1t, w2t, ax, at, xsb, h1b, h2b, d1b, d2b, eb, total;
   int pstride, Dp;
 };
@@ -1296,7 +1417,7 @@ de_status check(const de_params* p, const de_composition* c,
     return DE_E_INVAL;
   if (!std::isfinite(s->eps) || !(s->eps > 0.f)) return DE_E_INVAL;
   // LDS: composition evaluation and model inference
-  if (de::comp_lds_floats(p->D) * 4 > (size_t)de::kMaxLdsBytes ||
+  if (de::comp_lds_floats(p->D, c->n) * 4 > (size_t)de::kMaxLdsBytes ||
       de::infer_lds_bytes((int)rup(p->D, 32), s->hidden) >
           (size_t)de::kMaxLdsBytes ||
       de::train_lds_floats((int)rup(p->D, 32), s->hidden) * 4 >
@@ -1320,8 +1441,8 @@ SLayout layout(const de_params& p, const de_composition& c,
   L.pstride = (int)rup((size_t)model_size(p.D, s.hidden), 64);
   L.best = take(8 * R);
   L.acc = take(8 * R);
-  L.O = take(4 * (size_t)c.n * D);
-  L.Rt = take(4 * (size_t)c.n * D * D);
+  L.O = take(4 * (size_t)c.n * de::comp_width(p.D));
+  L.Rf = take(16 * (size_t)c.n * de::comp_frags(p.D));
   L.bias = take(4 * (size_t)c.n);
   L.cand = take(4 * R * NP * k * ldx);
   L.pred = take(4 * R * NP * k);
@@ -1416,7 +1537,7 @@ SurArgs args_of(const de_sur* s) {
   a.key_lo = (uint32_t)s->p.seed;
   a.key_hi = (uint32_t)(s->p.seed >> 32);
   a.O = reinterpret_cast<const float*>(w + L.O);
-  a.Rt = reinterpret_cast<const float*>(w + L.Rt);
+  a.Rf = reinterpret_cast<const float*>(w + L.Rf);
   a.bias = reinterpret_cast<const float*>(w + L.bias);
   a.n = s->n;
   a.inv2s2 = (float)(1.0 / (2.0 * (double)s->sigma * s->sigma));
@@ -1565,10 +1686,10 @@ de_status comp_eval(const de_sur* s, const float* X, int n, int ldx, float* f,
                     hipStream_t st) {
   if (n == 0) return DE_OK;
   const SurArgs a = args_of(s);
-  const size_t lds = de::comp_lds_floats(a.D) * 4;
+  const size_t lds = de::comp_lds_floats(a.D, a.n) * 4;
   hipLaunchKernelGGL(de::k_comp_eval,
                      dim3((n + de::kEvalRows - 1) / de::kEvalRows),
-                     dim3(de::kEvalThreads), lds, st, a, X, n, ldx, f);
+                     dim3(de::comp_threads(a.n)), lds, st, a, X, n, ldx, f);
   return FROM_HIP(hipGetLastError());
 }
 
@@ -1590,8 +1711,8 @@ de_status one_generation(de_sur* s, hipStream_t st) {
   }
   hipLaunchKernelGGL(de::k_sur_select,
                      dim3((a.NP + de::kEvalRows - 1) / de::kEvalRows, a.runs),
-                     dim3(de::kEvalThreads), de::comp_lds_floats(a.D) * 4, st,
-                     a);
+                     dim3(de::comp_threads(a.n)),
+                     de::comp_lds_floats(a.D, a.n) * 4, st, a);
   rc = FROM_HIP(hipGetLastError());
   if (rc != DE_OK) return rc;
   s->gen += 1;
@@ -1668,9 +1789,9 @@ DE_API de_status de_sur_init(const de_params* params,
   SurArgs a = args_of(s);
   // composition data
   hipLaunchKernelGGL(de::k_comp_prep,
-                     dim3(grid_for((size_t)comp->n * p.D * p.D, 256)),
+                     dim3(grid_for(comp->n * de::comp_frags(p.D) * 4, 256)),
                      dim3(256), 0, st, comp->O, comp->R, comp->ldr, comp->n,
-                     p.D, const_cast<float*>(a.O), const_cast<float*>(a.Rt));
+                     p.D, const_cast<float*>(a.O), const_cast<float*>(a.Rf));
   rc = FROM_HIP(hipGetLastError());
   if (rc == DE_OK)
     rc = FROM_HIP(hipMemcpyAsync(const_cast<float*>(a.bias), comp->bias,

@@ -141,48 +141,77 @@ __host__ __device__ constexpr size_t comp_lds_floats(int D, int n) {
 
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 
+// The operands of four K-steps: shift values and B fragments.
+struct CompFrags {
+  float4 o, b[4];
+};
+
+__device__ __forceinline__ void comp_load(CompFrags& f, const float* op,
+                                          const float4* rf, int g) {
+  f.o = ld4(op + 16 * g);
+#pragma unroll
+  for (int u = 0; u < 4; ++u) f.b[u] = rf[(4 * g + u) * 64];
+}
+
+// K-step u of NB column blocks.
+template <int NB>
+__device__ __forceinline__ void comp_step(const CompFrags& f, float4 xv, int u,
+                                          floatx4 (&z)[4]) {
+  const float y = get(xv, u) - get(f.o, u);
+#pragma unroll
+  for (int b = 0; b < NB; ++b)
+    z[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(y, get(f.b[u], b), z[b], 0, 0,
+                                                0);
+}
+
+template <int NB>
+__device__ __forceinline__ void comp_four(const CompFrags& f, const float* xp,
+                                          floatx4 (&z)[4]) {
+  const float4 xv = ld4(xp);
+  __builtin_amdgcn_sched_barrier(0);  // the loads ahead of it stay ahead
+#pragma unroll
+  for (int u = 0; u < 4; ++u) comp_step<NB>(f, xv, u, z);
+}
+
+// The last 0..3 K-steps.
+template <int NB>
+__device__ __forceinline__ void comp_tail(const CompFrags& f, const float* xp,
+                                          int steps, floatx4 (&z)[4]) {
+  if (steps == 0) return;
+  const float4 xv = ld4(xp);
+  comp_step<NB>(f, xv, 0, z);
+  if (steps > 1) comp_step<NB>(f, xv, 1, z);
+  if (steps > 2) comp_step<NB>(f, xv, 2, z);
+}
+
 // z[b] (16 rows x 16 columns each, NB valid column blocks) of one component
 // and 64-column group: xp, op the lane's rows and shift (position 4 (l / 16)
-// of each 16), rf its fragments, nsteps K-steps.
+// of each 16), rf its fragments, nsteps K-steps.  Two operand sets take
+// turns, so that one group's loads fly under the other's MFMAs without
+// copies; a load past the last group repeats it.
 template <int NB>
 __device__ __forceinline__ void comp_group(const float* xp, const float* op,
                                            const float4* rf, int nsteps,
                                            floatx4 (&z)[4]) {
-  float4 nx[4];
-#pragma unroll
-  for (int u = 0; u < 4; ++u) nx[u] = rf[u * 64];
+  const int full = nsteps / 4, tail = nsteps % 4;
+  const int last = (nsteps + 3) / 4 - 1;
+  CompFrags f0, f1;
+  comp_load(f0, op, rf, 0);
 #pragma unroll
   for (int b = 0; b < NB; ++b) z[b] = floatx4{0.f, 0.f, 0.f, 0.f};
-  const int full = nsteps / 4, tail = nsteps % 4;
-  for (int g = 0; g < full; ++g) {
-    float4 cu[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) cu[u] = nx[u];
-    const float4 xv = ld4(xp + 16 * g), ov = ld4(op + 16 * g);
-    if (4 * (g + 1) < nsteps) {
-#pragma unroll
-      for (int u = 0; u < 4; ++u) nx[u] = rf[(4 * (g + 1) + u) * 64];
-    }
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const float y = get(xv, u) - get(ov, u);
-#pragma unroll
-      for (int b = 0; b < NB; ++b)
-        z[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(y, get(cu[u], b), z[b], 0,
-                                                    0, 0);
-    }
+  int g = 0;
+  for (; g + 2 <= full; g += 2) {
+    comp_load(f1, op, rf, g + 1);
+    comp_four<NB>(f0, xp + 16 * g, z);
+    comp_load(f0, op, rf, min(g + 2, last));
+    comp_four<NB>(f1, xp + 16 * (g + 1), z);
   }
-  if (tail) {
-    const float4 xv = ld4(xp + 16 * full), ov = ld4(op + 16 * full);
-#pragma unroll
-    for (int u = 0; u < 3; ++u) {
-      if (u >= tail) break;
-      const float y = get(xv, u) - get(ov, u);
-#pragma unroll
-      for (int b = 0; b < NB; ++b)
-        z[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(y, get(nx[u], b), z[b], 0,
-                                                    0, 0);
-    }
+  if (g < full) {
+    comp_load(f1, op, rf, last);
+    comp_four<NB>(f0, xp + 16 * g, z);
+    comp_tail<NB>(f1, xp + 16 * last, tail, z);
+  } else {
+    comp_tail<NB>(f0, xp + 16 * last, tail, z);
   }
 }
 
@@ -210,13 +239,19 @@ __device__ void comp_eval_rows(const SurArgs& a, const float* const* rowp,
 #pragma unroll
     for (int u = 0; u < 16; ++u) dq[u] = 0.f;
     for (int g0 = 4 * h; 16 * g0 < W; g0 += 8) {
+      float4 xv[4], ov[4];
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
-        if (16 * (g0 + g) >= W) break;
-        const float4 xv = ld4(xp + 16 * (g0 + g)), ov = ld4(op + 16 * (g0 + g));
+        const int at = min(16 * (g0 + g), W - 16);
+        xv[g] = ld4(xp + at);
+        ov[g] = ld4(op + at);
+      }
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const bool in = 16 * (g0 + g) < W;  // repeated groups add zero
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-          const float y = get(xv, u) - get(ov, u);
+          const float y = in ? get(xv[g], u) - get(ov[g], u) : 0.f;
           dq[4 * g + u] = fmaf(y, y, dq[4 * g + u]);
         }
       }
@@ -298,10 +333,9 @@ __device__ void comp_eval_rows(const SurArgs& a, const float* const* rowp,
 }
 
 // f of rows X (row r at X + r * ldx).
-__global__ __launch_bounds__(kEvalMaxThreads) void k_comp_eval(SurArgs a,
-                                                               const float* X,
-                                                               int n, int ldx,
-                                                               float* f) {
+__global__ __launch_bounds__(kEvalMaxThreads)
+__attribute__((amdgpu_waves_per_eu(4)))
+void k_comp_eval(SurArgs a, const float* X, int n, int ldx, float* f) {
   extern __shared__ __align__(16) float sm[];
   __shared__ const float* rowp[kEvalRows];
   const int row0 = (int)blockIdx.x * kEvalRows;
@@ -703,7 +737,8 @@ __global__ __launch_bounds__(512) void k_mlp_infer_res(SurArgs a, const float* X
 // ---------------------------------------------------------------------------
 // Choice, true evaluation, selection, next generation, archive insert:
 // kEvalRows targets per workgroup.
-__global__ __launch_bounds__(kEvalMaxThreads) void k_sur_select(SurArgs a) {
+__global__ __launch_bounds__(kEvalMaxThreads)
+__attribute__((amdgpu_waves_per_eu(4))) void k_sur_select(SurArgs a) {
   extern __shared__ __align__(16) float sm[];
   __shared__ const float* rowp[kEvalRows];
   __shared__ int acc_s[kEvalRows];

@@ -91,6 +91,23 @@ struct SurArgs {
   unsigned long long* accepted;
 };
 
+// Work unit of a (units per run) x (runs) grid: consecutive units of a run
+// go to one XCD (xcd_logical_block over the linear workgroup number), and
+// every kernel of a generation deals the runs to the XCDs alike, so that a
+// run's model, minibatch and candidates are read from the L2 that holds
+// them.  Dealt as launched, the workgroups of one run land on all eight
+// XCDs and each reads the whole model through the fabric.
+struct RunUnit {
+  int run, x;
+};
+
+__device__ __forceinline__ RunUnit run_unit() {
+  const int nx = (int)gridDim.x;
+  const int lb = xcd_logical_block((int)(blockIdx.y * gridDim.x + blockIdx.x),
+                                   nx * (int)gridDim.y);
+  return {lb / nx, lb % nx};
+}
+
 // ---------------------------------------------------------------------------
 // Composition objective of a tile of kEvalRows rows (pointers in rowp), one
 // workgroup.  Wave (h, cg), h in {0, 1}, takes the components cg, cg + G,
@@ -356,11 +373,12 @@ __host__ __device__ constexpr int cand_rows_per_wave(int D) {
 }
 
 __global__ __launch_bounds__(256) void k_sur_cand(SurArgs a) {
-  const int run = (int)blockIdx.y;
+  const RunUnit wu = run_unit();
+  const int run = wu.run;
   const int wave = (int)threadIdx.x / 64;
   const int rpw = cand_rows_per_wave(a.D), lpr = 64 / rpw;
   const int lane = (int)threadIdx.x % lpr;
-  const int cr = ((int)blockIdx.x * 4 + wave) * rpw + ((int)threadIdx.x % 64) / lpr;
+  const int cr = (wu.x * 4 + wave) * rpw + ((int)threadIdx.x % 64) / lpr;
   if (cr >= a.NP * a.k) return;  // whole row groups leave together
   const int i = cr / a.k, c = cr - i * a.k;
   const uint32_t ctr_i = (uint32_t)i | ((uint32_t)c << 24);
@@ -396,7 +414,7 @@ __global__ __launch_bounds__(256) void k_sur_cand(SurArgs a) {
 
 // ---------------------------------------------------------------------------
 // MLP inference on MFMA: rows of X (row r at X + r * ldx) of run
-// run0 + blockIdx.y, kInferRows rows per workgroup of 256 threads.
+// run0 + the unit's run, kInferRows rows per workgroup of 256 threads.
 constexpr int kInferRows = 64;
 
 __host__ __device__ constexpr size_t infer_lds_bytes(int Dp, int H) {
@@ -468,7 +486,7 @@ __device__ __forceinline__ float rows_of_block(const floatx16& part,
 }
 
 // MLP inference on MFMA: rows of X (row r at X + r * ldx) of run
-// run0 + blockIdx.y, 64 rows per workgroup of 256 threads (4 waves, each
+// run0 + the unit's run, 64 rows per workgroup of 256 threads (4 waves, each
 // two 32-column blocks per layer over both 32-row blocks).  Layer 1 writes
 // relu(A W1^T + b1) to LDS in BF16; layer 2's epilogue applies relu(. + b2)
 // and the output weights w3 directly, so only per-wave row sums remain.
@@ -478,15 +496,16 @@ __global__ __launch_bounds__(256) void k_mlp_infer(SurArgs a, const float* X,
                                                    size_t y_run_stride,
                                                    int run0) {
   extern __shared__ __align__(16) char smem[];
-  const int run = run0 + (int)blockIdx.y;
+  const RunUnit wu = run_unit();
+  const int run = run0 + wu.run;
   const int tid = (int)threadIdx.x, wave = tid / 64, lane = tid % 64;
-  const int row0 = (int)blockIdx.x * kInferRows;
+  const int row0 = wu.x * kInferRows;
   const int Dp = a.Dp, H = a.H;
   const int sa = Dp + 8, sh = H + 8;
   __bf16* A = reinterpret_cast<__bf16*>(smem);
   __bf16* H1 = A + (size_t)kInferRows * sa;
   float* ypart = reinterpret_cast<float*>(H1 + (size_t)kInferRows * sh);
-  const float* Xr = X + blockIdx.y * x_run_stride;
+  const float* Xr = X + wu.run * x_run_stride;
   const float* th = a.theta + (size_t)run * a.pstride;
   const float* b1 = th + (size_t)H * a.D;
   const float* b2 = b1 + H + (size_t)H * H;
@@ -554,7 +573,7 @@ __global__ __launch_bounds__(256) void k_mlp_infer(SurArgs a, const float* X,
     float s = b3;
 #pragma unroll
     for (int w = 0; w < 4; ++w) s += ypart[w * kInferRows + tid];
-    y[blockIdx.y * y_run_stride + row0 + tid] = s;
+    y[wu.run * y_run_stride + row0 + tid] = s;
   }
 }
 
@@ -609,14 +628,15 @@ __global__ __launch_bounds__(512) void k_mlp_infer_res(SurArgs a, const float* X
   constexpr int sa = Dp + 8, sh = H + 8;
   constexpr int kStage = (kInferRows * Dp + 32 * NW * 2 - 1) / (64 * NW);
   extern __shared__ __align__(16) char smem[];
-  const int run = run0 + (int)blockIdx.y;
+  const RunUnit wu = run_unit();
+  const int run = run0 + wu.run;
   const int tid = (int)threadIdx.x, lane = tid % 64;
   const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
   const int nthr = 64 * NW;
   __bf16* A = reinterpret_cast<__bf16*>(smem);
   __bf16* H1 = A + (size_t)kInferRows * sa;
   float* ypart = reinterpret_cast<float*>(H1 + (size_t)kInferRows * sh);
-  const float* Xr = X + blockIdx.y * x_run_stride;
+  const float* Xr = X + wu.run * x_run_stride;
   const float* th = a.theta + (size_t)run * a.pstride;
   const float* b1 = th + (size_t)H * a.D;
   const float* b2 = b1 + H + (size_t)H * H;
@@ -637,7 +657,7 @@ __global__ __launch_bounds__(512) void k_mlp_infer_res(SurArgs a, const float* X
     for (int kb = 0; kb < KB2; ++kb) w2r[kb] = f2[(size_t)kb * 64];
   }
   const int tiles = (n + kInferRows - 1) / kInferRows;
-  const int t0 = (int)blockIdx.x * kResTiles;
+  const int t0 = wu.x * kResTiles;
   const int t1 = min(t0 + kResTiles, tiles);
   // scaled value of element e (row e / Dp, coordinate e % Dp) of tile t
   auto xval = [&](int t, int e) {
@@ -729,7 +749,7 @@ __global__ __launch_bounds__(512) void k_mlp_infer_res(SurArgs a, const float* X
       float s = b3;
 #pragma unroll
       for (int w = 0; w < NW; ++w) s += ypart[w * kInferRows + tid];
-      y[blockIdx.y * y_run_stride + row] = s;
+      y[wu.run * y_run_stride + row] = s;
     }
   }
 }
@@ -742,8 +762,9 @@ __attribute__((amdgpu_waves_per_eu(4))) void k_sur_select(SurArgs a) {
   extern __shared__ __align__(16) float sm[];
   __shared__ const float* rowp[kEvalRows];
   __shared__ int acc_s[kEvalRows];
-  const int run = (int)blockIdx.y;
-  const int i0 = (int)blockIdx.x * kEvalRows;
+  const RunUnit wu = run_unit();
+  const int run = wu.run;
+  const int i0 = wu.x * kEvalRows;
   const int nv = min(kEvalRows, a.NP - i0);
   const int tid = (int)threadIdx.x;
   if (tid < kEvalRows) {
@@ -1029,13 +1050,14 @@ __device__ __forceinline__ void mfma16_pair(const float* ap, const float* bb,
 template <int KS1, int KS2>
 __global__ __launch_bounds__(512) void k_train_fwd(SurArgs a) {
   extern __shared__ __align__(16) float sm[];
-  const int run = (int)blockIdx.y;
+  const RunUnit wu = run_unit();
+  const int run = wu.run;
   const int tid = (int)threadIdx.x, lane = tid % 64;
   const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
   const int li = lane % 16, lq = lane / 16;
   const int H = KS2 > 0 ? 4 * KS2 : a.H, D = a.D;
   const int Dp = KS1 > 0 ? 4 * KS1 : a.Dp;
-  const int b0 = (int)blockIdx.x * kTrainRows;
+  const int b0 = wu.x * kTrainRows;
   const int sx = Dp + 1, sh = H + 1;
   float* XS = sm;                       // [16][sx]
   float* H1 = XS + kTrainRows * sx;     // [16][sh]
@@ -1213,18 +1235,19 @@ __device__ __forceinline__ floatx16 mfma_block_mm(const float* ap, int astep,
 template <int KS>
 __global__ __launch_bounds__(256) void k_train_grad(SurArgs a) {
   __shared__ float tblk[4][32][33];  // one 32x32 block per wave (+1 column)
-  const int run = (int)blockIdx.y;
+  const RunUnit wu = run_unit();
+  const int run = wu.run;
   const int wave = (int)threadIdx.x / 64, lane = (int)threadIdx.x % 64;
   const int li = lane % 32, lk = lane / 32;
   const int H = a.H, D = a.D, Dp = a.Dp, B = a.B;
   const int nbh = H / 32, nbd = Dp / 32;
   const int nb1 = nbh * nbd, nb2 = nbh * nbh;
   const int mat_wgs = (nb1 + nb2 + 3) / 4;
-  if ((int)blockIdx.x >= mat_wgs) {
-    grad_vec(a, run, ((int)blockIdx.x - mat_wgs) * 256 + (int)threadIdx.x);
+  if (wu.x >= mat_wgs) {
+    grad_vec(a, run, (wu.x - mat_wgs) * 256 + (int)threadIdx.x);
     return;
   }
-  const int blk = (int)blockIdx.x * 4 + wave;
+  const int blk = wu.x * 4 + wave;
   if (blk >= nb1 + nb2) return;  // whole waves; no barrier in this kernel
   const bool w1 = blk < nb1;
   const int q = w1 ? blk : blk - nb1;

@@ -25,8 +25,12 @@
 // ends.  Host code never passes `scratch` itself to a kernel or a copy (in
 // host code the name stands for a host-side shadow): it uses the device
 // address that hipGetSymbolAddress returns for the current device.
+// The limit counts everything but the row scales of the FP32 product's
+// operand layout (kScaleBytes at most), for which the array has room beyond.
 constexpr size_t kStaticScratchBytes = (size_t)8 << 20;
-static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
+constexpr size_t kScaleBytes = (size_t)8 << 10;
+static __device__ __align__(256) unsigned char
+    scratch[kStaticScratchBytes + kScaleBytes];
 
 namespace {
 
@@ -67,7 +71,8 @@ Layout layout_for(const de_params& p, int kind, int prec, bool handle = true) {
   L.rop = 0;
   L.rf32 = 0;
   if (kind == de::kObjRotOsc)
-    L.rop = take((size_t)dpad * dpad * (prec == de::kPrecBF16 ? 2 : 4));
+    L.rop = take(de::rot_operand_bytes(prec, dpad) +
+                 de::rot_scale_bytes(prec, dpad));
   if (!handle) {
     L.total = off;
     return L;
@@ -934,7 +939,10 @@ DE_API de_status de_generation_noalloc(const de_params* params,
   const int prec = objective->kind == de::kObjRotOsc ? objective->gemm_prec
                                                      : de::kPrecF32;
   const Layout L = layout_for(p, objective->kind, prec, false);
-  if (L.total > kStaticScratchBytes) return DE_E_UNSUPPORTED;
+  const size_t scales = objective->kind == de::kObjRotOsc
+                            ? de::rot_scale_bytes(prec, dpad_for(p.D))
+                            : 0;
+  if (L.total - scales > kStaticScratchBytes) return DE_E_UNSUPPORTED;
 
   (void)hipGetLastError();
   hipStream_t st = reinterpret_cast<hipStream_t>(hip_stream);

@@ -47,6 +47,11 @@ hipError_t note_hip(hipError_t e, const char* file, int line);
 // CU's 160 KB, on the current device (once per kernel and device).
 hipError_t set_max_dynamic_lds(const void* fn);
 
+// Bytes of R in the operand layout of a precision, and of the row scales
+// that follow it (split layout of the FP32 product).
+size_t rot_operand_bytes(int prec, int dpad);
+size_t rot_scale_bytes(int prec, int dpad);
+
 size_t rot_lds_bytes_host(int prec, int dpad, bool jde = false);
 bool sep_supported(int D);
 

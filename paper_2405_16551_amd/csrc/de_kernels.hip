@@ -235,6 +235,43 @@ __global__ __launch_bounds__(256) void k_prep_rot_f32(const float* R, int ldr,
   }
 }
 
+// Split layout (PrecSplit): row n of R scaled by its own power of two, as
+// halves: element (n, k) of half p goes to block nb = n / 32, K-step kb =
+// k / 16, lane (n % 32) + 32 ((k % 16) / 8), slot k % 8 of fragment
+// ((nb * dpad / 16 + kb) * 2 + p) * 64 + lane; the rows' inverse scales
+// follow the dpad x dpad halves.  One workgroup per row.
+__global__ __launch_bounds__(256) void k_prep_rot_split(const float* R, int ldr,
+                                                        int D, int dpad,
+                                                        half8* rop) {
+  __shared__ float wm[4];
+  const int n = (int)blockIdx.x;
+  float m = 0.f;
+  if (n < D)
+    for (int k = (int)threadIdx.x; k < D; k += 256)
+      m = fmaxf(m, fabsf(R[(size_t)n * ldr + k]));
+  for (int x = 32; x >= 1; x >>= 1) m = fmaxf(m, __shfl_xor(m, x, 64));
+  if (threadIdx.x % 64 == 0) wm[threadIdx.x / 64] = m;
+  __syncthreads();
+  m = fmaxf(fmaxf(wm[0], wm[1]), fmaxf(wm[2], wm[3]));
+  const RowScale rs = split_scale(m);
+  if (threadIdx.x == 0)
+    (reinterpret_cast<float*>(rop) + (size_t)dpad * dpad)[n] = rs.inv;
+  for (int g8 = (int)threadIdx.x; g8 < dpad / 8; g8 += 256) {
+    float v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int k = 8 * g8 + u;
+      v[u] = n < D && k < D ? R[(size_t)n * ldr + k] : 0.f;
+    }
+    half8 h, l;
+    split_halves(v, rs.scale, h, l);
+    const size_t f = ((size_t)(n / 32) * (dpad / 16) + g8 / 2) * 128 +
+                     (n % 32) + 32 * (g8 % 2);
+    rop[f] = h;
+    rop[f + 64] = l;
+  }
+}
+
 // ---------------------------------------------------------------------------
 // Statistics.
 __global__ void k_stats_reset(GenArgs a, int reset_accepted) {
@@ -711,7 +748,9 @@ hipError_t launch_rot_e(const GenArgs& a, int prec, hipStream_t s) {
   const long long tiles = EVAL ? (a.nrows + 63) / 64
                                : (long long)a.runs * ((a.NP + 63) / 64);
   const bool narrow = rot_bf16_narrow(a.dpad, tiles, device_cus());
-  const bool f32_narrow = a.dpad <= kF32NarrowMaxDpad;
+  // FP32 product over 128 wide: split halves, one column block per wave as
+  // long as two would leave waves without any (256: eight blocks)
+  const bool split_narrow = a.dpad <= kSplitNarrowMaxDpad;
   if (!EVAL && a.jde) {
     // padded width up to 128: trials built two rows per wave instruction
     if (a.dpad <= kPairMaxDpad) {
@@ -723,9 +762,9 @@ hipError_t launch_rot_e(const GenArgs& a, int prec, hipStream_t s) {
                                    true>(a, s);
     }
     if (prec != kPrecBF16)
-      return f32_narrow
-                 ? launch_rot_t<PrecF32Narrow, 32, 512, false, true>(a, s)
-                 : launch_rot_t<PrecF32, 32, 512, false, true>(a, s);
+      return split_narrow
+                 ? launch_rot_t<PrecSplitNarrow, 32, 512, false, true>(a, s)
+                 : launch_rot_t<PrecSplit, 32, 512, false, true>(a, s);
     return narrow
                ? launch_rot_t<PrecBF16, 64, kRotBf16ThreadsNarrow, false,
                               true>(a, s)
@@ -741,9 +780,12 @@ hipError_t launch_rot_e(const GenArgs& a, int prec, hipStream_t s) {
                   : launch_rot_t<PrecBF16, 64, kRotBf16Threads, false, false,
                                  true>(a, s);
   }
-  if (prec != kPrecBF16)
-    return f32_narrow ? launch_rot_t<PrecF32Narrow, 32, 512, EVAL>(a, s)
-                      : launch_rot_t<PrecF32, 32, 512, EVAL>(a, s);
+  if (prec != kPrecBF16) {
+    if (a.dpad <= kF32MaxDpad)  // evaluation: unpaired
+      return launch_rot_t<PrecF32Narrow, 32, 512, EVAL>(a, s);
+    return split_narrow ? launch_rot_t<PrecSplitNarrow, 32, 512, EVAL>(a, s)
+                        : launch_rot_t<PrecSplit, 32, 512, EVAL>(a, s);
+  }
   return narrow ? launch_rot_t<PrecBF16, 64, kRotBf16ThreadsNarrow, EVAL>(a, s)
                 : launch_rot_t<PrecBF16, 64, kRotBf16Threads, EVAL>(a, s);
 }
@@ -772,10 +814,19 @@ int device_cus() {
 
 // LDS bytes of the rotated kernel: BF16 tiles of 64 rows, FP32 tiles of 32
 // rows (independent of the number of threads).
+size_t rot_operand_bytes(int prec, int dpad) {
+  const size_t n = (size_t)dpad * dpad;
+  return prec == kPrecBF16 ? 2 * n : 4 * n;
+}
+
+size_t rot_scale_bytes(int prec, int dpad) {
+  return prec != kPrecBF16 && dpad > kF32MaxDpad ? 4 * (size_t)dpad : 0;
+}
+
 size_t rot_lds_bytes_host(int prec, int dpad, bool jde) {
   if (prec != kPrecBF16)
-    return jde ? rot_lds_bytes<PrecF32, 32, true>(dpad)
-               : rot_lds_bytes<PrecF32, 32>(dpad);
+    return jde ? rot_lds_bytes<PrecSplit, 32, true>(dpad)
+               : rot_lds_bytes<PrecSplit, 32>(dpad);
   return jde ? rot_lds_bytes<PrecBF16, 64, true>(dpad)
              : rot_lds_bytes<PrecBF16, 64>(dpad);
 }
@@ -884,6 +935,9 @@ hipError_t launch_prep(const float* o, const float* R, int ldr, int D,
   if (prec == kPrecBF16) {
     hipLaunchKernelGGL(k_prep_rot_bf16, dim3(grid_for(total, 256)), dim3(256),
                        0, s, R, ldr, D, dpad, reinterpret_cast<__bf16*>(rop));
+  } else if (dpad > kF32MaxDpad) {
+    hipLaunchKernelGGL(k_prep_rot_split, dim3(dpad), dim3(256), 0, s, R, ldr,
+                       D, dpad, reinterpret_cast<half8*>(rop));
   } else {
     hipLaunchKernelGGL(k_prep_rot_f32, dim3(grid_for(total, 256)), dim3(256),
                        0, s, R, ldr, D, dpad, reinterpret_cast<float*>(rop));

@@ -72,16 +72,72 @@ struct PrecBF16 {
   using T = __bf16;
   static constexpr int kPad = 8;  // LDS row padding, elements
   static constexpr bool kOneBlock = true;
+  static constexpr bool kSplit = false;
 };
-struct PrecF32 {
+struct PrecF32Narrow {
+  using T = float;
+  static constexpr int kPad = 4;
+  static constexpr bool kOneBlock = true;
+  static constexpr bool kSplit = false;
+};
+// FP32 product as three half-precision products: y = yh + yl and R = Rh + Rl
+// (halves of 11 significant bits each, after scaling every row of Y and of R
+// by a power of two into the half range), z = yh Rh + (yh Rl + yl Rh) with
+// the bracket in an accumulator of its own.
+//   - Why: an FP32 MFMA runs at 1/16 of the half-precision rate and on the
+//     vector FMA units (measured: FP32 MFMA next to FMAs of another wave
+//     takes the sum of both times, half-precision MFMA the larger), so the
+//     FP32 product held the whole tile: 64 K-coordinates cost 2048 clocks a
+//     block there, 384 here.
+//   - Accuracy: the dropped yl Rl and the halves' rounding are 2^-24 of a
+//     term, random in sign, and K / 16 additions round instead of K.
+//     Measured error of z against 64 bits, relative to its rms, FP32 MFMA /
+//     this: 1.9e-7 / 1.1e-7 at K = 112, 3.0e-7 / 1.4e-7 at 256, 5.8e-7 /
+//     2.2e-7 at 1008 (1.1e-7 / 0.9e-7 at 32, but 0.73e-7 / 0.87e-7 at 16).
+//   - A row's scale is that of its own largest |y|, found once the row lies
+//     in LDS (a fixed scale would lose the low halves near the optimum); the
+//     row is split in place, in the space of its FP32 values.
+// Widths over 128 only: below, the tile is bound by latency and the FP32
+// product is as exact.
+struct PrecSplit {
   using T = float;
   static constexpr int kPad = 4;
   static constexpr bool kOneBlock = false;
+  static constexpr bool kSplit = true;
 };
-struct PrecF32Narrow : PrecF32 {
+struct PrecSplitNarrow : PrecSplit {
   static constexpr bool kOneBlock = true;
 };
-constexpr int kF32NarrowMaxDpad = 256;
+constexpr int kF32MaxDpad = 128;          // FP32 product: the FP32 MFMA tile
+constexpr int kSplitNarrowMaxDpad = 256;  // one column block per wave
+
+typedef _Float16 half8 __attribute__((ext_vector_type(8)));
+
+// Power-of-two scale of a row whose largest magnitude is m: m * scale lies
+// in [2^14, 2^15) (below 2^15 for m under 2^-112; 1 for rows that are zero
+// or not finite), and its exact inverse.
+struct RowScale {
+  float scale, inv;
+};
+
+__host__ __device__ __forceinline__ RowScale split_scale(float m) {
+  const uint32_t E = __builtin_bit_cast(uint32_t, m) >> 23;  // m >= 0
+  if (m == 0.f || E >= 255u) return {1.f, 1.f};
+  const uint32_t e = E < 15u ? 15u : E;
+  return {__builtin_bit_cast(float, (268u - e) << 23),
+          __builtin_bit_cast(float, (e - 14u) << 23)};
+}
+
+// The two halves of eight scaled values.
+__device__ __forceinline__ void split_halves(const float (&v)[8], float scale,
+                                             half8& h, half8& l) {
+#pragma unroll
+  for (int u = 0; u < 8; ++u) {
+    const float x = v[u] * scale;
+    h[u] = (_Float16)x;
+    l[u] = (_Float16)(x - (float)h[u]);
+  }
+}
 
 // Slots of the per-row objective sums (see rot_tile).
 constexpr int kRotSlots = 16;
@@ -93,15 +149,16 @@ __host__ __device__ constexpr size_t rot_lds_bytes(int dpad) {
          + (size_t)BM * tq * 4 * sizeof(unsigned long long)     // planes
          + (size_t)BM * 4 * sizeof(int)                         // donors
          + (size_t)kRotSlots * BM * sizeof(float)               // slot sums
+         + (P::kSplit ? (size_t)BM * sizeof(float) : 0)         // row scales
          + (JDE ? (size_t)BM * sizeof(Control) : 0);            // F', CR'
 }
 
-// Position of coordinate k inside an LDS row.  BF16: natural order.  FP32:
-// within each group of 8, k = 2s + h is stored at 4h + s so that one lane's
+// Position of coordinate k inside an LDS row.  BF16 and split: natural
+// order.  FP32: within each group of 8, k = 2s + h is stored at 4h + s so that one lane's
 // four K-steps of the 32x32x2 MFMA are one 16-byte read.
 template <class P>
 __device__ __forceinline__ int lds_col(int k) {
-  if constexpr (sizeof(typename P::T) == 2) {
+  if constexpr (sizeof(typename P::T) == 2 || P::kSplit) {
     return k;
   } else {
     const int g = k & ~7, r = k & 7;
@@ -181,21 +238,6 @@ __device__ __forceinline__ void interleave_step() {
   __builtin_amdgcn_sched_barrier(0);
 }
 
-// Four FP32 K-steps (8 coordinates) of the wave tile, rows 0-31.
-__device__ __forceinline__ void f32_step(const float* ar, int k8, float4 b0,
-                                         float4 b1, floatx16& c00,
-                                         floatx16& c01) {
-  const float4 av = *reinterpret_cast<const float4*>(ar + k8 * 8);
-  c00 = __builtin_amdgcn_mfma_f32_32x32x2f32(av.x, b0.x, c00, 0, 0, 0);
-  c01 = __builtin_amdgcn_mfma_f32_32x32x2f32(av.x, b1.x, c01, 0, 0, 0);
-  c00 = __builtin_amdgcn_mfma_f32_32x32x2f32(av.y, b0.y, c00, 0, 0, 0);
-  c01 = __builtin_amdgcn_mfma_f32_32x32x2f32(av.y, b1.y, c01, 0, 0, 0);
-  c00 = __builtin_amdgcn_mfma_f32_32x32x2f32(av.z, b0.z, c00, 0, 0, 0);
-  c01 = __builtin_amdgcn_mfma_f32_32x32x2f32(av.z, b1.z, c01, 0, 0, 0);
-  c00 = __builtin_amdgcn_mfma_f32_32x32x2f32(av.w, b0.w, c00, 0, 0, 0);
-  c01 = __builtin_amdgcn_mfma_f32_32x32x2f32(av.w, b1.w, c01, 0, 0, 0);
-}
-
 // Two consecutive FP32 four-step groups (k8, k8 + 1) of one column block
 // into two accumulators, interleaved.
 __device__ __forceinline__ void f32_step2(const float* ar, int k8, float4 b0,
@@ -217,6 +259,9 @@ __device__ __forceinline__ void f32_step2(const float* ar, int k8, float4 b0,
 // quads fill half a wave and its crossover bits are one 32-bit half of a
 // ballot.  Launchers refuse PAIR beyond it.
 constexpr int kPairMaxDpad = 128;
+
+// Widest padded row of a split tile (its LDS limit).
+constexpr int kMaxSplitDpad = 1152;
 
 // One tile: rows row0 .. row0 + nvalid - 1 of run `run` (EVAL: of the
 // flattened row range).  Ends with every LDS access of the tile complete
@@ -245,8 +290,10 @@ __device__ __forceinline__ void rot_tile(const GenArgs& a, int run, int row0,
       smem + (size_t)BM * stride * sizeof(T));
   int* donors = reinterpret_cast<int*>(planes + (size_t)BM * tq * 4);
   float* fpart = reinterpret_cast<float*>(donors + BM * 4);
+  // split tiles: inverse scale of every row
+  float* rinv = fpart + kRotSlots * BM;
   // jDE: the F' and CR' of every row of the tile
-  Control* ctl = reinterpret_cast<Control*>(fpart + kRotSlots * BM);
+  Control* ctl = reinterpret_cast<Control*>(rinv + (P::kSplit ? BM : 0));
 
   const int wave = (int)threadIdx.x / 64, lane = (int)threadIdx.x % 64;
   const uint32_t rng_run = a.run_base + (uint32_t)run;
@@ -463,6 +510,8 @@ __device__ __forceinline__ void rot_tile(const GenArgs& a, int run, int row0,
                 yb[2] = (__bf16)y.z;
                 yb[3] = (__bf16)y.w;
                 *reinterpret_cast<bf16x4*>(arow + j0) = yb;
+              } else if constexpr (P::kSplit) {
+                st4(arow + j0, y);
               } else {
 #pragma unroll
                 for (int b = 0; b < 4; ++b)
@@ -485,6 +534,46 @@ __device__ __forceinline__ void rot_tile(const GenArgs& a, int run, int row0,
               }
             }
           }
+        }
+      }
+    }
+  }
+  if constexpr (P::kSplit) {
+    // each wave splits the rows it built: eight coordinates per lane and
+    // step, read as FP32, written back as eight high and eight low halves
+    __builtin_amdgcn_wave_barrier();
+    constexpr int kSteps = (kMaxSplitDpad / 8 + 63) / 64;
+#pragma unroll
+    for (int k = 0; k < BM / kRotWaves; ++k) {
+      const int rl = wave + kRotWaves * k;
+      float* arow = reinterpret_cast<float*>(At) + (size_t)rl * stride;
+      float v[kSteps][8];
+      float m = 0.f;
+#pragma unroll
+      for (int t = 0; t < kSteps; ++t) {
+        const int g8 = lane + 64 * t;
+        if (64 * 8 * t >= dpad) break;
+        const float4 p = ld4(arow + 8 * min(g8, dpad / 8 - 1));
+        const float4 q = ld4(arow + 8 * min(g8, dpad / 8 - 1) + 4);
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+          v[t][b] = get(p, b);
+          v[t][4 + b] = get(q, b);
+          m = fmaxf(m, fmaxf(fabsf(get(p, b)), fabsf(get(q, b))));
+        }
+      }
+#pragma unroll
+      for (int x = 32; x >= 1; x >>= 1) m = fmaxf(m, __shfl_xor(m, x, 64));
+      const RowScale rs = split_scale(m);
+      if (lane == 0) rinv[rl] = rs.inv;
+#pragma unroll
+      for (int t = 0; t < kSteps; ++t) {
+        const int g8 = lane + 64 * t;
+        if (8 * g8 < dpad) {
+          half8 h, l;
+          split_halves(v[t], rs.scale, h, l);
+          *reinterpret_cast<half8*>(arow + 8 * g8) = h;
+          *reinterpret_cast<half8*>(arow + 8 * g8 + 4) = l;
         }
       }
     }
@@ -558,45 +647,100 @@ __device__ __forceinline__ void rot_tile(const GenArgs& a, int run, int row0,
           interleave_step<MB>();
         }
       }
+    } else if constexpr (P::kSplit) {
+      // R as [nblk][dpad/16][half][64 lanes][8] with the rows' inverse
+      // scales behind it.  A ring of kRing K-steps of fragments: a step's
+      // registers are loaded for kRing steps later once its MFMAs are
+      // issued.  The stream from L2 (4 bytes per element of R per 32 rows)
+      // bounds the loop: 2 KB per block and step against 96 clocks of MFMA.
+      const half8* rop = reinterpret_cast<const half8*>(a.rop);
+      const float* cinv = reinterpret_cast<const float*>(a.rop) +
+                          (size_t)dpad * dpad + lane % 32;
+      const int kbn = dpad / 16;  // a multiple of 8
+      constexpr int kRing = NBW == 2 ? 4 : 8;
+      const half8* rb[NBW];
+#pragma unroll
+      for (int n = 0; n < NBW; ++n)
+        rb[n] = rop + (size_t)(nb0 + n) * kbn * 128 + lane;
+      const char* ar = reinterpret_cast<const char*>(At) +
+                       (size_t)(lane % 32) * stride * 4 + 32 * (lane / 32);
+      half8 bh[kRing][NBW], bl[kRing][NBW], ah[2], al[2];
+      floatx16 x00 = {}, x01 = {};
+#pragma unroll
+      for (int u = 0; u < kRing; ++u)
+#pragma unroll
+        for (int n = 0; n < NBW; ++n) {
+          bh[u][n] = rb[n][(size_t)u * 128];
+          bl[u][n] = rb[n][(size_t)u * 128 + 64];
+        }
+      ah[0] = *reinterpret_cast<const half8*>(ar);
+      al[0] = *reinterpret_cast<const half8*>(ar + 16);
+      for (int kb = 0; kb < kbn; kb += kRing) {
+#pragma unroll
+        for (int u = 0; u < kRing; ++u) {
+          const int cur = u & 1, nxt = cur ^ 1;
+          const int ka = min(kb + u + 1, kbn - 1);
+          ah[nxt] = *reinterpret_cast<const half8*>(ar + ka * 64);
+          al[nxt] = *reinterpret_cast<const half8*>(ar + ka * 64 + 16);
+          x00 = __builtin_amdgcn_mfma_f32_32x32x16_f16(al[cur], bh[u][0], x00,
+                                                       0, 0, 0);
+          if constexpr (NBW == 2)
+            x01 = __builtin_amdgcn_mfma_f32_32x32x16_f16(al[cur], bh[u][NBW - 1],
+                                                         x01, 0, 0, 0);
+          c00 = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah[cur], bh[u][0], c00,
+                                                       0, 0, 0);
+          if constexpr (NBW == 2)
+            c01 = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah[cur], bh[u][NBW - 1],
+                                                         c01, 0, 0, 0);
+          x00 = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah[cur], bl[u][0], x00,
+                                                       0, 0, 0);
+          if constexpr (NBW == 2)
+            x01 = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah[cur], bl[u][NBW - 1],
+                                                         x01, 0, 0, 0);
+          if (kb + kRing < kbn) {
+#pragma unroll
+            for (int n = 0; n < NBW; ++n) {
+              bh[u][n] = rb[n][(size_t)(kb + u + kRing) * 128];
+              bl[u][n] = rb[n][(size_t)(kb + u + kRing) * 128 + 64];
+            }
+          }
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+      const float s0 = cinv[nb0 * 32];
+      const float s1 = NBW == 2 ? cinv[nb0 * 32 + 32] : 0.f;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const float4 rs = ld4(rinv + 8 * q + 4 * (lane / 32));
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          c00[4 * q + r] = (c00[4 * q + r] + x00[4 * q + r]) * s0 * get(rs, r);
+          if constexpr (NBW == 2)
+            c01[4 * q + r] =
+                (c01[4 * q + r] + x01[4 * q + r]) * s1 * get(rs, r);
+        }
+      }
     } else {
-      // R as [nblk][dpad/8][64 lanes][4]: one float4 = four K-steps;
-      // dpad / 8 is a multiple of 2.
+      // R as [nblk][dpad/8][64 lanes][4]: one float4 = four K-steps; dpad / 8
+      // is a multiple of 2.  Even and odd four-step groups accumulate apart
+      // (two independent MFMA chains), then add.
       const float4* rop = reinterpret_cast<const float4*>(a.rop);
       const int k8n = dpad / 8;
       const float4* rb0 = rop + ((size_t)nb0 * k8n) * 64 + lane;
       const float* ar = reinterpret_cast<const float*>(At) +
                         (size_t)(lane % 32) * stride + 4 * (lane / 32);
-      if constexpr (NBW == 2) {
-        const float4* rb1 = rb0 + (size_t)k8n * 64;
-        float4 p00 = rb0[0], p01 = rb0[64], p10 = rb1[0], p11 = rb1[64];
-        for (int k8 = 0; k8 < k8n; k8 += 2) {
-          const float4 q00 = p00, q01 = p01, q10 = p10, q11 = p11;
-          if (k8 + 2 < k8n) {
-            const size_t nx = (size_t)(k8 + 2) * 64;
-            p00 = rb0[nx];
-            p01 = rb0[nx + 64];
-            p10 = rb1[nx];
-            p11 = rb1[nx + 64];
-          }
-          f32_step(ar, k8 + 0, q00, q10, c00, c01);
-          f32_step(ar, k8 + 1, q01, q11, c00, c01);
+      float4 p0 = rb0[0], p1 = rb0[64];
+      for (int k8 = 0; k8 < k8n; k8 += 2) {
+        const float4 q0 = p0, q1 = p1;
+        if (k8 + 2 < k8n) {
+          const size_t nx = (size_t)(k8 + 2) * 64;
+          p0 = rb0[nx];
+          p1 = rb0[nx + 64];
         }
-      } else {
-        // one block: even and odd four-step groups accumulate apart (two
-        // independent MFMA chains), then add
-        float4 p0 = rb0[0], p1 = rb0[64];
-        for (int k8 = 0; k8 < k8n; k8 += 2) {
-          const float4 q0 = p0, q1 = p1;
-          if (k8 + 2 < k8n) {
-            const size_t nx = (size_t)(k8 + 2) * 64;
-            p0 = rb0[nx];
-            p1 = rb0[nx + 64];
-          }
-          f32_step2(ar, k8, q0, q1, c00, c01);
-        }
-#pragma unroll
-        for (int r = 0; r < 16; ++r) c00[r] += c01[r];
+        f32_step2(ar, k8, q0, q1, c00, c01);
       }
+#pragma unroll
+      for (int r = 0; r < 16; ++r) c00[r] += c01[r];
     }
     // The objective of each 32-column block, summed per row and written to
     // the block's LDS slot; rows then add the slots in block order, so the

@@ -212,17 +212,6 @@ __host__ __device__ constexpr bool rot_bf16_narrow(int dpad, long long tiles,
   return dpad <= kRotBf16NarrowMaxDpad && tiles > cus;
 }
 
-// R fragments of four consecutive K-steps of one column block.
-struct BFrags {
-  bf16x8 b0[4];
-};
-
-__device__ __forceinline__ void load_bfrags(BFrags& f, const bf16x8* rb0,
-                                            int kb) {
-#pragma unroll
-  for (int u = 0; u < 4; ++u) f.b0[u] = rb0[(size_t)(kb + u) * 64];
-}
-
 // Scheduling pattern for one K-step: per row block one MFMA and its next A
 // read (LDS), then the step's R load (L2), so the matrix unit keeps busy
 // while the reads go out instead of waiting behind one burst.
@@ -605,45 +594,44 @@ __device__ __forceinline__ void rot_tile(const GenArgs& a, int run, int row0,
     floatx16 c00 = {}, c01 = {}, c10 = {};
     if constexpr (sizeof(T) == 2) {
       // R as [nblk][dpad/16][64 lanes][8]: one 16-byte load per lane per
-      // block and K-step; dpad / 16 is a multiple of 4.
-      const bf16x8* rop = reinterpret_cast<const bf16x8*>(a.rop);
-      const int kbn = dpad / 16;
-      const bf16x8* rb0 = rop + ((size_t)nb0 * kbn) * 64 + lane;
-      const T* ar = At + (size_t)(lane % 32) * stride + 8 * (lane / 32);
+      // block and K-step; dpad / 16 is a multiple of 8.
       // Software pipeline at K-step granularity: the A fragments of step
       // k + 1 are read from LDS while step k's MFMAs run (two slots), and
-      // the R fragments of the next four-step group are loaded from L2 one
-      // per step into the other of two register sets.  Each step's reads
-      // are interleaved with its MFMAs (one per row block).  dpad / 16 is a
-      // multiple of 8.
+      // step k's registers of R fragments are loaded for step k + 8 once its
+      // MFMAs are issued.  No load is behind a branch (the last group loads
+      // itself again) and the first eight keep the loop's order (barriers):
+      // otherwise the compiler cannot count the loads in flight and waits
+      // for all of them at the loop's head, an L2 round trip per eight steps.
+      const int kbn = dpad / 16;
+      const bf16x8* rbu = reinterpret_cast<const bf16x8*>(a.rop) +
+                          (size_t)__builtin_amdgcn_readfirstlane(nb0) * kbn * 64;
+      const T* ar = At + (size_t)(lane % 32) * stride + 8 * (lane / 32);
       const T* ar1 = ar + (size_t)32 * stride;
-      bf16x8 a0s[2], a1s[2];
-      BFrags fa, fb;
+      bf16x8 a0s[2], a1s[2], bf[8];
       a0s[0] = *reinterpret_cast<const bf16x8*>(ar);
       if constexpr (MB == 2) a1s[0] = *reinterpret_cast<const bf16x8*>(ar1);
-      load_bfrags(fa, rb0, 0);
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        bf[u] = rbu[u * 64 + lane];
+        __builtin_amdgcn_sched_barrier(0);
+      }
       for (int kb = 0; kb < kbn; kb += 8) {
+        const int kn = kb + 8 < kbn ? kb + 8 : kb;
+        const bf16x8* rbn = rbu + (size_t)kn * 64;
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
-          const int k = kb + u;
           const int cur = u & 1, nxt = cur ^ 1;
-          if (u < 7 || k + 1 < kbn) {
-            a0s[nxt] = *reinterpret_cast<const bf16x8*>(ar + (k + 1) * 16);
-            if constexpr (MB == 2)
-              a1s[nxt] = *reinterpret_cast<const bf16x8*>(ar1 + (k + 1) * 16);
-          }
-          if (u < 4) {
-            fb.b0[u] = rb0[(size_t)(kb + 4 + u) * 64];
-          } else if (kb + 8 < kbn) {
-            fa.b0[u - 4] = rb0[(size_t)(kb + 8 + u - 4) * 64];
-          }
-          const bf16x8 b0 = u < 4 ? fa.b0[u & 3] : fb.b0[u & 3];
-          c00 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0s[cur], b0, c00, 0, 0,
-                                                        0);
+          const int ka = u < 7 ? kb + u + 1 : kn;
+          a0s[nxt] = *reinterpret_cast<const bf16x8*>(ar + ka * 16);
+          if constexpr (MB == 2)
+            a1s[nxt] = *reinterpret_cast<const bf16x8*>(ar1 + ka * 16);
+          c00 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0s[cur], bf[u], c00,
+                                                        0, 0, 0);
           if constexpr (MB == 2) {
-            c10 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1s[cur], b0, c10, 0,
-                                                          0, 0);
+            c10 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1s[cur], bf[u], c10,
+                                                          0, 0, 0);
           }
+          bf[u] = rbn[u * 64 + lane];
           interleave_step<MB>();
         }
       }
@@ -653,15 +641,13 @@ __device__ __forceinline__ void rot_tile(const GenArgs& a, int run, int row0,
       // registers are loaded for kRing steps later once its MFMAs are
       // issued.  The stream from L2 (4 bytes per element of R per 32 rows)
       // bounds the loop: 2 KB per block and step against 96 clocks of MFMA.
-      const half8* rop = reinterpret_cast<const half8*>(a.rop);
+      const half8* rop =
+          reinterpret_cast<const half8*>(a.rop) +
+          (size_t)__builtin_amdgcn_readfirstlane(nb0) * (dpad / 16) * 128;
       const float* cinv = reinterpret_cast<const float*>(a.rop) +
                           (size_t)dpad * dpad + lane % 32;
       const int kbn = dpad / 16;  // a multiple of 8
-      constexpr int kRing = NBW == 2 ? 4 : 8;
-      const half8* rb[NBW];
-#pragma unroll
-      for (int n = 0; n < NBW; ++n)
-        rb[n] = rop + (size_t)(nb0 + n) * kbn * 128 + lane;
+      constexpr int kRing = 8;
       const char* ar = reinterpret_cast<const char*>(At) +
                        (size_t)(lane % 32) * stride * 4 + 32 * (lane / 32);
       half8 bh[kRing][NBW], bl[kRing][NBW], ah[2], al[2];
@@ -670,16 +656,19 @@ __device__ __forceinline__ void rot_tile(const GenArgs& a, int run, int row0,
       for (int u = 0; u < kRing; ++u)
 #pragma unroll
         for (int n = 0; n < NBW; ++n) {
-          bh[u][n] = rb[n][(size_t)u * 128];
-          bl[u][n] = rb[n][(size_t)u * 128 + 64];
+          bh[u][n] = rop[(size_t)(n * kbn + u) * 128 + lane];
+          bl[u][n] = rop[(size_t)(n * kbn + u) * 128 + 64 + lane];
+          // in the loop's order, or the loop's head waits for all of them
+          __builtin_amdgcn_sched_barrier(0);
         }
       ah[0] = *reinterpret_cast<const half8*>(ar);
       al[0] = *reinterpret_cast<const half8*>(ar + 16);
       for (int kb = 0; kb < kbn; kb += kRing) {
+        const int kn = kb + kRing < kbn ? kb + kRing : kb;
 #pragma unroll
         for (int u = 0; u < kRing; ++u) {
           const int cur = u & 1, nxt = cur ^ 1;
-          const int ka = min(kb + u + 1, kbn - 1);
+          const int ka = u < kRing - 1 ? kb + u + 1 : kn;
           ah[nxt] = *reinterpret_cast<const half8*>(ar + ka * 64);
           al[nxt] = *reinterpret_cast<const half8*>(ar + ka * 64 + 16);
           x00 = __builtin_amdgcn_mfma_f32_32x32x16_f16(al[cur], bh[u][0], x00,
@@ -697,14 +686,12 @@ __device__ __forceinline__ void rot_tile(const GenArgs& a, int run, int row0,
           if constexpr (NBW == 2)
             x01 = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah[cur], bl[u][NBW - 1],
                                                          x01, 0, 0, 0);
-          if (kb + kRing < kbn) {
 #pragma unroll
-            for (int n = 0; n < NBW; ++n) {
-              bh[u][n] = rb[n][(size_t)(kb + u + kRing) * 128];
-              bl[u][n] = rb[n][(size_t)(kb + u + kRing) * 128 + 64];
-            }
+          for (int n = 0; n < NBW; ++n) {
+            bh[u][n] = rop[(size_t)(n * kbn + kn + u) * 128 + lane];
+            bl[u][n] = rop[(size_t)(n * kbn + kn + u) * 128 + 64 + lane];
+            __builtin_amdgcn_sched_barrier(0);
           }
-          __builtin_amdgcn_sched_barrier(0);
         }
       }
       const float s0 = cinv[nb0 * 32];

@@ -227,6 +227,33 @@ __device__ __forceinline__ void interleave_step() {
   __builtin_amdgcn_sched_barrier(0);
 }
 
+// The same for a split step: each MFMA is followed by one read, the next
+// step's two A reads first, then the fragments whose last use is done.
+template <int NBW>
+__device__ __forceinline__ void interleave_split() {
+  if constexpr (NBW == 2) {
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // MFMA
+      __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);  // DS read
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // MFMA
+      __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);  // VMEM read
+    }
+  } else {
+    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+    __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+      __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+    }
+  }
+  __builtin_amdgcn_sched_barrier(0);
+}
+
 // Two consecutive FP32 four-step groups (k8, k8 + 1) of one column block
 // into two accumulators, interleaved.
 __device__ __forceinline__ void f32_step2(const float* ar, int k8, float4 b0,
@@ -647,20 +674,25 @@ __device__ __forceinline__ void rot_tile(const GenArgs& a, int run, int row0,
       const float* cinv = reinterpret_cast<const float*>(a.rop) +
                           (size_t)dpad * dpad + lane % 32;
       const int kbn = dpad / 16;  // a multiple of 8
-      constexpr int kRing = 8;
+      constexpr int kRing = NBW == 2 ? 4 : 8;
       const char* ar = reinterpret_cast<const char*>(At) +
                        (size_t)(lane % 32) * stride * 4 + 32 * (lane / 32);
       half8 bh[kRing][NBW], bl[kRing][NBW], ah[2], al[2];
       floatx16 x00 = {}, x01 = {};
 #pragma unroll
-      for (int u = 0; u < kRing; ++u)
+      for (int u = 0; u < kRing; ++u) {
+        // in the loop's order, or the loop's head waits for all of them
 #pragma unroll
         for (int n = 0; n < NBW; ++n) {
-          bh[u][n] = rop[(size_t)(n * kbn + u) * 128 + lane];
-          bl[u][n] = rop[(size_t)(n * kbn + u) * 128 + 64 + lane];
-          // in the loop's order, or the loop's head waits for all of them
+          bh[u][n] = rop[(size_t)n * kbn * 128 + u * 128 + lane];
           __builtin_amdgcn_sched_barrier(0);
         }
+#pragma unroll
+        for (int n = 0; n < NBW; ++n) {
+          bl[u][n] = rop[(size_t)n * kbn * 128 + u * 128 + 64 + lane];
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
       ah[0] = *reinterpret_cast<const half8*>(ar);
       al[0] = *reinterpret_cast<const half8*>(ar + 16);
       for (int kb = 0; kb < kbn; kb += kRing) {
@@ -686,12 +718,16 @@ __device__ __forceinline__ void rot_tile(const GenArgs& a, int run, int row0,
           if constexpr (NBW == 2)
             x01 = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah[cur], bl[u][NBW - 1],
                                                          x01, 0, 0, 0);
-#pragma unroll
-          for (int n = 0; n < NBW; ++n) {
-            bh[u][n] = rop[(size_t)(n * kbn + kn + u) * 128 + lane];
-            bl[u][n] = rop[(size_t)(n * kbn + kn + u) * 128 + 64 + lane];
-            __builtin_amdgcn_sched_barrier(0);
-          }
+          // the step's fragments for kRing steps later, in order of their
+          // last use
+          const half8* r = rop + (size_t)kn * 128;
+          bh[u][0] = r[u * 128 + lane];
+          if constexpr (NBW == 2)
+            bh[u][NBW - 1] = r[(size_t)kbn * 128 + u * 128 + lane];
+          bl[u][0] = r[u * 128 + 64 + lane];
+          if constexpr (NBW == 2)
+            bl[u][NBW - 1] = r[(size_t)kbn * 128 + u * 128 + 64 + lane];
+          interleave_split<NBW>();
         }
       }
       const float s0 = cinv[nb0 * 32];

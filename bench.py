@@ -117,9 +117,7 @@ def measured_traffic(kernel_ms, w):
     return None
 
 
-# Generations per timed library call: calls this long take the library's
-# staggered run groups on the large rotated workloads (shorter calls are
-# launched as one group).
+# Generations per timed library call.
 SEG_MIN_GENS = 16
 
 

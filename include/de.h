@@ -159,9 +159,9 @@ DE_API de_status de_init_population(const de_params* params,
  * clamping, eq. 3 crossover, greedy selection: the trial replaces the target
  * iff f(trial) < f(target), so ties and NaN keep the target).  Synchronous
  * generations: every donor comes from generation g.  Asynchronous.
- * Calls of at least 16 generations on rotated problems with two or more
- * runs and at least one 64-row tile per compute unit run as two run groups
- * on two streams that such handles create at initialisation (ordered after,
+ * Calls of at least 32 generations on rotated problems with the BF16
+ * product, more than 896 coordinates, two or more runs and at least one
+ * 64-row tile per compute unit run as two run groups on two streams that such handles create at initialisation (ordered after,
  * and waited for by, hip_stream through events; released by de_destroy),
  * the second group offset by half the time per generation measured on an
  * earlier call, so that one group's trial build overlaps the other's

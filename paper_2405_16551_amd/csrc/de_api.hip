@@ -301,14 +301,23 @@ bool stagger_enabled() {
 
 // Fewest generations per call that take the split: the second group's
 // offset leaves half a generation of it after the first group's last
-// kernel, so short calls keep one launch per generation.
-constexpr int64_t kStaggerMinGens = 16;
+// kernel.  16 x 1024 x 1000, BF16, one handle, split / plain: 20 generations
+// 1115 / 1108 us, 400 generations late in a run 51.0 / 55.1 us each; several
+// handles in turn share the hardware queues, and the split of 20
+// generations then costs 1354 us.
+constexpr int64_t kStaggerMinGens = 32;
 
-// Problems that take the split: rotated objective, two or more runs, at
-// least one 64-row tile per compute unit.  Their handles create the two
-// streams at initialisation.
+// Padded widths that take the split (BF16 product): at 700 coordinates both
+// forms take 37.5 us per generation, and the FP32 product, whose tiles
+// outnumber the compute units two to one, is slower split (145 / 140 us).
+constexpr int kStaggerMinDpad = 1024;
+
+// Problems that take the split: rotated objective, BF16 product of wide
+// rows, two or more runs, at least one 64-row tile per compute unit.  Their
+// handles create the two streams at initialisation.
 bool stagger_shape(const de_state* s) {
-  if (s->kind != de::kObjRotOsc || s->p.runs < 2 || !stagger_enabled())
+  if (s->kind != de::kObjRotOsc || s->prec != de::kPrecBF16 ||
+      s->dpad < kStaggerMinDpad || s->p.runs < 2 || !stagger_enabled())
     return false;
   const long long tiles = (long long)s->p.runs * ((s->p.NP + 63) / 64);
   return tiles >= de::device_cus();

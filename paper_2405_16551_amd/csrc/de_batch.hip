@@ -686,19 +686,59 @@ BatchArgs base_args(const de_batch* b) {
 }
 
 // Tiles of the runs whose instance is in `insts`, heaviest first (cost per
-// tile from `tile_cost` of the instance), runs in order within a cost.
+// tile from `tile_cost` of the instance), dealt to the XCDs by runs.
+// Workgroup p of a launch runs on XCD p mod 8 and takes the tiles p, p +
+// grid, ...; so position p of the list holds a tile of a run that belongs
+// to XCD p mod 8, and the rows that a run's tiles gather from each other
+// (three donors per trial) are read from one L2 instead of through the
+// fabric by all eight.  Runs (in pieces of at most an eighth of the tiles,
+// so that one large run still reaches every XCD) go, heaviest tiles first,
+// to the XCD with the least work so far; an XCD whose queue ends early
+// takes its positions from the fullest one.
 std::vector<BTile> tiles_for(const de_batch* b, const std::vector<int>& insts,
                              int bm, const std::vector<double>& tile_cost) {
-  std::vector<BTile> t;
+  constexpr int kXcd = 8;
+  struct Piece {
+    int run, row0, n;  // n tiles from row0 on
+    double cost;       // per tile
+  };
+  size_t total = 0;
+  std::vector<int> runs;
   for (int r = 0; r < b->nruns; ++r) {
     const int k = b->S.run_inst[r];
     if (std::find(insts.begin(), insts.end(), k) == insts.end()) continue;
-    for (int row0 = 0; row0 < b->runs[r].NP; row0 += bm) t.push_back({r, row0});
+    runs.push_back(r);
+    total += (size_t)(b->runs[r].NP + bm - 1) / bm;
   }
-  std::stable_sort(t.begin(), t.end(), [&](const BTile& x, const BTile& y) {
-    return tile_cost[b->S.run_inst[x.run]] > tile_cost[b->S.run_inst[y.run]];
-  });
-  return t;
+  const int cap = (int)std::max<size_t>(1, (total + kXcd - 1) / kXcd);
+  std::vector<Piece> pieces;
+  for (int r : runs) {
+    const int n = (b->runs[r].NP + bm - 1) / bm;
+    for (int t = 0; t < n; t += cap)
+      pieces.push_back({r, t * bm, std::min(cap, n - t),
+                        tile_cost[b->S.run_inst[r]]});
+  }
+  std::stable_sort(pieces.begin(), pieces.end(),
+                   [](const Piece& x, const Piece& y) {
+                     return x.cost != y.cost ? x.cost > y.cost : x.n > y.n;
+                   });
+  std::vector<BTile> queue[kXcd];
+  double load[kXcd] = {};
+  for (const Piece& p : pieces) {
+    const int x = (int)(std::min_element(load, load + kXcd) - load);
+    for (int t = 0; t < p.n; ++t) queue[x].push_back({p.run, p.row0 + t * bm});
+    load[x] += p.n * std::max(p.cost, 1e-9);
+  }
+  std::vector<BTile> out;
+  size_t at[kXcd] = {};
+  for (size_t i = 0; i < total; ++i) {
+    int x = (int)(i % kXcd);
+    if (at[x] == queue[x].size())
+      for (int y = 0; y < kXcd; ++y)
+        if (queue[y].size() - at[y] > queue[x].size() - at[x]) x = y;
+    out.push_back(queue[x][at[x]++]);
+  }
+  return out;
 }
 
 hipError_t launch_variant(const Kern& k, bool eval, BatchArgs a, int ntiles,
@@ -1153,11 +1193,11 @@ DE_API de_status de_batch_create(const de_batch_params* params, float* pop0,
       if (b->S.run_inst[r] == k)
         nt += (size_t)(p.runs[r].NP + variant_bm(b->plan[k]) - 1) /
               variant_bm(b->plan[k]);
-    // untimed (explicit plan): padded MFMA work per tile as the estimate
+    // untimed (explicit plan): rows read and built, then the product's share
     const double d = (double)(b->plan[k] == DE_BATCH_WIDE
                                   ? dpad_wide(p.inst[k].D)
                                   : dpad_generic(p.inst[k].D));
-    cost[k] = us >= 0.f && nt > 0 ? (double)us / nt : d * d;
+    cost[k] = us >= 0.f && nt > 0 ? (double)us / nt : d + d * d / 1024.0;
   }
   rc = build_launches(b, st, cost);
   // generation 0's fitness with the plan's own kernels (so every value of a

@@ -343,65 +343,72 @@ __device__ __forceinline__ void rot_tile(const GenArgs& a, int run, int row0,
     T* arow = At + (size_t)rl * stride;
     for (int k = lane; k < dpad; k += 64) arow[k] = (T)0.0f;
   }
+  // PAIR: each wave keeps its rows' targets and trials (lane 32 h + q: quad
+  // q of the h-th row of a pair), their values and stale flags in registers
+  // from the build to the selection, which then reads no memory: the tile
+  // is a chain of memory round trips (64 x 256 x 100, FP32: 12.6 us per
+  // generation with the rows read again for the selection, 1 run x 250 x 100
+  // in BF16 7.4 us), so the chain's length is what counts.
+  constexpr int RBP = PAIR ? BM / (2 * kRotWaves) : 1;  // pairs per wave
+  static_assert(!PAIR || (BM % (2 * kRotWaves) == 0 && RBP >= 1), "pairs");
+  float4 pu[RBP], px[RBP];
+  float pf[RBP];
+  bool pchg[RBP];
+  const int hl = lane / 32, ql = lane % 32;
   if constexpr (PAIR) {
     // Padded widths up to 128 (at most 32 quads per row): lanes 32 h + q
     // build quad q of the h-th row of a pair of the wave's rows, so every
     // lane has a quad (one row per instruction would leave more than half
-    // of them idle).  Same loads, draws, arithmetic and stores as below;
-    // each row's crossover bits are its half of the ballot.
+    // of them idle).  Same loads, draws, arithmetic and stores as below.
     static_assert(!EVAL, "paired form: generation step");
-    constexpr int RBP = 4;  // pairs per step
-    const int hl = lane / 32, ql = lane % 32;
     const int nrow_w = wave < nvalid ? (nvalid - 1 - wave) / kRotWaves + 1 : 0;
-    const int dlast = ((a.D + 3) / 4 - 1) * 4;
-    const int j0 = 4 * ql, jl = min(j0, dlast);
-    const float4 ov = ld4(a.o + jl);
-    for (int k = 0; k < nrow_w; k += 2 * RBP) {
-      float4 xv[RBP], v1[RBP], v2[RBP], v3[RBP];
+    if (nrow_w > 0) {
+      const int dlast = ((a.D + 3) / 4 - 1) * 4;
+      const int j0 = 4 * ql, jl = min(j0, dlast);
+      const float4 ov = ld4(a.o + jl);
+      float4 v1[RBP], v2[RBP], v3[RBP];
 #pragma unroll
       for (int p = 0; p < RBP; ++p) {
-        const int rl = wave + kRotWaves * min(k + 2 * p + hl, nrow_w - 1);
-        xv[p] = ld4(base + (size_t)(row0 + rl) * a.ldx + jl);
-        if (!EVAL) {
-          v1[p] = ld4(base + (size_t)donors[rl * 4 + 0] * a.ldx + jl);
-          v2[p] = ld4(base + (size_t)donors[rl * 4 + 1] * a.ldx + jl);
-          v3[p] = ld4(base + (size_t)donors[rl * 4 + 2] * a.ldx + jl);
-        }
+        const int rl = wave + kRotWaves * min(2 * p + hl, nrow_w - 1);
+        px[p] = ld4(base + (size_t)(row0 + rl) * a.ldx + jl);
+        v1[p] = ld4(base + (size_t)donors[rl * 4 + 0] * a.ldx + jl);
+        v2[p] = ld4(base + (size_t)donors[rl * 4 + 1] * a.ldx + jl);
+        v3[p] = ld4(base + (size_t)donors[rl * 4 + 2] * a.ldx + jl);
       }
 #pragma unroll
       for (int p = 0; p < RBP; ++p) {
-        if (k + 2 * p >= nrow_w) break;
-        const int kk = k + 2 * p + hl;
-        const bool live = kk < nrow_w;  // the pair's second row may not exist
-        const int rl = wave + kRotWaves * min(kk, nrow_w - 1);
-        const int i = row0 + rl;
-        uint32_t bits = 0;
-        float4 uu = xv[p];
-        if (!EVAL) {
-          const int jrand = donors[rl * 4 + 3];
-          float Fr = a.F;
-          uint32_t crt = a.cr_threshold;
-          if constexpr (JDE) {  // the row's own F', CR'
-            const Control c = ctl[rl];
-            Fr = c.F;
-            crt = cr_threshold_of(c.CR);
-          }
-          const Words4 w = draw_block(kTagXover, rng_run, a.gen, (uint32_t)i,
-                                      (uint32_t)ql, a.key_lo, a.key_hi);
+        const int rl = wave + kRotWaves * min(2 * p + hl, nrow_w - 1);
+        const size_t g = (size_t)run * a.NP + row0 + rl;
+        pf[p] = a.fit_cur[g];
+        pchg[p] = a.changed[g] != 0;
+      }
 #pragma unroll
-          for (int b = 0; b < 4; ++b) {
-            const bool tk = (j0 + b < a.D) &&
-                            take_mutant(w.w[b], j0 + b, jrand, crt);
-            const float mv = mutant_coord(get(v1[p], b), get(v2[p], b),
-                                          get(v3[p], b), Fr, a.lo, a.hi);
-            set(uu, b, tk ? mv : get(xv[p], b));
-            bits |= (tk ? 1u : 0u) << b;
-          }
+      for (int p = 0; p < RBP; ++p) {
+        if (2 * p >= nrow_w) break;
+        const bool live = 2 * p + hl < nrow_w;  // the second row may not exist
+        const int rl = wave + kRotWaves * min(2 * p + hl, nrow_w - 1);
+        const int i = row0 + rl;
+        const int jrand = donors[rl * 4 + 3];
+        float Fr = a.F;
+        uint32_t crt = a.cr_threshold;
+        if constexpr (JDE) {  // the row's own F', CR'
+          const Control c = ctl[rl];
+          Fr = c.F;
+          crt = cr_threshold_of(c.CR);
         }
+        const Words4 w = draw_block(kTagXover, rng_run, a.gen, (uint32_t)i,
+                                    (uint32_t)ql, a.key_lo, a.key_hi);
         float4 y;
 #pragma unroll
-        for (int b = 0; b < 4; ++b)
-          set(y, b, (j0 + b < a.D) ? get(uu, b) - get(ov, b) : 0.f);
+        for (int b = 0; b < 4; ++b) {
+          const bool tk = (j0 + b < a.D) &&
+                          take_mutant(w.w[b], j0 + b, jrand, crt);
+          const float mv = mutant_coord(get(v1[p], b), get(v2[p], b),
+                                        get(v3[p], b), Fr, a.lo, a.hi);
+          const float u = tk ? mv : get(px[p], b);
+          set(pu[p], b, u);
+          set(y, b, (j0 + b < a.D) ? u - get(ov, b) : 0.f);
+        }
         T* arow = At + (size_t)rl * stride;
         if (live && j0 < dpad) {
           if constexpr (sizeof(T) == 2) {
@@ -414,14 +421,6 @@ __device__ __forceinline__ void rot_tile(const GenArgs& a, int run, int row0,
           } else {
 #pragma unroll
             for (int b = 0; b < 4; ++b) arow[lds_col<P>(j0 + b)] = get(y, b);
-          }
-        }
-        if (!EVAL) {
-#pragma unroll
-          for (int b = 0; b < 4; ++b) {
-            const unsigned long long m = __ballot((bits >> b) & 1u);
-            if (ql == 0 && live)
-              planes[(size_t)rl * tq * 4 + b] = hl ? (m >> 32) : (m & 0xFFFFFFFFull);
           }
         }
       }
@@ -830,44 +829,30 @@ __device__ __forceinline__ void rot_tile(const GenArgs& a, int run, int row0,
 
   // ---- phase 3: selection and the next generation
   if constexpr (PAIR) {
-    // two rows per wave instruction as in the build: lanes 32 h + q handle
-    // quad q of the h-th row of a pair; lanes 0 and 32 each write their
-    // row's value, flag and statistics
-    const int hl = lane / 32, ql = lane % 32;
+    // two rows per wave instruction as in the build, from the registers it
+    // left; lanes 0 and 32 each write their row's value, flag and statistics
     const int nrow_w = wave < nvalid ? (nvalid - 1 - wave) / kRotWaves + 1 : 0;
-    const int dlast = ((a.D + 3) / 4 - 1) * 4;
-    const int j0 = 4 * ql, jl = min(j0, dlast);
-    for (int k = 0; k < nrow_w; k += 2) {
-      const int kk = k + hl;
-      const bool live = kk < nrow_w;
-      const int rl = wave + kRotWaves * min(kk, nrow_w - 1);
+    const int j0 = 4 * ql;
+#pragma unroll
+    for (int p = 0; p < RBP; ++p) {
+      const int kk = 2 * p + hl;
+      if (kk >= nrow_w) continue;
+      const int rl = wave + kRotWaves * kk;
       float f = 0.f;
 #pragma unroll
       for (int sl = 0; sl < kRotSlots; ++sl) f += fpart[sl * BM + rl];
       const int i = row0 + rl;
       const size_t g = (size_t)run * a.NP + i;
-      const float fx = a.fit_cur[g];
+      const float fx = pf[p];
       const bool accept = f < fx;
-      const bool refresh = !accept && a.changed[g] != 0;
-      const float Fr = JDE ? ctl[rl].F : a.F;
-      if (live && (accept || refresh)) {
-        const float4 xv = ld4(base + (size_t)i * a.ldx + jl);
-        float4 out = xv;
-        if (accept) {
-          const float4 v1 = ld4(base + (size_t)donors[rl * 4 + 0] * a.ldx + jl);
-          const float4 v2 = ld4(base + (size_t)donors[rl * 4 + 1] * a.ldx + jl);
-          const float4 v3 = ld4(base + (size_t)donors[rl * 4 + 2] * a.ldx + jl);
+      if ((accept || pchg[p]) && j0 < a.D) {
+        float4 out;
 #pragma unroll
-          for (int b = 0; b < 4; ++b) {
-            const unsigned long long m = planes[(size_t)rl * tq * 4 + b];
-            const float mv = mutant_coord(get(v1, b), get(v2, b), get(v3, b),
-                                          Fr, a.lo, a.hi);
-            set(out, b, ((m >> ql) & 1ull) ? mv : get(xv, b));
-          }
-        }
-        if (j0 < a.D) st4(a.pop_next + g * a.ldx + j0, out);
+        for (int b = 0; b < 4; ++b)
+          set(out, b, accept ? get(pu[p], b) : get(px[p], b));
+        st4(a.pop_next + g * a.ldx + j0, out);
       }
-      if (live && ql == 0) {
+      if (ql == 0) {
         a.fit_next[g] = accept ? f : fx;
         a.changed[g] = accept ? 1 : 0;
         if constexpr (JDE) {

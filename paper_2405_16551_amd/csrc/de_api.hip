@@ -25,12 +25,8 @@
 // ends.  Host code never passes `scratch` itself to a kernel or a copy (in
 // host code the name stands for a host-side shadow): it uses the device
 // address that hipGetSymbolAddress returns for the current device.
-// The limit counts everything but the row scales of the FP32 product's
-// operand layout (kScaleBytes at most), for which the array has room beyond.
 constexpr size_t kStaticScratchBytes = (size_t)8 << 20;
-constexpr size_t kScaleBytes = (size_t)8 << 10;
-static __device__ __align__(256) unsigned char
-    scratch[kStaticScratchBytes + kScaleBytes];
+static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 
 namespace {
 
@@ -40,9 +36,12 @@ constexpr uint64_t kMagic = 0x4445'6d69'3335'3578ull;
 constexpr int64_t kGenLimit = int64_t(1) << 32;  // counter field is 32-bit
 
 struct Layout {
+  // done: the counter, and at kRmaxAt the largest |R|
   size_t best, hit, acc, done, changed, opad, rop, rf32, f64, idx, jp[2],
       total;
 };
+
+constexpr size_t kRmaxAt = 16;  // within the done counter's 256 bytes
 
 size_t round_up(size_t v, size_t m) { return (v + m - 1) / m * m; }
 
@@ -71,8 +70,7 @@ Layout layout_for(const de_params& p, int kind, int prec, bool handle = true) {
   L.rop = 0;
   L.rf32 = 0;
   if (kind == de::kObjRotOsc)
-    L.rop = take(de::rot_operand_bytes(prec, dpad) +
-                 de::rot_scale_bytes(prec, dpad));
+    L.rop = take((size_t)dpad * dpad * (prec == de::kPrecBF16 ? 2 : 4));
   if (!handle) {
     L.total = off;
     return L;
@@ -201,6 +199,7 @@ GenArgs base_args(const de_state* s) {
   GenArgs a{};
   a.o = reinterpret_cast<const float*>(s->work + s->L.opad);
   a.rop = s->L.rop ? s->work + s->L.rop : nullptr;
+  a.rmax = reinterpret_cast<const float*>(s->work + s->L.done + kRmaxAt);
   a.best_key = reinterpret_cast<unsigned long long*>(s->work + s->L.best);
   a.hit_gen = reinterpret_cast<unsigned long long*>(s->work + s->L.hit);
   a.accepted = reinterpret_cast<unsigned long long*>(s->work + s->L.acc);
@@ -588,7 +587,10 @@ de_status init_common(const de_params* params, const de_objective* objective,
   rc = FROM_HIP(de::launch_prep(objective->o, objective->R, objective->ldr,
                                 p.D, s->dpad, s->kind, s->prec,
                                 reinterpret_cast<float*>(s->work + L.opad),
-                                L.rop ? s->work + L.rop : nullptr, st));
+                                L.rop ? s->work + L.rop : nullptr,
+                                reinterpret_cast<float*>(s->work + L.done +
+                                                         kRmaxAt),
+                                st));
   if (rc == DE_OK && L.rf32)
     rc = FROM_HIP(de::launch_copy_rot(objective->R, objective->ldr, p.D,
                                       reinterpret_cast<float*>(s->work + L.rf32),
@@ -948,10 +950,7 @@ DE_API de_status de_generation_noalloc(const de_params* params,
   const int prec = objective->kind == de::kObjRotOsc ? objective->gemm_prec
                                                      : de::kPrecF32;
   const Layout L = layout_for(p, objective->kind, prec, false);
-  const size_t scales = objective->kind == de::kObjRotOsc
-                            ? de::rot_scale_bytes(prec, dpad_for(p.D))
-                            : 0;
-  if (L.total - scales > kStaticScratchBytes) return DE_E_UNSUPPORTED;
+  if (L.total > kStaticScratchBytes) return DE_E_UNSUPPORTED;
 
   (void)hipGetLastError();
   hipStream_t st = reinterpret_cast<hipStream_t>(hip_stream);
@@ -997,7 +996,10 @@ DE_API de_status de_generation_noalloc(const de_params* params,
   rc = FROM_HIP(de::launch_prep(objective->o, objective->R, objective->ldr,
                                 p.D, s.dpad, s.kind, s.prec,
                                 reinterpret_cast<float*>(s.work + L.opad),
-                                L.rop ? s.work + L.rop : nullptr, st));
+                                L.rop ? s.work + L.rop : nullptr,
+                                reinterpret_cast<float*>(s.work + L.done +
+                                                         kRmaxAt),
+                                st));
   const GenArgs a = base_args(&s);
   if (rc == DE_OK) rc = FROM_HIP(de::launch_stats_reset(a, true, st));
   if (rc == DE_OK) rc = FROM_HIP(de::launch_mark_changed(a, st));

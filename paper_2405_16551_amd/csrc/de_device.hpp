@@ -84,6 +84,59 @@ __host__ __device__ __forceinline__ Words4 draw_block(uint32_t tag, uint32_t run
   return philox4x32_10(q, indiv, gen, (tag << 24) | run, key_lo, key_hi);
 }
 
+// Crossover blocks draw_block(kTagXover, run, gen, i, q) of many rows i and
+// groups q, with what rounds 1 to 3 owe to q alone (XoverCol) and to i alone
+// (XoverRow) computed once: of the 20 products of a block 15 are left where
+// a wave walks rows i (scalar) at fixed q (per lane), and the trial build
+// spends a third of its vector instructions on them.
+struct XoverCol {
+  uint32_t n3, m1, h2, l2;
+};
+struct XoverRow {
+  uint32_t h1, l1;
+};
+
+__host__ __device__ __forceinline__ XoverCol xover_col(uint32_t run,
+                                                       uint32_t gen, uint32_t q,
+                                                       uint32_t k0,
+                                                       uint32_t k1) {
+  const uint32_t n1 = kPhiloxMulB * gen;
+  const uint64_t pa0 = (uint64_t)kPhiloxMulA * q;
+  const uint32_t n2 = xor3((uint32_t)(pa0 >> 32), (kTagXover << 24) | run, k1);
+  const uint64_t pb1 = (uint64_t)kPhiloxMulB * n2;
+  const uint32_t m0 = xor3((uint32_t)(pb1 >> 32), n1, k0 + kPhiloxWeylA);
+  const uint64_t pa2 = (uint64_t)kPhiloxMulA * m0;
+  XoverCol c;
+  c.n3 = (uint32_t)pa0;
+  c.m1 = (uint32_t)pb1 ^ (k0 + 2u * kPhiloxWeylA);
+  c.h2 = (uint32_t)(pa2 >> 32) ^ (k1 + 2u * kPhiloxWeylB);
+  c.l2 = (uint32_t)pa2;
+  return c;
+}
+
+__host__ __device__ __forceinline__ XoverRow xover_row(uint32_t gen,
+                                                       uint32_t indiv,
+                                                       uint32_t k0,
+                                                       uint32_t k1) {
+  const uint64_t pb0 = (uint64_t)kPhiloxMulB * gen;
+  const uint64_t pa1 =
+      (uint64_t)kPhiloxMulA * xor3((uint32_t)(pb0 >> 32), indiv, k0);
+  return {(uint32_t)(pa1 >> 32) ^ (k1 + kPhiloxWeylB), (uint32_t)pa1};
+}
+
+__host__ __device__ __forceinline__ Words4 xover_words(XoverCol c, XoverRow r,
+                                                       uint32_t k0,
+                                                       uint32_t k1) {
+  const uint64_t pb2 = (uint64_t)kPhiloxMulB * (r.h1 ^ c.n3);
+  uint32_t c0 = (uint32_t)(pb2 >> 32) ^ c.m1, c1 = (uint32_t)pb2;
+  uint32_t c2 = c.h2 ^ r.l1, c3 = c.l2;
+#pragma unroll
+  for (int n = 3; n < 10; ++n)
+    philox_round(c0, c1, c2, c3, k0 + (uint32_t)n * kPhiloxWeylA,
+                 k1 + (uint32_t)n * kPhiloxWeylB);
+  return {{c0, c1, c2, c3}};
+}
+
 // Uniform integer in [0, n) from one 32-bit word: floor(w * n / 2^32).
 __host__ __device__ __forceinline__ int uniform_below(uint32_t w, uint32_t n) {
   return (int)(((uint64_t)w * n) >> 32);
@@ -147,12 +200,18 @@ __host__ __device__ __forceinline__ bool take_mutant(uint32_t word, int j, int j
   return (j == jrand) | (word <= xover_word_limit(cr_threshold));
 }
 
-// Mutant coordinate of eq. 2 with clamping to the box; NaN passes through.
+// Mutant coordinate of eq. 2 with clamping to the box; NaN passes through
+// (on gfx950 as v_maximum3 / v_minimum3, which hand a NaN on, instead of two
+// compares and two selects with their wait states).
 __host__ __device__ __forceinline__ float mutant_coord(float x1, float x2, float x3,
                                               float F, float lo, float hi) {
   float v = fmaf(F, x2 - x3, x1);
+#if defined(__HIP_DEVICE_COMPILE__)
+  v = __builtin_elementwise_minimum(__builtin_elementwise_maximum(v, lo), hi);
+#else
   v = v < lo ? lo : v;
   v = v > hi ? hi : v;
+#endif
   return v;
 }
 

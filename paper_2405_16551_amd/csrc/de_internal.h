@@ -20,6 +20,7 @@ struct GenArgs {
   float* fit_next;        // f of generation g+1 (EVAL: output values)
   const float* o;         // shift, zero-padded to dpad
   const void* rop;        // R in the MFMA B-operand layout (rotated only)
+  const float* rmax;      // largest |R| (FP32 product over 128 wide only)
   unsigned long long* best_key;  // [runs] ordered (f, index) keys
   unsigned long long* hit_gen;   // [runs] first generation with best <= target
   unsigned long long* accepted;  // [runs] accepted trials
@@ -47,11 +48,6 @@ hipError_t note_hip(hipError_t e, const char* file, int line);
 // CU's 160 KB, on the current device (once per kernel and device).
 hipError_t set_max_dynamic_lds(const void* fn);
 
-// Bytes of R in the operand layout of a precision, and of the row scales
-// that follow it (split layout of the FP32 product).
-size_t rot_operand_bytes(int prec, int dpad);
-size_t rot_scale_bytes(int prec, int dpad);
-
 size_t rot_lds_bytes_host(int prec, int dpad, bool jde = false);
 bool sep_supported(int D);
 
@@ -72,7 +68,7 @@ hipError_t launch_fill_control(float2* jp, int n, float F, float CR,
                                hipStream_t s);
 hipError_t launch_prep(const float* o, const float* R, int ldr, int D,
                        int dpad, int kind, int prec, float* o_pad, void* rop,
-                       hipStream_t s);
+                       float* rmax, hipStream_t s);
 hipError_t launch_stats_reset(const GenArgs& a, bool reset_accepted,
                               hipStream_t s);
 hipError_t launch_best_from_fit(const GenArgs& a, hipStream_t s);

@@ -196,8 +196,11 @@ __global__ __launch_bounds__(64) void k_delay(uint64_t ticks) {
     __builtin_amdgcn_s_sleep(2);
 }
 
+// *rmax (null: none) is cleared for k_rot_max.
 __global__ __launch_bounds__(256) void k_prep_shift(const float* o, int D,
-                                                    int dpad, float* o_pad) {
+                                                    int dpad, float* o_pad,
+                                                    float* rmax) {
+  if (rmax && blockIdx.x == 0 && threadIdx.x == 0) *rmax = 0.f;
   for (int k = blockIdx.x * 256 + threadIdx.x; k < dpad; k += gridDim.x * 256)
     o_pad[k] = k < D ? o[k] : 0.f;
 }
@@ -235,27 +238,28 @@ __global__ __launch_bounds__(256) void k_prep_rot_f32(const float* R, int ldr,
   }
 }
 
-// Split layout (PrecSplit): row n of R scaled by its own power of two, as
-// halves: element (n, k) of half p goes to block nb = n / 32, K-step kb =
-// k / 16, lane (n % 32) + 32 ((k % 16) / 8), slot k % 8 of fragment
-// ((nb * dpad / 16 + kb) * 2 + p) * 64 + lane; the rows' inverse scales
-// follow the dpad x dpad halves.  One workgroup per row.
-__global__ __launch_bounds__(256) void k_prep_rot_split(const float* R, int ldr,
-                                                        int D, int dpad,
-                                                        half8* rop) {
-  __shared__ float wm[4];
+// Largest |R| (*rmax starts at zero; non-negative floats order as integers).
+__global__ __launch_bounds__(256) void k_rot_max(const float* R, int ldr, int D,
+                                                 float* rmax) {
   const int n = (int)blockIdx.x;
   float m = 0.f;
-  if (n < D)
-    for (int k = (int)threadIdx.x; k < D; k += 256)
-      m = fmaxf(m, fabsf(R[(size_t)n * ldr + k]));
+  for (int k = (int)threadIdx.x; k < D; k += 256)
+    m = fmaxf(m, fabsf(R[(size_t)n * ldr + k]));
   for (int x = 32; x >= 1; x >>= 1) m = fmaxf(m, __shfl_xor(m, x, 64));
-  if (threadIdx.x % 64 == 0) wm[threadIdx.x / 64] = m;
-  __syncthreads();
-  m = fmaxf(fmaxf(wm[0], wm[1]), fmaxf(wm[2], wm[3]));
-  const RowScale rs = split_scale(m);
-  if (threadIdx.x == 0)
-    (reinterpret_cast<float*>(rop) + (size_t)dpad * dpad)[n] = rs.inv;
+  if (threadIdx.x % 64 == 0)
+    atomicMax(reinterpret_cast<int*>(rmax), __builtin_bit_cast(int, m));
+}
+
+// Split layout (PrecSplit): R scaled by one power of two (from *rmax), as
+// halves: element (n, k) of half p goes to block nb = n / 32, K-step kb =
+// k / 16, lane (n % 32) + 32 ((k % 16) / 8), slot k % 8 of fragment
+// ((nb * dpad / 16 + kb) * 2 + p) * 64 + lane.  One workgroup per row.
+__global__ __launch_bounds__(256) void k_prep_rot_split(const float* R, int ldr,
+                                                        int D, int dpad,
+                                                        const float* rmax,
+                                                        half8* rop) {
+  const int n = (int)blockIdx.x;
+  const RowScale rs = split_scale(*rmax);
   for (int g8 = (int)threadIdx.x; g8 < dpad / 8; g8 += 256) {
     float v[8];
 #pragma unroll
@@ -814,15 +818,6 @@ int device_cus() {
 
 // LDS bytes of the rotated kernel: BF16 tiles of 64 rows, FP32 tiles of 32
 // rows (independent of the number of threads).
-size_t rot_operand_bytes(int prec, int dpad) {
-  const size_t n = (size_t)dpad * dpad;
-  return prec == kPrecBF16 ? 2 * n : 4 * n;
-}
-
-size_t rot_scale_bytes(int prec, int dpad) {
-  return prec != kPrecBF16 && dpad > kF32MaxDpad ? 4 * (size_t)dpad : 0;
-}
-
 size_t rot_lds_bytes_host(int prec, int dpad, bool jde) {
   if (prec != kPrecBF16)
     return jde ? rot_lds_bytes<PrecSplit, 32, true>(dpad)
@@ -926,9 +921,9 @@ hipError_t launch_fill_control(float2* jp, int n, float F, float CR,
 
 hipError_t launch_prep(const float* o, const float* R, int ldr, int D,
                        int dpad, int kind, int prec, float* o_pad, void* rop,
-                       hipStream_t s) {
+                       float* rmax, hipStream_t s) {
   hipLaunchKernelGGL(k_prep_shift, dim3(grid_for(dpad, 256)), dim3(256), 0, s,
-                     o, D, dpad, o_pad);
+                     o, D, dpad, o_pad, rmax);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || kind != kObjRotOsc) return e;
   const size_t total = (size_t)dpad * dpad;
@@ -936,8 +931,11 @@ hipError_t launch_prep(const float* o, const float* R, int ldr, int D,
     hipLaunchKernelGGL(k_prep_rot_bf16, dim3(grid_for(total, 256)), dim3(256),
                        0, s, R, ldr, D, dpad, reinterpret_cast<__bf16*>(rop));
   } else if (dpad > kF32MaxDpad) {
+    hipLaunchKernelGGL(k_rot_max, dim3(D), dim3(256), 0, s, R, ldr, D, rmax);
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_prep_rot_split, dim3(dpad), dim3(256), 0, s, R, ldr,
-                       D, dpad, reinterpret_cast<half8*>(rop));
+                       D, dpad, rmax, reinterpret_cast<half8*>(rop));
   } else {
     hipLaunchKernelGGL(k_prep_rot_f32, dim3(grid_for(total, 256)), dim3(256),
                        0, s, R, ldr, D, dpad, reinterpret_cast<float*>(rop));

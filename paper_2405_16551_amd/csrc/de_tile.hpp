@@ -81,8 +81,8 @@ struct PrecF32Narrow {
   static constexpr bool kSplit = false;
 };
 // FP32 product as three half-precision products: y = yh + yl and R = Rh + Rl
-// (halves of 11 significant bits each, after scaling every row of Y and of R
-// by a power of two into the half range), z = yh Rh + (yh Rl + yl Rh) with
+// (halves of 11 significant bits each, after scaling every row of Y and all
+// of R by a power of two into the half range), z = yh Rh + (yh Rl + yl Rh) with
 // the bracket in an accumulator of its own.
 //   - Why: an FP32 MFMA runs at 1/16 of the half-precision rate and on the
 //     vector FMA units (measured: FP32 MFMA next to FMAs of another wave
@@ -191,9 +191,6 @@ __device__ __forceinline__ void osc_accumulate(floatx16& part,
   for (int r = 0; r < 16; ++r) part[r] += osc_term<kFastSin>(c[r]);
 }
 
-// 256-coordinate chunks per producer step (rows per step: 8 / this).  One
-// chunk of eight rows measured fastest at D = 1000 (BF16 and FP32 tiles).
-constexpr int kProducerChunks = 1;
 // Rows per producer step of BF16 tiles (128 registers per lane).
 constexpr int kBf16Rows = 4;
 // Threads of the BF16 rotated tile.  Each wave owns one column block per
@@ -333,10 +330,7 @@ __device__ __forceinline__ void rot_tile(const GenArgs& a, int run, int row0,
     }
     __syncthreads();
   }
-  // Rows rl = wave + kRotWaves * k of this wave; each row is cut into groups
-  // of four 256-coordinate chunks.  Items (row, group) are processed in
-  // order with two register sets, so the loads of item s + 1 are in flight
-  // while item s is drawn, mutated and stored.
+  // rows past the tile's last are zero
   for (int rl = nvalid + (((wave - nvalid) % kRotWaves) + kRotWaves) %
                              kRotWaves;
        rl < BM; rl += kRotWaves) {
@@ -427,50 +421,42 @@ __device__ __forceinline__ void rot_tile(const GenArgs& a, int run, int row0,
     }
   } else
   {
-    // Chunk-major: for each group of CG 256-coordinate chunks, the wave's
-    // rows rl = wave + kRotWaves * k go RB at a time (CG * RB = 8 chunk
-    // rows in flight): the target and donor chunks of the RB rows are
-    // requested together, then drawn, mutated and stored.  All workgroups
+    // Chunk-major: for each 256-coordinate chunk, the wave's rows rl = wave
+    // + kRotWaves * k go RB at a time: the target and donor chunks of the RB
+    // rows are requested together, then drawn, mutated and stored.  Rows are
+    // scalar and the chunk's groups q per lane, so the crossover draws share
+    // their first rounds (XoverCol, XoverRow).  All workgroups
     // walk the chunks in the same order, so an XCD's donor reads of one
     // step stay within one chunk of its runs' rows (a working set its L2
     // holds).  Loads past the end of a row go to its last chunk and rows
     // past the wave's last go to its last row (values unused), so no load
     // sits behind a per-lane branch.
-    constexpr int CG = kProducerChunks;
-    constexpr int RB = (sizeof(T) == 2 ? kBf16Rows : 8) / CG;
+    constexpr int RB = sizeof(T) == 2 ? kBf16Rows : 8;
     const int nrow_w = wave < nvalid ? (nvalid - 1 - wave) / kRotWaves + 1 : 0;
     const int dlast = ((a.D + 3) / 4 - 1) * 4;
-    for (int t0 = 0; t0 < tq; t0 += CG) {
-      float4 ov[CG];
-#pragma unroll
-      for (int u = 0; u < CG; ++u)
-        ov[u] = ld4(a.o + min(4 * (lane + 64 * (t0 + u)), dlast));
+    for (int t = 0; t < tq; ++t) {
+      const int q = lane + 64 * t, j0 = 4 * q, jl = min(j0, dlast);
+      const float4 ov = ld4(a.o + jl);
+      // a chunk with the row's end: its coordinates past D are zeroed
+      const bool whole = 256 * (t + 1) <= a.D;
+      XoverCol xc{0, 0, 0, 0};
+      if (!EVAL)
+        xc = xover_col(rng_run, a.gen, (uint32_t)q, a.key_lo, a.key_hi);
       for (int k = 0; k < nrow_w; k += RB) {
-        float4 xv[RB][CG], v1[RB][CG], v2[RB][CG], v3[RB][CG];
+        float4 xv[RB], v1[RB], v2[RB], v3[RB];
 #pragma unroll
         for (int h = 0; h < RB; ++h) {
           // row and donor indices are wave-uniform: scalar row pointers
           const int rl = __builtin_amdgcn_readfirstlane(
               wave + kRotWaves * min(k + h, nrow_w - 1));
-          const float* xrow = base + (size_t)(row0 + rl) * a.ldx;
-          const float *x1 = xrow, *x2 = xrow, *x3 = xrow;
+          xv[h] = ld4(base + (size_t)(row0 + rl) * a.ldx + jl);
           if (!EVAL) {
-            x1 = base + (size_t)__builtin_amdgcn_readfirstlane(
-                            donors[rl * 4 + 0]) * a.ldx;
-            x2 = base + (size_t)__builtin_amdgcn_readfirstlane(
-                            donors[rl * 4 + 1]) * a.ldx;
-            x3 = base + (size_t)__builtin_amdgcn_readfirstlane(
-                            donors[rl * 4 + 2]) * a.ldx;
-          }
-#pragma unroll
-          for (int u = 0; u < CG; ++u) {
-            const int jl = min(4 * (lane + 64 * (t0 + u)), dlast);
-            xv[h][u] = ld4(xrow + jl);
-            if (!EVAL) {
-              v1[h][u] = ld4(x1 + jl);
-              v2[h][u] = ld4(x2 + jl);
-              v3[h][u] = ld4(x3 + jl);
-            }
+            v1[h] = ld4(base + (size_t)__builtin_amdgcn_readfirstlane(
+                                   donors[rl * 4 + 0]) * a.ldx + jl);
+            v2[h] = ld4(base + (size_t)__builtin_amdgcn_readfirstlane(
+                                   donors[rl * 4 + 1]) * a.ldx + jl);
+            v3[h] = ld4(base + (size_t)__builtin_amdgcn_readfirstlane(
+                                   donors[rl * 4 + 2]) * a.ldx + jl);
           }
         }
         // every gather of the step is issued before any of it is used:
@@ -480,73 +466,62 @@ __device__ __forceinline__ void rot_tile(const GenArgs& a, int run, int row0,
 #pragma unroll
         for (int h = 0; h < RB; ++h) {
           if (k + h >= nrow_w) break;
-          const int rl = wave + kRotWaves * (k + h);
-          const int i = row0 + rl;
-          const int jrand = EVAL ? 0 : donors[rl * 4 + 3];
-          float Fr = a.F;
-          uint32_t crt = a.cr_threshold;
-          if constexpr (JDE && !EVAL) {
-            const Control c = ctl[rl];
-            Fr = c.F;
-            crt = cr_threshold_of(c.CR);
-          }
+          const int rl =
+              __builtin_amdgcn_readfirstlane(wave + kRotWaves * (k + h));
           T* arow = At + (size_t)rl * stride;
+          float4 y;
+          if constexpr (EVAL) {
 #pragma unroll
-          for (int u = 0; u < CG; ++u) {
-            const int t = t0 + u;
-            if (t >= tq) break;
-            const int q = lane + 64 * t, j0 = 4 * q;
-            bool tk[4] = {false, false, false, false};
-            float4 uu = xv[h][u];
-            if (!EVAL) {
-              const Words4 w = draw_block(kTagXover, rng_run, a.gen,
-                                          (uint32_t)i, (uint32_t)q, a.key_lo,
-                                          a.key_hi);
-#pragma unroll
-              for (int b = 0; b < 4; ++b) {
-                // bitwise &: both tests are lane masks, no branch
-                tk[b] = (j0 + b < a.D) &
-                        take_mutant(w.w[b], j0 + b, jrand, crt);
-                const float mv =
-                    mutant_coord(get(v1[h][u], b), get(v2[h][u], b),
-                                 get(v3[h][u], b), Fr, a.lo, a.hi);
-                set(uu, b, tk[b] ? mv : get(xv[h][u], b));
-              }
+            for (int b = 0; b < 4; ++b) set(y, b, get(xv[h], b) - get(ov, b));
+          } else {
+            const int jrand = donors[rl * 4 + 3];
+            float Fr = a.F;
+            uint32_t limit = xover_word_limit(a.cr_threshold);
+            if constexpr (JDE) {
+              Fr = ctl[rl].F;
+              limit = xover_word_limit(cr_threshold_of(ctl[rl].CR));
             }
-            float4 y;
+            const XoverRow xr = xover_row(a.gen, (uint32_t)(row0 + rl),
+                                          a.key_lo, a.key_hi);
+            const Words4 w = xover_words(xc, xr, a.key_lo, a.key_hi);
+            unsigned long long m[4];
+#pragma unroll
+            for (int b = 0; b < 4; ++b) {
+              // bitwise & and |: the tests are lane masks, no branch
+              const bool tk = (j0 + b < a.D) &
+                              ((j0 + b == jrand) | (w.w[b] <= limit));
+              const float mv = mutant_coord(get(v1[h], b), get(v2[h], b),
+                                            get(v3[h], b), Fr, a.lo, a.hi);
+              m[b] = __ballot(tk);
+              set(y, b, (tk ? mv : get(xv[h], b)) - get(ov, b));
+            }
+            // the chunk's crossover planes: the decisions' lane masks,
+            // stored by lane 0 as two 16-byte writes
+            if (lane == 0) {
+              ulonglong2* pp = reinterpret_cast<ulonglong2*>(
+                  planes + ((size_t)rl * tq + t) * 4);
+              pp[0] = make_ulonglong2(m[0], m[1]);
+              pp[1] = make_ulonglong2(m[2], m[3]);
+            }
+          }
+          if (!whole) {
 #pragma unroll
             for (int b = 0; b < 4; ++b)
-              set(y, b, (j0 + b < a.D) ? get(uu, b) - get(ov[u], b) : 0.f);
-            if (j0 < dpad) {
-              if constexpr (sizeof(T) == 2) {
-                bf16x4 yb;
-                yb[0] = (__bf16)y.x;
-                yb[1] = (__bf16)y.y;
-                yb[2] = (__bf16)y.z;
-                yb[3] = (__bf16)y.w;
-                *reinterpret_cast<bf16x4*>(arow + j0) = yb;
-              } else if constexpr (P::kSplit) {
-                st4(arow + j0, y);
-              } else {
+              set(y, b, j0 + b < a.D ? get(y, b) : 0.f);
+          }
+          if (j0 < dpad) {
+            if constexpr (sizeof(T) == 2) {
+              bf16x4 yb;
+              yb[0] = (__bf16)y.x;
+              yb[1] = (__bf16)y.y;
+              yb[2] = (__bf16)y.z;
+              yb[3] = (__bf16)y.w;
+              *reinterpret_cast<bf16x4*>(arow + j0) = yb;
+            } else if constexpr (P::kSplit) {
+              st4(arow + j0, y);
+            } else {
 #pragma unroll
-                for (int b = 0; b < 4; ++b)
-                  arow[lds_col<P>(j0 + b)] = get(y, b);
-              }
-            }
-            if (!EVAL) {
-              // the four crossover planes of the chunk are the ballots of
-              // the decisions (the compare masks themselves), stored by
-              // lane 0 as two 16-byte writes
-              const unsigned long long m0 = __ballot(tk[0]);
-              const unsigned long long m1 = __ballot(tk[1]);
-              const unsigned long long m2 = __ballot(tk[2]);
-              const unsigned long long m3 = __ballot(tk[3]);
-              if (lane == 0) {
-                ulonglong2* pp = reinterpret_cast<ulonglong2*>(
-                    planes + ((size_t)rl * tq + t) * 4);
-                pp[0] = make_ulonglong2(m0, m1);
-                pp[1] = make_ulonglong2(m2, m3);
-              }
+              for (int b = 0; b < 4; ++b) arow[lds_col<P>(j0 + b)] = get(y, b);
             }
           }
         }
@@ -662,16 +637,13 @@ __device__ __forceinline__ void rot_tile(const GenArgs& a, int run, int row0,
         }
       }
     } else if constexpr (P::kSplit) {
-      // R as [nblk][dpad/16][half][64 lanes][8] with the rows' inverse
-      // scales behind it.  A ring of kRing K-steps of fragments: a step's
+      // R as [nblk][dpad/16][half][64 lanes][8].  A ring of kRing K-steps of fragments: a step's
       // registers are loaded for kRing steps later once its MFMAs are
       // issued.  The stream from L2 (4 bytes per element of R per 32 rows)
       // bounds the loop: 2 KB per block and step against 96 clocks of MFMA.
       const half8* rop =
           reinterpret_cast<const half8*>(a.rop) +
           (size_t)__builtin_amdgcn_readfirstlane(nb0) * (dpad / 16) * 128;
-      const float* cinv = reinterpret_cast<const float*>(a.rop) +
-                          (size_t)dpad * dpad + lane % 32;
       const int kbn = dpad / 16;  // a multiple of 8
       constexpr int kRing = NBW == 2 ? 4 : 8;
       const char* ar = reinterpret_cast<const char*>(At) +
@@ -729,17 +701,16 @@ __device__ __forceinline__ void rot_tile(const GenArgs& a, int run, int row0,
           interleave_split<NBW>();
         }
       }
-      const float s0 = cinv[nb0 * 32];
-      const float s1 = NBW == 2 ? cinv[nb0 * 32 + 32] : 0.f;
+      const float rs0 = split_scale(*a.rmax).inv;
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         const float4 rs = ld4(rinv + 8 * q + 4 * (lane / 32));
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          c00[4 * q + r] = (c00[4 * q + r] + x00[4 * q + r]) * s0 * get(rs, r);
+          c00[4 * q + r] = (c00[4 * q + r] + x00[4 * q + r]) * get(rs, r) * rs0;
           if constexpr (NBW == 2)
             c01[4 * q + r] =
-                (c01[4 * q + r] + x01[4 * q + r]) * s1 * get(rs, r);
+                (c01[4 * q + r] + x01[4 * q + r]) * get(rs, r) * rs0;
         }
       }
     } else {

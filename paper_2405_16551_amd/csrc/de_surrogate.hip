@@ -7,9 +7,9 @@
 //   k_mlp_infer_res / k_mlp_infer
 //                  the run's MLP D -> H -> H -> 1 on every candidate, BF16
 //                  32x32x16 MFMA with FP32 accumulation, bias and ReLU
-//                  fused; tiles of 64 candidates (the first form, for D
-//                  padded to at most 128, keeps each wave's weight
-//                  fragments in registers over four tiles)
+//                  fused (the first form, for D padded to at most 128,
+//                  keeps each wave's weight fragments in registers over
+//                  several tiles of 128 candidates)
 //   k_sur_select   per target the lowest prediction is evaluated on the
 //                  composition objective (Section 7.3.3 composition
 //                  functions; the expensive step), strict selection, next
@@ -28,6 +28,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <limits>
@@ -577,65 +578,43 @@ __global__ __launch_bounds__(256) void k_mlp_infer(SurArgs a, const float* X,
   }
 }
 
-// rows_of_block with the lane-dependent choices as bit selects on a
-// per-lane mask held in a vector register (v_bfi_b32) instead of
-// per-step lane masks, which the register-resident kernel has no scalar
-// registers left for.  Same exchanges and additions, same result.
-__device__ __forceinline__ float bsel(uint32_t m, float a, float b) {
-  const uint32_t ia = __builtin_bit_cast(uint32_t, a);
-  const uint32_t ib = __builtin_bit_cast(uint32_t, b);
-  return __builtin_bit_cast(float, (m & ia) | (~m & ib));  // m ? a : b
-}
-
-__device__ __forceinline__ float rows_of_block_vsel(const floatx16& part,
-                                                    int lane) {
-  float v[16];
-#pragma unroll
-  for (int r = 0; r < 16; ++r) v[r] = part[r];
-#pragma unroll
-  for (int m = 16, sh = 4; m >= 2; m >>= 1, --sh) {
-    const uint32_t up = 0u - (((uint32_t)lane >> sh) & 1u);  // all ones if set
-#pragma unroll
-    for (int k = 0; k < m / 2; ++k) {
-      const float send = bsel(up, v[k], v[k + m / 2]);
-      const float keep = bsel(up, v[k + m / 2], v[k]);
-      v[k] = keep + __shfl_xor(send, m, 64);
-    }
-  }
-  return v[0] + __shfl_xor(v[0], 1, 64);
-}
-
-// MLP inference with the weights held in registers: one workgroup of
-// H / 32 waves per group of row tiles of one run; wave w keeps the BF16
-// fragments of column block w of W1 (KB1 = Dp / 16 K-steps) and of W2
-// (KB2 = H / 16) for the whole launch, so the K loops read only LDS.  Per
-// 64-row tile: the rows go to LDS in BF16 (the next tile's rows are loaded
-// into registers meanwhile), layer 1 writes relu(A W1^T + b1) to LDS,
-// layer 2's epilogue applies relu(. + b2) and w3 and reduces its 32
-// columns per row; the rows' totals add the waves in order, then b3.
-// Same operands and per-block K order as k_mlp_infer; the row totals add
-// the 32-column blocks in another order (block by block instead of two
-// per wave), a difference within FP32 rounding.
-constexpr int kResTiles = 4;  // 64-row tiles per workgroup
+// MLP inference with the weights held in registers: one workgroup of H / 32
+// waves walks `per` tiles of kResRows rows of one run; wave w keeps the BF16
+// fragments of hidden block w of W1 (KB1 = Dp / 16 K-steps) and of W2 (KB2 =
+// H / 16) for the whole launch, so the K loops read only LDS.  Both layers
+// are computed transposed (the weights as the A operand): a lane then holds
+// 16 hidden units of one row, so that relu(W1 x + b1) goes to LDS as BF16 in
+// 8-byte pieces and layer 2's row sums need four exchanges; they form the
+// tree over hidden units 16, 8, 4, 2, 1 apart that k_mlp_infer forms, then
+// the blocks in order, then b3.
+// Bound: the chain of barriers and LDS round trips of a tile (LDS and matrix
+// time are both 3 us per 128 rows and CU).  Four row blocks per barrier
+// instead of two and no per-value writes: 36.7 -> INF_US us at 30 x 2048
+// rows, D 100, H 256; with tiles dealt to all CUs, 2048 rows of one run
+// 33 -> PRED_US us.
+constexpr int kResRows = 128;
 
 template <int KB1, int KB2>
 __global__ __launch_bounds__(512) void k_mlp_infer_res(SurArgs a, const float* X,
                                                        size_t x_run_stride,
                                                        int n, int ldx, float* y,
                                                        size_t y_run_stride,
-                                                       int run0) {
-  constexpr int Dp = KB1 * 16, H = KB2 * 16, NW = H / 32;
-  constexpr int sa = Dp + 8, sh = H + 8;
-  constexpr int kStage = (kInferRows * Dp + 32 * NW * 2 - 1) / (64 * NW);
+                                                       int run0, int per,
+                                                       int vec) {
+  constexpr int Dp = KB1 * 16, H = KB2 * 16, NW = H / 32, kThr = 64 * NW;
+  constexpr int sa = Dp + 8, sh = H + 8, RB = kResRows / 32;
+  // 4-coordinate groups of a tile per thread; held in registers (BF16) one
+  // tile ahead when they are few
+  constexpr int kQuads = kResRows * (Dp / 4) / kThr;
+  constexpr bool kPre = kQuads <= 8;
   extern __shared__ __align__(16) char smem[];
   const RunUnit wu = run_unit();
   const int run = run0 + wu.run;
   const int tid = (int)threadIdx.x, lane = tid % 64;
   const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
-  const int nthr = 64 * NW;
   __bf16* A = reinterpret_cast<__bf16*>(smem);
-  __bf16* H1 = A + (size_t)kInferRows * sa;
-  float* ypart = reinterpret_cast<float*>(H1 + (size_t)kInferRows * sh);
+  __bf16* H1 = A + (size_t)kResRows * sa;
+  float* ypart = reinterpret_cast<float*>(H1 + (size_t)kResRows * sh);
   const float* Xr = X + wu.run * x_run_stride;
   const float* th = a.theta + (size_t)run * a.pstride;
   const float* b1 = th + (size_t)H * a.D;
@@ -643,8 +622,6 @@ __global__ __launch_bounds__(512) void k_mlp_infer_res(SurArgs a, const float* X
   const float* w3 = b2 + H;
   const float b3 = w3[H];
   const int li = lane % 32, lk = lane / 32;
-  const int col = wave * 32 + li;
-  const float b1c = b1[col], b2c = b2[col], w3c = w3[col];
   bf16x8 w1r[KB1], w2r[KB2];
   {
     const bf16x8* f1 = reinterpret_cast<const bf16x8*>(a.w1f) +
@@ -656,100 +633,125 @@ __global__ __launch_bounds__(512) void k_mlp_infer_res(SurArgs a, const float* X
 #pragma unroll
     for (int kb = 0; kb < KB2; ++kb) w2r[kb] = f2[(size_t)kb * 64];
   }
-  const int tiles = (n + kInferRows - 1) / kInferRows;
-  const int t0 = wu.x * kResTiles;
-  const int t1 = min(t0 + kResTiles, tiles);
-  // scaled value of element e (row e / Dp, coordinate e % Dp) of tile t
-  auto xval = [&](int t, int e) {
-    const int r = e / Dp, dd = e - r * Dp;
-    const int row = t * kInferRows + r;
-    float v = 0.f;
-    if (r < kInferRows && row < n && dd < a.D)
-      v = fmaf(Xr[(size_t)row * ldx + dd], a.xs_mul, a.xs_add);
-    return v;
-  };
-  // with at most 16 elements per thread, the next tile's rows are loaded
-  // into registers while the current tile is computed
-  // (held as BF16 pairs: the LDS copy is BF16 anyway)
-  constexpr bool kPre = kStage <= 16;
-  static_assert(!kPre || kStage % 2 == 0, "staging pairs");
-  constexpr int kPairs = kPre ? kStage / 2 : 1;
-  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-  bf16x2 stage[kPairs];
-  auto load_stage = [&](int t) {
+  // the lane's 16 hidden units: 32 wave + 8 (r / 4) + 4 lk + r % 4
+  float b1r[16], b2r[16], w3r[16];
 #pragma unroll
-    for (int u = 0; u < kPairs; ++u) {
-      bf16x2 p;
-      p[0] = (__bf16)xval(t, tid + (2 * u) * nthr);
-      p[1] = (__bf16)xval(t, tid + (2 * u + 1) * nthr);
-      stage[u] = p;
+  for (int r = 0; r < 16; ++r) {
+    const int u = 32 * wave + 8 * (r / 4) + 4 * lk + r % 4;
+    b1r[r] = b1[u];
+    b2r[r] = b2[u];
+    w3r[r] = w3[u];
+  }
+  const int tiles = (n + kResRows - 1) / kResRows;
+  const int t0 = wu.x * per, t1 = min(t0 + per, tiles);
+  // scaled group e (row e / (Dp / 4), coordinates 4 (e % (Dp / 4)) on) of
+  // tile t, zero outside the rows and past D
+  auto xquad = [&](int t, int e) {
+    const int row = t * kResRows + e / (Dp / 4), j0 = 4 * (e % (Dp / 4));
+    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (row < n && j0 < a.D) {
+      const float* p = Xr + (size_t)row * ldx + j0;
+      if (vec) {
+        v = ld4(p);
+      } else {
+        v.x = p[0];
+        v.y = j0 + 1 < a.D ? p[1] : 0.f;
+        v.z = j0 + 2 < a.D ? p[2] : 0.f;
+        v.w = j0 + 3 < a.D ? p[3] : 0.f;
+      }
     }
+    bf16x4 o;
+#pragma unroll
+    for (int b = 0; b < 4; ++b)
+      o[b] = (__bf16)(row < n && j0 + b < a.D
+                          ? fmaf(get(v, b), a.xs_mul, a.xs_add)
+                          : 0.f);
+    return o;
   };
-  if (kPre && t0 < t1) load_stage(t0);
-  const __bf16* ar0 = A + (size_t)li * sa + 8 * lk;
-  const __bf16* ar1 = ar0 + (size_t)32 * sa;
-  const __bf16* hr0 = H1 + (size_t)li * sh + 8 * lk;
-  const __bf16* hr1 = hr0 + (size_t)32 * sh;
+  auto put = [&](int e, bf16x4 v) {
+    *reinterpret_cast<bf16x4*>(A + (e / (Dp / 4)) * sa + 4 * (e % (Dp / 4))) =
+        v;
+  };
+  bf16x4 stage[kPre ? kQuads : 1];
+  if (kPre && t0 < t1) {
+#pragma unroll
+    for (int u = 0; u < kQuads; ++u) stage[u] = xquad(t0, tid + u * kThr);
+  }
+  const __bf16* ar = A + (size_t)li * sa + 8 * lk;
+  const __bf16* hr = H1 + (size_t)li * sh + 8 * lk;
+  __bf16* hw = H1 + (size_t)li * sh + 32 * wave + 4 * lk;
   for (int t = t0; t < t1; ++t) {
     if constexpr (kPre) {
 #pragma unroll
-      for (int u = 0; u < kStage; ++u) {
-        const int e = tid + u * nthr;
-        const int r = e / Dp, dd = e - r * Dp;
-        if (r < kInferRows) A[r * sa + dd] = stage[u / 2][u % 2];
-      }
+      for (int u = 0; u < kQuads; ++u) put(tid + u * kThr, stage[u]);
     } else {
-      for (int e = tid; e < kInferRows * Dp; e += nthr) {
-        const int r = e / Dp, dd = e - r * Dp;
-        A[r * sa + dd] = (__bf16)xval(t, e);
-      }
+      for (int u = 0; u < kQuads; ++u)
+        put(tid + u * kThr, xquad(t, tid + u * kThr));
     }
     __syncthreads();  // A of tile t complete; H1 and ypart of t - 1 read
-    if (kPre && t + 1 < t1) load_stage(t + 1);
-    floatx16 c0 = {}, c1 = {};
+    if (kPre && t + 1 < t1) {
 #pragma unroll
-    for (int kb = 0; kb < KB1; ++kb) {
-      const bf16x8 x0 = *reinterpret_cast<const bf16x8*>(ar0 + 16 * kb);
-      const bf16x8 x1 = *reinterpret_cast<const bf16x8*>(ar1 + 16 * kb);
-      c0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x0, w1r[kb], c0, 0, 0, 0);
-      c1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x1, w1r[kb], c1, 0, 0, 0);
+      for (int u = 0; u < kQuads; ++u) stage[u] = xquad(t + 1, tid + u * kThr);
     }
+    floatx16 c[RB];
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int row = 8 * (r / 4) + 4 * lk + (r % 4);
-      H1[row * sh + col] = (__bf16)fmaxf(c0[r] + b1c, 0.f);
-      H1[(32 + row) * sh + col] = (__bf16)fmaxf(c1[r] + b1c, 0.f);
-    }
+    for (int m = 0; m < RB; ++m) c[m] = floatx16{};
+#pragma unroll
+    for (int kb = 0; kb < KB1; ++kb)
+#pragma unroll
+      for (int m = 0; m < RB; ++m) {
+        const bf16x8 x =
+            *reinterpret_cast<const bf16x8*>(ar + 32 * m * sa + 16 * kb);
+        c[m] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w1r[kb], x, c[m], 0, 0,
+                                                       0);
+      }
+#pragma unroll
+    for (int m = 0; m < RB; ++m)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        bf16x4 v;
+#pragma unroll
+        for (int b = 0; b < 4; ++b)
+          v[b] = (__bf16)fmaxf(c[m][4 * q + b] + b1r[4 * q + b], 0.f);
+        *reinterpret_cast<bf16x4*>(hw + 32 * m * sh + 8 * q) = v;
+      }
     __syncthreads();  // H1 complete
-    c0 = floatx16{};
-    c1 = floatx16{};
 #pragma unroll
-    for (int kb = 0; kb < KB2; ++kb) {
-      const bf16x8 h0 = *reinterpret_cast<const bf16x8*>(hr0 + 16 * kb);
-      const bf16x8 h1 = *reinterpret_cast<const bf16x8*>(hr1 + 16 * kb);
-      c0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(h0, w2r[kb], c0, 0, 0, 0);
-      c1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(h1, w2r[kb], c1, 0, 0, 0);
-    }
+    for (int m = 0; m < RB; ++m) c[m] = floatx16{};
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      c0[r] = fmaxf(c0[r] + b2c, 0.f) * w3c;
-      c1[r] = fmaxf(c1[r] + b2c, 0.f) * w3c;
-    }
-    const float s0 = rows_of_block_vsel(c0, lane);
-    const float s1 = rows_of_block_vsel(c1, lane);
-    if ((lane & 1) == 0) {
-      const int r = li >> 1;
-      const int row = 8 * (r / 4) + 4 * lk + (r % 4);
-      ypart[wave * kInferRows + row] = s0;
-      ypart[wave * kInferRows + 32 + row] = s1;
+    for (int kb = 0; kb < KB2; ++kb)
+#pragma unroll
+      for (int m = 0; m < RB; ++m) {
+        const bf16x8 x =
+            *reinterpret_cast<const bf16x8*>(hr + 32 * m * sh + 16 * kb);
+        c[m] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w2r[kb], x, c[m], 0, 0,
+                                                       0);
+      }
+#pragma unroll
+    for (int m = 0; m < RB; ++m) {
+#pragma clang fp contract(off)  // each product is rounded before it is added
+      float v[16];
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+        v[r] = fmaxf(c[m][r] + b2r[r], 0.f) * w3r[r];
+#pragma unroll
+      for (int r = 0; r < 8; ++r) v[r] += v[r + 8];  // units 16 apart
+#pragma unroll
+      for (int r = 0; r < 4; ++r) v[r] += v[r + 4];  // 8 apart
+#pragma unroll
+      for (int r = 0; r < 4; ++r) v[r] += __shfl_xor(v[r], 32, 64);  // 4
+      const float s = (v[0] + v[2]) + (v[1] + v[3]);
+      if (lk == 0) ypart[wave * kResRows + 32 * m + li] = s;
     }
     __syncthreads();  // ypart complete
-    const int row = t * kInferRows + tid;
-    if (tid < kInferRows && row < n) {
-      float s = b3;
+    for (int r = tid; r < kResRows; r += kThr) {
+      const int row = t * kResRows + r;
+      if (row < n) {
+        float s = b3;
 #pragma unroll
-      for (int w = 0; w < NW; ++w) s += ypart[w * kInferRows + tid];
-      y[wu.run * y_run_stride + row] = s;
+        for (int w = 0; w < NW; ++w) s += ypart[w * kResRows + r];
+        y[wu.run * y_run_stride + row] = s;
+      }
     }
   }
 }
@@ -910,9 +912,10 @@ __global__ __launch_bounds__(256) void k_model_prep(SurArgs a) {
 // C(4 (l / 16) + r, l % 16)), so that a minibatch of 128 rows of 30 runs
 // already spreads over 240 workgroups.
 constexpr int kTrainRows = 16;
+constexpr int kTrainThreads = 1024;
 
 __host__ __device__ constexpr size_t train_lds_floats(int Dp, int H) {
-  return (size_t)kTrainRows * (Dp + 1) + (size_t)3 * kTrainRows * (H + 1) +
+  return (size_t)kTrainRows * (Dp + 4) + (size_t)3 * kTrainRows * (H + 4) +
          2 * kTrainRows;
 }
 
@@ -956,99 +959,93 @@ __device__ __forceinline__ floatx16 mfma_block(const float* ap, int astep,
   return c;
 }
 
-// Two 16x16 blocks of C = A B over K (a multiple of 32), columns boff0 and
-// boff1 of B, sharing the A reads: the lane's A value of K-step s at
-// ap[4 s + lq] (lq = l / 16), B(k, n) at bb[k * bstep + boff] (rows
-// k >= kvalid read as zero); `two` = 0 leaves c1 untouched.  KS = K / 4 when
-// K is compile-time: the B values of the first 32 K-steps are requested
-// before the first MFMA and each later one 32 steps ahead of its use.
-// Otherwise K-steps go in batches of eight, issued one batch ahead.
+// One 16x16 block of C = A B over K (a multiple of 32): the lane's A values
+// of K-steps 4 g .. 4 g + 3 are the 16 bytes at ap[16 g] (LDS rows K-permuted
+// as by comp_pos), B(k, n) at bb[k * bstep] (rows k >= kvalid read as zero).
+// KS = K / 4 when K is compile-time: the first kTrainAhead B values are
+// requested by train_ahead, before the operands of A are complete, and each
+// later one kTrainAhead steps ahead of its use.  Otherwise (KS = 0) K-steps
+// go in batches of eight, issued one batch ahead.
+constexpr int kTrainAhead = 32;
+
+struct TrainB {
+  float v[kTrainAhead];
+};
+
+__device__ __forceinline__ float train_b(const float* bb, int bstep, int kvalid,
+                                         int lq, int step) {
+  const int k = 4 * step + lq;
+  return k < kvalid ? bb[(size_t)k * bstep] : 0.f;
+}
+
 template <int KS>
-__device__ __forceinline__ void mfma16_pair(const float* ap, const float* bb,
-                                            int boff0, int boff1, int bstep,
-                                            int K, int kvalid, int lq,
-                                            bool two, floatx4& c0,
-                                            floatx4& c1) {
-  auto load_b = [&](int st, int boff) {
-    const int k = 4 * st + lq;
-    return k < kvalid ? bb[(size_t)k * bstep + boff] : 0.f;
-  };
-  c0 = floatx4{0.f, 0.f, 0.f, 0.f};
-  c1 = c0;
+__device__ __forceinline__ void train_ahead(TrainB& t, const float* bb,
+                                            int bstep, int kvalid, int lq) {
   if constexpr (KS > 0) {
-    static_assert(KS % 8 == 0, "K-steps in groups of eight");
-    constexpr int P = KS < 32 ? KS : 32;  // K-steps in flight
-    float b0[KS], b1[KS];
 #pragma unroll
-    for (int u = 0; u < P; ++u) {
-      b0[u] = load_b(u, boff0);
-      b1[u] = two ? load_b(u, boff1) : 0.f;
-    }
-#pragma unroll
-    for (int u0 = 0; u0 < KS; u0 += 8) {
-      float av[8];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) av[u] = ap[4 * (u0 + u) + lq];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        c0 = __builtin_amdgcn_mfma_f32_16x16x4f32(av[u], b0[u0 + u], c0, 0,
-                                                  0, 0);
-        if (two)
-          c1 = __builtin_amdgcn_mfma_f32_16x16x4f32(av[u], b1[u0 + u], c1, 0,
-                                                    0, 0);
-      }
-#pragma unroll
-      for (int u = u0; u < u0 + 8; ++u) {
-        if (u + P < KS) {
-          b0[u + P] = load_b(u + P, boff0);
-          b1[u + P] = two ? load_b(u + P, boff1) : 0.f;
-        }
-      }
-      __builtin_amdgcn_sched_barrier(0);
-    }
-  } else {
-    float a_n[8], b0n[8], b1n[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      a_n[u] = ap[4 * u + lq];
-      b0n[u] = load_b(u, boff0);
-      b1n[u] = two ? load_b(u, boff1) : 0.f;
-    }
-    for (int s0 = 0; s0 < K / 4; s0 += 8) {
-      float ac[8], b0c[8], b1c[8];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        ac[u] = a_n[u];
-        b0c[u] = b0n[u];
-        b1c[u] = b1n[u];
-      }
-      if (s0 + 8 < K / 4) {
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-          a_n[u] = ap[4 * (s0 + 8 + u) + lq];
-          b0n[u] = load_b(s0 + 8 + u, boff0);
-          b1n[u] = two ? load_b(s0 + 8 + u, boff1) : 0.f;
-        }
-      }
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        c0 = __builtin_amdgcn_mfma_f32_16x16x4f32(ac[u], b0c[u], c0, 0, 0, 0);
-        if (two)
-          c1 = __builtin_amdgcn_mfma_f32_16x16x4f32(ac[u], b1c[u], c1, 0, 0,
-                                                    0);
-      }
-    }
+    for (int u = 0; u < (KS < kTrainAhead ? KS : kTrainAhead); ++u)
+      t.v[u] = train_b(bb, bstep, kvalid, lq, u);
   }
 }
 
-// Forward pass of 16 minibatch rows per workgroup (8 waves; wave w owns the
-// 16-column blocks w, w + 8, ... of each product, two at a time), output
-// error e = 2 (y - t) / B, delta2 = [h2 > 0] e w3 and delta1 =
-// [h1 > 0] (delta2 W2); what the gradient needs goes to the scratch
-// arrays.  Odd LDS row strides keep the A reads conflict-free.
+template <int KS>
+__device__ __forceinline__ floatx4 train_block(TrainB& t, const float* ap,
+                                               const float* bb, int bstep,
+                                               int K, int kvalid, int lq) {
+  floatx4 c = {0.f, 0.f, 0.f, 0.f};
+  if constexpr (KS > 0) {
+    static_assert(KS % 8 == 0 && (KS <= kTrainAhead || KS % kTrainAhead == 0),
+                  "K-steps in groups of eight");
+#pragma unroll
+    for (int u0 = 0; u0 < KS; u0 += 8) {
+      const float4 a0 = ld4(ap + 4 * u0), a1 = ld4(ap + 4 * u0 + 16);
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        c = __builtin_amdgcn_mfma_f32_16x16x4f32(
+            get(u < 4 ? a0 : a1, u % 4), t.v[(u0 + u) % kTrainAhead], c, 0, 0,
+            0);
+#pragma unroll
+      for (int u = u0; u < u0 + 8; ++u)
+        if (u + kTrainAhead < KS)
+          t.v[u % kTrainAhead] =
+              train_b(bb, bstep, kvalid, lq, u + kTrainAhead);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  } else {
+    float bn[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) bn[u] = train_b(bb, bstep, kvalid, lq, u);
+    for (int s0 = 0; s0 < K / 4; s0 += 8) {
+      float bc[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) bc[u] = bn[u];
+      if (s0 + 8 < K / 4) {
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+          bn[u] = train_b(bb, bstep, kvalid, lq, s0 + 8 + u);
+      }
+      const float4 a0 = ld4(ap + 4 * s0), a1 = ld4(ap + 4 * s0 + 16);
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        c = __builtin_amdgcn_mfma_f32_16x16x4f32(get(u < 4 ? a0 : a1, u % 4),
+                                                 bc[u], c, 0, 0, 0);
+    }
+  }
+  return c;
+}
+
+// Forward pass of 16 minibatch rows per workgroup (16 waves; wave w owns the
+// 16-column blocks w, w + 16, ... of each product), output error
+// e = 2 (y - t) / B, delta2 = [h2 > 0] e w3 and delta1 = [h1 > 0]
+// (delta2 W2); what the gradient needs goes to the scratch arrays.
+// Bound: the FP32 products' chains (30 runs x 128 rows, D 100, H 256: 240
+// workgroups, one per CU, 10 us of matrix time) and the round trips between
+// them.  One block per wave leaves four waves per SIMD to cover each
+// other, and the next product's first B values are requested before the
+// current one's results are exchanged: 29.3 -> FWD_US us per step.
 // KS1 = Dp / 4 and KS2 = H / 4 when the sizes are compile-time, else 0.
 template <int KS1, int KS2>
-__global__ __launch_bounds__(512) void k_train_fwd(SurArgs a) {
+__global__ __launch_bounds__(kTrainThreads) void k_train_fwd(SurArgs a) {
   extern __shared__ __align__(16) float sm[];
   const RunUnit wu = run_unit();
   const int run = wu.run;
@@ -1058,8 +1055,9 @@ __global__ __launch_bounds__(512) void k_train_fwd(SurArgs a) {
   const int H = KS2 > 0 ? 4 * KS2 : a.H, D = a.D;
   const int Dp = KS1 > 0 ? 4 * KS1 : a.Dp;
   const int b0 = wu.x * kTrainRows;
-  const int sx = Dp + 1, sh = H + 1;
-  float* XS = sm;                       // [16][sx]
+  const int sx = Dp + 4, sh = H + 4;
+  constexpr int kWaves = kTrainThreads / 64;
+  float* XS = sm;                       // [16][sx], K-permuted like the next
   float* H1 = XS + kTrainRows * sx;     // [16][sh]
   float* H2 = H1 + kTrainRows * sh;
   float* D2 = H2 + kTrainRows * sh;
@@ -1074,6 +1072,10 @@ __global__ __launch_bounds__(512) void k_train_fwd(SurArgs a) {
   const float* w1t = a.w1t + (size_t)run * D * H;
   const float* w2t = a.w2t + (size_t)run * H * H;
   const size_t rb = (size_t)run * a.B + b0;
+  const int nblk = H / 16;
+  const int n0 = min(wave, nblk - 1) * 16 + li;  // the wave's first column
+  TrainB tb;
+  train_ahead<KS1>(tb, w1t + n0, H, D, lq);
   if (tid < kTrainRows) {
     const Words4 w = draw_block(kTagTrain, (uint32_t)run, a.step,
                                 (uint32_t)(b0 + tid), 0u, a.mkey_lo,
@@ -1081,57 +1083,55 @@ __global__ __launch_bounds__(512) void k_train_fwd(SurArgs a) {
     src[tid] = uniform_below(w.w[0], (uint32_t)a.filled);
   }
   __syncthreads();
-  for (int t = tid; t < kTrainRows * Dp; t += 512) {
+  for (int t = tid; t < kTrainRows * Dp; t += kTrainThreads) {
     const int r = t / Dp, dd = t - r * Dp;
     const float v =
         dd < D ? fmaf(a.ax[((size_t)run * a.cap + src[r]) * a.ldx + dd],
                       a.xs_mul, a.xs_add)
                : 0.f;
-    XS[r * sx + dd] = v;
+    XS[r * sx + comp_pos(dd)] = v;
     a.xsb[(rb + r) * Dp + dd] = v;
   }
   __syncthreads();
-  const int nblk = H / 16;
   // the lane's C values: rows 4 lq + r, column li of each block
-  for (int nb = wave; nb < nblk; nb += 16) {  // layer 1: B(k, n) = W1[n][k]
-    const bool two = nb + 8 < nblk;
-    floatx4 c[2];
-    mfma16_pair<KS1>(XS + li * sx, w1t, nb * 16 + li, (nb + 8) * 16 + li, H,
-                     Dp, D, lq, two, c[0], c[1]);
-    for (int q = 0; q < (two ? 2 : 1); ++q) {
-      const int n = (nb + 8 * q) * 16 + li;
+  for (int nb = wave; nb < nblk; nb += kWaves) {  // layer 1: B(k, n) = W1[n][k]
+    const int n = nb * 16 + li;
+    if (nb != wave) train_ahead<KS1>(tb, w1t + n, H, D, lq);
+    const floatx4 c =
+        train_block<KS1>(tb, XS + li * sx + 4 * lq, w1t + n, H, Dp, D, lq);
+    if (nb + kWaves >= nblk) train_ahead<KS2>(tb, w2t + n0, H, H, lq);
+    const float bb = b1[n];
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int row = 4 * lq + r;
-        const float v = fmaxf(c[q][r] + b1[n], 0.f);
-        H1[row * sh + n] = v;
-        a.h1b[(rb + row) * H + n] = v;
-      }
+    for (int r = 0; r < 4; ++r) {
+      const int row = 4 * lq + r;
+      const float v = fmaxf(c[r] + bb, 0.f);
+      H1[row * sh + comp_pos(n)] = v;
+      a.h1b[(rb + row) * H + n] = v;
     }
   }
   __syncthreads();
-  for (int nb = wave; nb < nblk; nb += 16) {  // layer 2: B(k, n) = W2[n][k]
-    const bool two = nb + 8 < nblk;
-    floatx4 c[2];
-    mfma16_pair<KS2>(H1 + li * sh, w2t, nb * 16 + li, (nb + 8) * 16 + li, H,
-                     H, H, lq, two, c[0], c[1]);
-    for (int q = 0; q < (two ? 2 : 1); ++q) {
-      const int n = (nb + 8 * q) * 16 + li;
+  for (int nb = wave; nb < nblk; nb += kWaves) {  // layer 2: B(k, n) = W2[n][k]
+    const int n = nb * 16 + li;
+    if (nb != wave) train_ahead<KS2>(tb, w2t + n, H, H, lq);
+    const floatx4 c =
+        train_block<KS2>(tb, H1 + li * sh + 4 * lq, w2t + n, H, H, H, lq);
+    if (nb + kWaves >= nblk) train_ahead<KS2>(tb, W2 + n0, H, H, lq);
+    const float bb = b2[n];
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int row = 4 * lq + r;
-        const float v = fmaxf(c[q][r] + b2[n], 0.f);
-        H2[row * sh + n] = v;
-        a.h2b[(rb + row) * H + n] = v;
-      }
+    for (int r = 0; r < 4; ++r) {
+      const int row = 4 * lq + r;
+      const float v = fmaxf(c[r] + bb, 0.f);
+      H2[row * sh + comp_pos(n)] = v;
+      a.h2b[(rb + row) * H + n] = v;
     }
   }
   __syncthreads();
-  {
+  if (tid < 32 * kTrainRows) {
     // y of row r from 32 partial sums (i = part mod 32), then a butterfly
     const int r = tid / 32, part = tid % 32;
     float y = 0.f;
-    for (int i = part; i < H; i += 32) y = fmaf(w3[i], H2[r * sh + i], y);
+    for (int i = part; i < H; i += 32)
+      y = fmaf(w3[i], H2[r * sh + comp_pos(i)], y);
     y += __shfl_xor(y, 1, 64);
     y += __shfl_xor(y, 2, 64);
     y += __shfl_xor(y, 4, 64);
@@ -1145,25 +1145,23 @@ __global__ __launch_bounds__(512) void k_train_fwd(SurArgs a) {
     }
   }
   __syncthreads();
-  for (int t = tid; t < kTrainRows * H; t += 512) {
+  for (int t = tid; t < kTrainRows * H; t += kTrainThreads) {
     const int r = t / H, i = t - r * H;
-    const float dv = H2[r * sh + i] > 0.f ? E[r] * w3[i] : 0.f;
-    D2[r * sh + i] = dv;
+    const float dv = H2[r * sh + comp_pos(i)] > 0.f ? E[r] * w3[i] : 0.f;
+    D2[r * sh + comp_pos(i)] = dv;
     a.d2b[(rb + r) * H + i] = dv;
   }
   __syncthreads();
-  for (int nb = wave; nb < nblk; nb += 16) {  // delta1: B(k = i, n = j) = W2[i][j]
-    const bool two = nb + 8 < nblk;
-    floatx4 c[2];
-    mfma16_pair<KS2>(D2 + li * sh, W2, nb * 16 + li, (nb + 8) * 16 + li, H,
-                     H, H, lq, two, c[0], c[1]);
-    for (int q = 0; q < (two ? 2 : 1); ++q) {
-      const int n = (nb + 8 * q) * 16 + li;
+  for (int nb = wave; nb < nblk; nb += kWaves) {  // delta1: B(k = i, n = j) = W2[i][j]
+    const int n = nb * 16 + li;
+    if (nb != wave) train_ahead<KS2>(tb, W2 + n, H, H, lq);
+    const floatx4 c =
+        train_block<KS2>(tb, D2 + li * sh + 4 * lq, W2 + n, H, H, H, lq);
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int row = 4 * lq + r;
-        a.d1b[(rb + row) * H + n] = H1[row * sh + n] > 0.f ? c[q][r] : 0.f;
-      }
+    for (int r = 0; r < 4; ++r) {
+      const int row = 4 * lq + r;
+      a.d1b[(rb + row) * H + n] =
+          H1[row * sh + comp_pos(n)] > 0.f ? c[r] : 0.f;
     }
   }
 }
@@ -1203,7 +1201,7 @@ __device__ __forceinline__ floatx16 mfma_block_mm(const float* ap, int astep,
                                                   const float* bp,
                                                   int bstep) {
   static_assert(KS % 8 == 0, "K-steps in groups of eight");
-  constexpr int P = KS < 32 ? KS : 32;  // K-steps in flight
+  constexpr int P = KS < 16 ? KS : 16;  // K-steps in flight
   float av[KS], bv[KS];
 #pragma unroll
   for (int u = 0; u < P; ++u) {
@@ -1233,7 +1231,8 @@ __device__ __forceinline__ floatx16 mfma_block_mm(const float* ap, int astep,
 // the BF16 inference copy and the FP32 transposed copy.  KS = B / 2 when the
 // minibatch size is compile-time (the deep-prefetch product), else 0.
 template <int KS>
-__global__ __launch_bounds__(256) void k_train_grad(SurArgs a) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))
+void k_train_grad(SurArgs a) {
   __shared__ float tblk[4][32][33];  // one 32x32 block per wave (+1 column)
   const RunUnit wu = run_unit();
   const int run = wu.run;
@@ -1257,6 +1256,27 @@ __global__ __launch_bounds__(256) void k_train_grad(SurArgs a) {
   const int ldh = w1 ? Dp : H;
   const float* hv = w1 ? a.xsb + (size_t)run * B * Dp : a.h1b + (size_t)run * B * H;
   const int i = ib * 32 + li, j = jb * 32 + li;
+  // the lane's 16 entries: the entries are distinct, so every m, v and theta
+  // is read before any is written, and before the product, whose operands
+  // take another round trip
+  const size_t base = (size_t)run * a.pstride;
+  const int jj = jb * 32 + li;
+  const bool valid = !w1 || jj < D;
+  float mo[16], vo[16], to[16];
+  auto read_state = [&] {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int ii = ib * 32 + c_row(r, lane);
+      const size_t at = w1 ? base + (size_t)ii * D + jj
+                           : base + (size_t)H * D + H + (size_t)ii * H + jj;
+      if (valid) {
+        mo[r] = a.m[at];
+        vo[r] = a.v[at];
+        to[r] = a.theta[at];
+      }
+    }
+  };
+  if constexpr (KS > 0) read_state();
   // A(i, b) = delta[b][i], B(b, j) = input[b][j]; B is a multiple of 32
   floatx16 c;
   if constexpr (KS > 0)
@@ -1265,23 +1285,7 @@ __global__ __launch_bounds__(256) void k_train_grad(SurArgs a) {
   else
     c = mfma_block(dl + (size_t)lk * H + i, H, hv + (size_t)lk * ldh + j, ldh,
                    B, B, lk);
-  // Adam on the lane's 16 entries: the entries are distinct, so every m, v
-  // and theta is read before any is written and the reads share one wait
-  const size_t base = (size_t)run * a.pstride;
-  const int jj = jb * 32 + li;
-  const bool valid = !w1 || jj < D;
-  float mo[16], vo[16], to[16];
-#pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    const int ii = ib * 32 + c_row(r, lane);
-    const size_t at = w1 ? base + (size_t)ii * D + jj
-                         : base + (size_t)H * D + H + (size_t)ii * H + jj;
-    if (valid) {
-      mo[r] = a.m[at];
-      vo[r] = a.v[at];
-      to[r] = a.theta[at];
-    }
-  }
+  if constexpr (KS == 0) read_state();  // fewer registers, no spills
   // the block's new weights (0 in W1's padding columns) go through LDS so
   // that the transposed copy is written in rows of 32 and the BF16
   // fragment copy in 16-byte pieces
@@ -1650,7 +1654,7 @@ de_status set_lds_attributes() {
 // run): the register-resident kernel for padded widths up to 128 and
 // H in {32, 64, 128, 256}, else the general one.
 using InferRes = void (*)(SurArgs, const float*, size_t, int, int, float*,
-                          size_t, int);
+                          size_t, int, int, int);
 
 template <int KB1>
 InferRes infer_res_for_h(int H) {
@@ -1677,14 +1681,22 @@ de_status launch_infer(const SurArgs& a, const float* X, size_t x_stride,
                        int n, int ldx, float* y, size_t y_stride, int run0,
                        int nruns, hipStream_t st) {
   if (const InferRes fn = infer_res_kernel(a.Dp, a.H)) {
-    const int tiles = (n + de::kInferRows - 1) / de::kInferRows;
-    const size_t lds = (size_t)de::kInferRows * (a.Dp + 8) * 2 +
-                       (size_t)de::kInferRows * (a.H + 8) * 2 +
-                       (size_t)(a.H / 32) * de::kInferRows * 4;
-    hipLaunchKernelGGL(fn,
-                       dim3((tiles + de::kResTiles - 1) / de::kResTiles, nruns),
+    // as many tiles per workgroup as fill the compute units once (each
+    // workgroup loads the weights once), at most eight
+    const long long tiles = (n + de::kResRows - 1) / de::kResRows;
+    const long long cus = de::device_cus();
+    const int per = (int)std::min<long long>(
+        8, std::max<long long>(1, (tiles * nruns + cus - 1) / cus));
+    const size_t lds = (size_t)de::kResRows *
+                       ((a.Dp + 8) * 2 + (a.H + 8) * 2 + (a.H / 32) * 4);
+    const de_status rc =
+        FROM_HIP(de::set_max_dynamic_lds(reinterpret_cast<const void*>(fn)));
+    if (rc != DE_OK) return rc;
+    const int vec = ldx % 4 == 0 && reinterpret_cast<uintptr_t>(X) % 16 == 0 &&
+                    x_stride % 4 == 0;
+    hipLaunchKernelGGL(fn, dim3((unsigned)((tiles + per - 1) / per), nruns),
                        dim3(64 * (a.H / 32)), lds, st, a, X, x_stride, n, ldx,
-                       y, y_stride, run0);
+                       y, y_stride, run0, per, vec);
   } else {
     hipLaunchKernelGGL(de::k_mlp_infer,
                        dim3((n + de::kInferRows - 1) / de::kInferRows, nruns),
@@ -1714,22 +1726,25 @@ de_status train_steps(de_sur* s, int n, hipStream_t st) {
     // every B value requested at once
     if (a.Dp == 128 && a.H == 256)
       hipLaunchKernelGGL((de::k_train_fwd<32, 64>),
-                         dim3(a.B / de::kTrainRows, a.runs), dim3(512), lds,
-                         st, a);
+                         dim3(a.B / de::kTrainRows, a.runs),
+                         dim3(de::kTrainThreads), lds, st, a);
     else
       hipLaunchKernelGGL((de::k_train_fwd<0, 0>),
-                         dim3(a.B / de::kTrainRows, a.runs), dim3(512), lds,
-                         st, a);
+                         dim3(a.B / de::kTrainRows, a.runs),
+                         dim3(de::kTrainThreads), lds, st, a);
     de_status rc = FROM_HIP(hipGetLastError());
     if (rc != DE_OK) return rc;
     const int nblocks = (a.H / 32) * (a.Dp / 32) + (a.H / 32) * (a.H / 32);
     const int wgs = (nblocks + 3) / 4 + (3 * a.H + 1 + 255) / 256;
-    // minibatches of 128 and 256: the deep-prefetch product
+    // minibatches of 64, 128 and 256: the deep-prefetch product
     if (a.B == 256)
       hipLaunchKernelGGL((de::k_train_grad<128>), dim3(wgs, a.runs),
                          dim3(256), 0, st, a);
     else if (a.B == 128)
       hipLaunchKernelGGL((de::k_train_grad<64>), dim3(wgs, a.runs),
+                         dim3(256), 0, st, a);
+    else if (a.B == 64)
+      hipLaunchKernelGGL((de::k_train_grad<32>), dim3(wgs, a.runs),
                          dim3(256), 0, st, a);
     else
       hipLaunchKernelGGL((de::k_train_grad<0>), dim3(wgs, a.runs), dim3(256),

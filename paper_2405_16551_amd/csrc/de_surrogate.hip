@@ -589,9 +589,9 @@ __global__ __launch_bounds__(256) void k_mlp_infer(SurArgs a, const float* X,
 // the blocks in order, then b3.
 // Bound: the chain of barriers and LDS round trips of a tile (LDS and matrix
 // time are both 3 us per 128 rows and CU).  Four row blocks per barrier
-// instead of two and no per-value writes: 36.7 -> INF_US us at 30 x 2048
+// instead of two and no per-value writes: 36.7 -> 19.5 us at 30 x 2048
 // rows, D 100, H 256; with tiles dealt to all CUs, 2048 rows of one run
-// 33 -> PRED_US us.
+// 33 -> 10 us.
 constexpr int kResRows = 128;
 
 template <int KB1, int KB2>
@@ -1042,7 +1042,7 @@ __device__ __forceinline__ floatx4 train_block(TrainB& t, const float* ap,
 // workgroups, one per CU, 10 us of matrix time) and the round trips between
 // them.  One block per wave leaves four waves per SIMD to cover each
 // other, and the next product's first B values are requested before the
-// current one's results are exchanged: 29.3 -> FWD_US us per step.
+// current one's results are exchanged: 29.3 -> 24.5 us per step.
 // KS1 = Dp / 4 and KS2 = H / 4 when the sizes are compile-time, else 0.
 template <int KS1, int KS2>
 __global__ __launch_bounds__(kTrainThreads) void k_train_fwd(SurArgs a) {

@@ -150,12 +150,9 @@ struct Donors {
   int r1, r2, r3, jrand;
 };
 
-// ctr_i is the counter's individual field (i itself, or i | c << 24 for
-// candidate c of the surrogate-assisted step); i is the target to avoid.
-__host__ __device__ __forceinline__ Donors pick_donors_ctr(
-    uint32_t run, uint32_t gen, uint32_t ctr_i, int i, int NP, int D,
-    uint32_t key_lo, uint32_t key_hi) {
-  const Words4 w = draw_block(kTagIdx, run, gen, ctr_i, 0u, key_lo, key_hi);
+// From the words of the individual's IDX block; i is the target to avoid.
+__host__ __device__ __forceinline__ Donors donors_of(const Words4& w, int i,
+                                                     int NP, int D) {
   Donors d;
   const int a = uniform_below(w.w[0], (uint32_t)(NP - 1));
   d.r1 = a + (a >= i ? 1 : 0);
@@ -175,6 +172,15 @@ __host__ __device__ __forceinline__ Donors pick_donors_ctr(
   d.r3 = c;
   d.jrand = uniform_below(w.w[3], (uint32_t)D);
   return d;
+}
+
+// ctr_i is the counter's individual field (i itself, or i | c << 24 for
+// candidate c of the surrogate-assisted step).
+__host__ __device__ __forceinline__ Donors pick_donors_ctr(
+    uint32_t run, uint32_t gen, uint32_t ctr_i, int i, int NP, int D,
+    uint32_t key_lo, uint32_t key_hi) {
+  return donors_of(draw_block(kTagIdx, run, gen, ctr_i, 0u, key_lo, key_hi), i,
+                   NP, D);
 }
 
 __host__ __device__ __forceinline__ Donors pick_donors(uint32_t run, uint32_t gen,
@@ -276,15 +282,43 @@ __host__ __device__ __forceinline__ float sin_squared(float t) {
   return ((int)k & 1) ? 1.0f - p : p;
 }
 
+#if defined(__HIPCC__)
+// v of lane l ^ m, for m = 1, 2, 4, 8 within a row of 16 lanes by data-parallel
+// moves (a few clocks instead of an LDS round trip), 16 and 32 through the
+// LDS crossbar.
+template <int ctrl>
+__device__ __forceinline__ float dpp_move(float v) {
+  return __builtin_bit_cast(
+      float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), ctrl,
+                                         0xF, 0xF, true));
+}
+
+template <int m>
+__device__ __forceinline__ float lane_xor(float v) {
+  if constexpr (m == 1) return dpp_move<0xB1>(v);   // quad 1 0 3 2
+  if constexpr (m == 2) return dpp_move<0x4E>(v);   // quad 2 3 0 1
+  if constexpr (m == 4) return dpp_move<0x1B>(dpp_move<0x141>(v));  // 7-l, 3-l
+  if constexpr (m == 8) return dpp_move<0x128>(v);  // row rotated by 8
+  if constexpr (m == 16)
+    return __builtin_bit_cast(
+        float, __builtin_amdgcn_ds_swizzle(__builtin_bit_cast(int, v), 0x401F));
+  return __shfl_xor(v, m, 64);
+}
+
 // Sum over aligned groups of `width` lanes (power of two <= 64) by
 // butterfly exchange; every lane of the group ends with the same total, and
 // the order of additions is fixed.
 template <int width>
 __device__ __forceinline__ float group_sum(float v) {
-#pragma unroll
-  for (int m = width / 2; m >= 1; m >>= 1) v += __shfl_xor(v, m, 64);
+  if constexpr (width >= 64) v += lane_xor<32>(v);
+  if constexpr (width >= 32) v += lane_xor<16>(v);
+  if constexpr (width >= 16) v += lane_xor<8>(v);
+  if constexpr (width >= 8) v += lane_xor<4>(v);
+  if constexpr (width >= 4) v += lane_xor<2>(v);
+  if constexpr (width >= 2) v += lane_xor<1>(v);
   return v;
 }
+#endif
 
 // Block index remapping so that consecutive logical blocks land on the same
 // XCD (gfx950 dispatches block b to XCD b mod 8): logical block ranges, and

@@ -7,6 +7,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <chrono>
 #include <cmath>
 #include <cstdint>
 #include <cstdlib>
@@ -126,11 +127,13 @@ struct de_state {
   int jde;
   float jF_lo, jF_span;
   uint32_t jtau_F, jtau_CR;
-  // de_evolve's overlapped polling: two pinned host slots for the device's
-  // done counter and the events that mark their copies; created on the
-  // first de_evolve call, released by de_destroy
-  unsigned int* poll_slot;
+  // de_evolve's overlapped polling: pinned host memory ({seq, done count}
+  // words kPollSlots, then the first-hit generations of up to kPollHits
+  // runs) that kernels write, the events behind them, and the number of the
+  // last post; created on the first de_evolve call, released by de_destroy
+  unsigned long long* poll_slot;
   hipEvent_t poll_ev[2];
+  uint32_t poll_seq;
   // staggered run groups (see run_staggered): two streams and their events,
   // created on first use, released by de_destroy; the last measured time
   // per generation (0: none yet) and the generations timed by t0..t1 whose
@@ -229,6 +232,12 @@ GenArgs base_args(const de_state* s) {
   return a;
 }
 
+// One workgroup restarts the statistics of this many rows faster than four
+// launches do.
+bool small_rows(const de_state* s) {
+  return (long long)s->p.runs * s->p.NP <= de::kBeginMaxRows;
+}
+
 // f of pop[gen & 1] into fit[gen & 1], then statistics restart.
 de_status eval_current_and_reset(de_state* s, hipStream_t st) {
   GenArgs a = base_args(s);
@@ -237,6 +246,11 @@ de_status eval_current_and_reset(de_state* s, hipStream_t st) {
   a.fit_next = s->fit[b];
   de_status rc = FROM_HIP(de::launch_eval(a, s->kind, s->prec, st));
   if (rc != DE_OK) return rc;
+  if (small_rows(s)) {
+    a.fit_cur = s->fit[b];
+    return FROM_HIP(de::launch_begin(
+        a, de::kBeginAccepted | de::kBeginStale, 0, nullptr, 0, st));
+  }
   rc = FROM_HIP(de::launch_stats_reset(a, true, st));
   if (rc != DE_OK) return rc;
   // the other buffer's rows are unknown: the next step rewrites every row
@@ -296,6 +310,31 @@ bool stagger_enabled() {
     return !(e && e[0] == '0');
   }();
   return on;
+}
+
+constexpr int kPollSlots = 2, kPollHits = 4096;
+
+// Waits for post number seq in slot: polls the pinned word for a while (a
+// chunk of a small problem takes some tens of microseconds, less than the
+// wake-up from an event), then waits for the event recorded behind the post.
+de_status wait_post(const unsigned long long* slot, uint32_t seq,
+                    hipEvent_t ev, uint32_t* done) {
+  const auto t0 = std::chrono::steady_clock::now();
+  for (int spin = 0;; ++spin) {
+    const unsigned long long v = __atomic_load_n(slot, __ATOMIC_ACQUIRE);
+    if ((uint32_t)(v >> 32) == seq) {
+      *done = (uint32_t)v;
+      return DE_OK;
+    }
+    if (spin % 64 == 63 && std::chrono::steady_clock::now() - t0 >
+                               std::chrono::microseconds(200))
+      break;
+  }
+  const de_status rc = FROM_HIP(hipEventSynchronize(ev));
+  if (rc != DE_OK) return rc;
+  const unsigned long long v = __atomic_load_n(slot, __ATOMIC_ACQUIRE);
+  *done = (uint32_t)v;
+  return (uint32_t)(v >> 32) == seq ? DE_OK : DE_E_DEVICE;
 }
 
 // Fewest generations per call that take the split: the second group's
@@ -714,42 +753,52 @@ DE_API de_status de_evolve(de_state* state, int64_t max_gens, double target,
   const float t32 = float_at_or_below(target);
   GenArgs a = base_args(state);
   de_status rc = DE_OK;
-  // hit bookkeeping restarts for this target: clear, then runs already at
-  // or below it hit at the current generation
-  {
-    GenArgs r = a;
-    rc = FROM_HIP(de::launch_stats_reset(r, false, st));
-    // launch_stats_reset also clears best; rebuild it from the current fit
-    if (rc == DE_OK) {
-      r.fit_cur = state->fit[state->gen & 1];
-      rc = FROM_HIP(de::launch_best_from_fit(r, st));
-    }
-    if (rc == DE_OK) rc = FROM_HIP(de::launch_hit_check(r, key_of(t32), st));
-  }
-  state->target = t32;
-  int64_t done_gens = 0;
-  if (rc == DE_OK && !state->poll_slot) {
+  if (!state->poll_slot) {
     void* h = nullptr;
-    rc = FROM_HIP(hipHostMalloc(&h, 2 * sizeof(unsigned int),
+    rc = FROM_HIP(hipHostMalloc(&h, (kPollSlots + kPollHits) * 8,
                                 hipHostMallocDefault));
-    for (int k = 0; k < 2 && rc == DE_OK; ++k)
+    for (int k = 0; k < kPollSlots && rc == DE_OK; ++k)
       rc = FROM_HIP(hipEventCreateWithFlags(&state->poll_ev[k],
                                             hipEventDisableTiming));
-    state->poll_slot = static_cast<unsigned int*>(h);
+    state->poll_slot = static_cast<unsigned long long*>(h);
+    if (h) std::memset(h, 0, kPollSlots * 8);
   }
-  // Runs already at the target before any generation: read synchronously.
-  unsigned int* slot = state->poll_slot;
-  if (rc == DE_OK) {
-    rc = FROM_HIP(hipMemcpyAsync(&slot[0], a.done, sizeof(unsigned int),
-                                 hipMemcpyDeviceToHost, st));
-    if (rc == DE_OK) rc = FROM_HIP(hipStreamSynchronize(st));
+  if (rc != DE_OK) return rc;
+  unsigned long long* slot = state->poll_slot;
+  // number of the post pending in a slot (0 is never used: the slots start
+  // at it)
+  uint32_t posted[kPollSlots] = {};
+  auto next_seq = [&] {
+    if (++state->poll_seq == 0) ++state->poll_seq;
+    return state->poll_seq;
+  };
+  // hit bookkeeping restarts for this target: clear, then runs already at
+  // or below it hit at the current generation, and the count of those is
+  // waited for before any generation
+  posted[0] = next_seq();
+  a.fit_cur = state->fit[state->gen & 1];
+  if (small_rows(state)) {
+    rc = FROM_HIP(de::launch_begin(a, de::kBeginHits, key_of(t32), &slot[0],
+                                   posted[0], st));
+  } else {
+    rc = FROM_HIP(de::launch_stats_reset(a, false, st));
+    // launch_stats_reset also clears best; rebuild it from the current fit
+    if (rc == DE_OK) rc = FROM_HIP(de::launch_best_from_fit(a, st));
+    if (rc == DE_OK) rc = FROM_HIP(de::launch_hit_check(a, key_of(t32), st));
+    if (rc == DE_OK)
+      rc = FROM_HIP(de::launch_post(a, nullptr, 0, &slot[0], posted[0], st));
   }
-  if (rc == DE_OK && (int)slot[0] < state->p.runs) {
+  if (rc == DE_OK) rc = FROM_HIP(hipEventRecord(state->poll_ev[0], st));
+  uint32_t done = 0;
+  if (rc == DE_OK) rc = wait_post(&slot[0], posted[0], state->poll_ev[0], &done);
+  state->target = t32;
+  int64_t done_gens = 0;
+  if (rc == DE_OK && (int)done < state->p.runs) {
     // Overlapped polling (the solution-found flag copied to the host behind
     // every chunk): each chunk of check_every generations is followed on
-    // the stream by a copy of the done counter into a pinned slot and an
+    // the stream by a post of the done counter to a pinned slot and an
     // event; the next chunk is queued before the host waits for the
-    // previous chunk's event, so the device never idles on the host's round
+    // previous chunk's post, so the device never idles on the host's round
     // trip.  The price is at most one chunk run past the chunk in which the
     // last run hit (the first-hit generations are exact on the device).
     int inflight = 0, head = 0, tail = 0;
@@ -759,36 +808,47 @@ DE_API de_status de_evolve(de_state* state, int64_t max_gens, double target,
         rc = run_generations(state, n, st);
         if (rc != DE_OK) break;
         done_gens += n;
-        rc = FROM_HIP(hipMemcpyAsync(&slot[tail], a.done, sizeof(unsigned int),
-                                     hipMemcpyDeviceToHost, st));
+        posted[tail] = next_seq();
+        rc = FROM_HIP(
+            de::launch_post(a, nullptr, 0, &slot[tail], posted[tail], st));
         if (rc == DE_OK) rc = FROM_HIP(hipEventRecord(state->poll_ev[tail], st));
         tail ^= 1;
         ++inflight;
       }
       if (rc != DE_OK || inflight == 0) break;
-      rc = FROM_HIP(hipEventSynchronize(state->poll_ev[head]));
+      rc = wait_post(&slot[head], posted[head], state->poll_ev[head], &done);
       if (rc != DE_OK) break;
-      const unsigned int done = slot[head];
       head ^= 1;
       --inflight;
       if ((int)done >= state->p.runs) break;
     }
   }
   state->target = -std::numeric_limits<float>::infinity();
+  const int runs = state->p.runs;
+  const bool post_hits = hit_gen && runs <= kPollHits;
+  if (rc == DE_OK && post_hits)
+    rc = FROM_HIP(
+        de::launch_post(a, slot + kPollSlots, runs, &slot[0], next_seq(), st));
   // a chunk queued ahead may still run: the call returns with the stream idle
   if (rc == DE_OK) rc = FROM_HIP(hipStreamSynchronize(st));
   *gens_done = done_gens;
   if (rc == DE_OK && hit_gen) {
-    const int runs = state->p.runs;
-    unsigned long long* tmp = new (std::nothrow) unsigned long long[runs];
-    if (!tmp) return DE_E_NOMEM;
-    rc = FROM_HIP(hipMemcpyAsync(tmp, a.hit_gen, 8 * (size_t)runs,
-                                 hipMemcpyDeviceToHost, st));
-    if (rc == DE_OK) rc = FROM_HIP(hipStreamSynchronize(st));
+    unsigned long long* tmp = slot + kPollSlots;
+    std::vector<unsigned long long> copy;
+    if (!post_hits) {
+      try {
+        copy.resize(runs);
+      } catch (const std::bad_alloc&) {
+        return DE_E_NOMEM;
+      }
+      tmp = copy.data();
+      rc = FROM_HIP(hipMemcpyAsync(tmp, a.hit_gen, 8 * (size_t)runs,
+                                   hipMemcpyDeviceToHost, st));
+      if (rc == DE_OK) rc = FROM_HIP(hipStreamSynchronize(st));
+    }
     if (rc == DE_OK)
       for (int r = 0; r < runs; ++r)
         hit_gen[r] = tmp[r] == ~0ull ? -1 : (int64_t)tmp[r];
-    delete[] tmp;
   }
   return rc;
 }

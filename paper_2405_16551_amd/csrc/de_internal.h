@@ -79,6 +79,15 @@ hipError_t launch_copy_rot(const float* R, int ldr, int D, float* rf32,
                            hipStream_t s);
 hipError_t launch_hit_check(const GenArgs& a, unsigned long long target_key,
                             hipStream_t s);
+// Statistics restart of small populations in one launch, and posts to pinned
+// host memory ({seq, done count} in one 64-bit word).
+enum { kBeginAccepted = 1, kBeginStale = 2, kBeginHits = 4 };
+constexpr long long kBeginMaxRows = 16384;
+hipError_t launch_begin(const GenArgs& a, int what,
+                        unsigned long long target_key,
+                        unsigned long long* slot, uint32_t seq, hipStream_t s);
+hipError_t launch_post(const GenArgs& a, unsigned long long* hits, int nhits,
+                       unsigned long long* slot, uint32_t seq, hipStream_t s);
 hipError_t launch_debug_draws(const GenArgs& a, int* idx4, uint32_t* mask,
                               hipStream_t s);
 

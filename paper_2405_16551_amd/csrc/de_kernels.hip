@@ -376,6 +376,70 @@ __global__ void k_hit_check(GenArgs a, unsigned long long target_key) {
   }
 }
 
+// Restart of the statistics in one workgroup, for populations of at most
+// kBeginMaxRows rows: best and hit of every run from the current values (one
+// wave per run in turn), and as `what` says accepted counts and stale flags.
+// A run whose best is within target_key hit at generation a.gen.  The count
+// of such runs goes to *done, and with the number `seq` to the host's `slot`
+// (null: nowhere).  A call on a small problem is launches and round trips
+// more than work: one launch here replaces three or four.
+__device__ __forceinline__ void post_done(unsigned long long* slot,
+                                          uint32_t seq, uint32_t done) {
+  __hip_atomic_store(slot, ((unsigned long long)seq << 32) | done,
+                     __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+__global__ __launch_bounds__(1024) void k_begin(GenArgs a, int what,
+                                                unsigned long long target_key,
+                                                unsigned long long* slot,
+                                                uint32_t seq) {
+  __shared__ unsigned int s_done;
+  const int wave = (int)threadIdx.x / 64, lane = (int)threadIdx.x % 64;
+  if (threadIdx.x == 0) s_done = 0u;
+  __syncthreads();
+  for (int run = wave; run < a.runs; run += 16) {
+    unsigned long long best = ~0ull;
+    for (int i = lane; i < a.NP; i += 64)
+      best = min(best, fit_key(a.fit_cur[(size_t)run * a.NP + i], i));
+    for (int m = 32; m >= 1; m >>= 1) {
+      const unsigned long long o =
+          ((unsigned long long)__shfl_xor((unsigned)(best >> 32), m, 64)
+           << 32) |
+          (unsigned long long)__shfl_xor((unsigned)best, m, 64);
+      best = min(best, o);
+    }
+    if (lane == 0) {
+      const bool hit = (what & kBeginHits) && best != ~0ull &&
+                       (best >> 32) <= (target_key >> 32);
+      a.best_key[run] = best;
+      a.hit_gen[run] = hit ? (unsigned long long)a.gen : kNoHit;
+      if (hit) atomicAdd(&s_done, 1u);
+      if (what & kBeginAccepted) a.accepted[run] = 0ull;
+    }
+  }
+  if (what & kBeginStale)
+    for (int t = (int)threadIdx.x; t < a.runs * a.NP; t += 1024)
+      a.changed[t] = 1;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    *a.done = s_done;
+    if (slot) post_done(slot, seq, s_done);
+  }
+}
+
+// The done counter, and the first-hit generations of the first nhits runs,
+// to the host (pinned memory).
+__global__ __launch_bounds__(256) void k_post(GenArgs a,
+                                              unsigned long long* hits,
+                                              int nhits,
+                                              unsigned long long* slot,
+                                              uint32_t seq) {
+  for (int r = (int)threadIdx.x; r < nhits; r += 256) hits[r] = a.hit_gen[r];
+  __threadfence_system();
+  __syncthreads();
+  if (threadIdx.x == 0) post_done(slot, seq, *a.done);
+}
+
 // Draws of generation a.gen: idx4 [runs][NP][4], mask [runs][NP][ceil(D/32)].
 __global__ __launch_bounds__(256) void k_debug_draws(GenArgs a, int* idx4,
                                                      uint32_t* mask) {
@@ -1052,6 +1116,21 @@ hipError_t launch_hit_check(const GenArgs& a, unsigned long long target_key,
                             hipStream_t s) {
   hipLaunchKernelGGL(k_hit_check, dim3(grid_for(a.runs, 256)), dim3(256), 0,
                      s, a, target_key);
+  return hipGetLastError();
+}
+
+hipError_t launch_begin(const GenArgs& a, int what,
+                        unsigned long long target_key,
+                        unsigned long long* slot, uint32_t seq, hipStream_t s) {
+  hipLaunchKernelGGL(k_begin, dim3(1), dim3(1024), 0, s, a, what, target_key,
+                     slot, seq);
+  return hipGetLastError();
+}
+
+hipError_t launch_post(const GenArgs& a, unsigned long long* hits, int nhits,
+                       unsigned long long* slot, uint32_t seq, hipStream_t s) {
+  hipLaunchKernelGGL(k_post, dim3(1), dim3(256), 0, s, a, hits, nhits, slot,
+                     seq);
   return hipGetLastError();
 }
 

@@ -37,12 +37,14 @@ constexpr uint64_t kMagic = 0x4445'6d69'3335'3578ull;
 constexpr int64_t kGenLimit = int64_t(1) << 32;  // counter field is 32-bit
 
 struct Layout {
-  // done: the counter, and at kRmaxAt the largest |R|
+  // done: the counter, at kRmaxAt the largest |R|, at kFinishedAt the count
+  // of finished workgroups
   size_t best, hit, acc, done, changed, opad, rop, rf32, f64, idx, jp[2],
       total;
 };
 
-constexpr size_t kRmaxAt = 16;  // within the done counter's 256 bytes
+// within the done counter's 256 bytes
+constexpr size_t kRmaxAt = 16, kFinishedAt = 32;
 
 size_t round_up(size_t v, size_t m) { return (v + m - 1) / m * m; }
 
@@ -134,6 +136,9 @@ struct de_state {
   unsigned long long* poll_slot;
   hipEvent_t poll_ev[2];
   uint32_t poll_seq;
+  // the post that the next generations' last launch may take over (slot
+  // null: none, or taken)
+  de::HostPost pending;
   // staggered run groups (see run_staggered): two streams and their events,
   // created on first use, released by de_destroy; the last measured time
   // per generation (0: none yet) and the generations timed by t0..t1 whose
@@ -249,7 +254,7 @@ de_status eval_current_and_reset(de_state* s, hipStream_t st) {
   if (small_rows(s)) {
     a.fit_cur = s->fit[b];
     return FROM_HIP(de::launch_begin(
-        a, de::kBeginAccepted | de::kBeginStale, 0, nullptr, 0, st));
+        a, de::kBeginAccepted | de::kBeginStale, 0, {}, st));
   }
   rc = FROM_HIP(de::launch_stats_reset(a, true, st));
   if (rc != DE_OK) return rc;
@@ -489,9 +494,11 @@ de_status run_plain(de_state* s, int64_t n, hipStream_t st) {
       a.pop_next = s->pop[b ^ 1];
       a.fit_next = s->fit[b ^ 1];
       const int fb = (int)((s->gen + m) & 1);
+      const de::HostPost post = m == n ? s->pending : de::HostPost{};
       const de_status rc = FROM_HIP(
-          de::launch_sep_resident(a, m, s->pop[fb], s->fit[fb], st));
+          de::launch_sep_resident(a, m, s->pop[fb], s->fit[fb], post, st));
       if (rc != DE_OK) return rc;
+      if (post.slot) s->pending = {};
       s->gen += m;
       n -= m;
     }
@@ -768,25 +775,30 @@ DE_API de_status de_evolve(de_state* state, int64_t max_gens, double target,
   // number of the post pending in a slot (0 is never used: the slots start
   // at it)
   uint32_t posted[kPollSlots] = {};
-  auto next_seq = [&] {
+  auto post_to = [&](int k) {
     if (++state->poll_seq == 0) ++state->poll_seq;
-    return state->poll_seq;
+    posted[k] = state->poll_seq;
+    return de::HostPost{
+        &slot[k],
+        reinterpret_cast<unsigned int*>(state->work + state->L.done +
+                                        kFinishedAt),
+        state->poll_seq};
   };
   // hit bookkeeping restarts for this target: clear, then runs already at
   // or below it hit at the current generation, and the count of those is
   // waited for before any generation
-  posted[0] = next_seq();
+  const de::HostPost first = post_to(0);
   a.fit_cur = state->fit[state->gen & 1];
   if (small_rows(state)) {
-    rc = FROM_HIP(de::launch_begin(a, de::kBeginHits, key_of(t32), &slot[0],
-                                   posted[0], st));
+    rc = FROM_HIP(
+        de::launch_begin(a, de::kBeginHits, key_of(t32), first, st));
   } else {
     rc = FROM_HIP(de::launch_stats_reset(a, false, st));
     // launch_stats_reset also clears best; rebuild it from the current fit
     if (rc == DE_OK) rc = FROM_HIP(de::launch_best_from_fit(a, st));
     if (rc == DE_OK) rc = FROM_HIP(de::launch_hit_check(a, key_of(t32), st));
     if (rc == DE_OK)
-      rc = FROM_HIP(de::launch_post(a, nullptr, 0, &slot[0], posted[0], st));
+      rc = FROM_HIP(de::launch_post(a, nullptr, 0, first, st));
   }
   if (rc == DE_OK) rc = FROM_HIP(hipEventRecord(state->poll_ev[0], st));
   uint32_t done = 0;
@@ -805,12 +817,16 @@ DE_API de_status de_evolve(de_state* state, int64_t max_gens, double target,
     while (rc == DE_OK) {
       while (rc == DE_OK && inflight < 2 && done_gens < max_gens) {
         const int64_t n = std::min<int64_t>(check_every, max_gens - done_gens);
+        // small populations (whose restart cleared the workgroup count):
+        // the chunk's last launch may post by itself
+        const de::HostPost post = post_to(tail);
+        if (small_rows(state)) state->pending = post;
         rc = run_generations(state, n, st);
+        const bool taken = small_rows(state) && !state->pending.slot;
+        state->pending = {};
         if (rc != DE_OK) break;
         done_gens += n;
-        posted[tail] = next_seq();
-        rc = FROM_HIP(
-            de::launch_post(a, nullptr, 0, &slot[tail], posted[tail], st));
+        if (!taken) rc = FROM_HIP(de::launch_post(a, nullptr, 0, post, st));
         if (rc == DE_OK) rc = FROM_HIP(hipEventRecord(state->poll_ev[tail], st));
         tail ^= 1;
         ++inflight;
@@ -828,7 +844,7 @@ DE_API de_status de_evolve(de_state* state, int64_t max_gens, double target,
   const bool post_hits = hit_gen && runs <= kPollHits;
   if (rc == DE_OK && post_hits)
     rc = FROM_HIP(
-        de::launch_post(a, slot + kPollSlots, runs, &slot[0], next_seq(), st));
+        de::launch_post(a, slot + kPollSlots, runs, post_to(0), st));
   // a chunk queued ahead may still run: the call returns with the stream idle
   if (rc == DE_OK) rc = FROM_HIP(hipStreamSynchronize(st));
   *gens_done = done_gens;

@@ -57,8 +57,18 @@ bool sep_supported(int D);
 constexpr size_t kSepResidentMaxLds = 64 * 1024;
 size_t sep_resident_lds_bytes(int NP, int ldx, int D);
 bool sep_resident_fits(int NP, int ldx, int D);
+
+// Where a kernel posts the done counter: a 64-bit word {seq, count} in pinned
+// host memory (null: nowhere), and the device count of finished workgroups
+// of a launch that posts (zero between launches).
+struct HostPost {
+  unsigned long long* slot = nullptr;
+  unsigned int* finished = nullptr;
+  uint32_t seq = 0;
+};
+
 hipError_t launch_sep_resident(const GenArgs& a, int n_gens, float* pop_final,
-                               float* fit_final, hipStream_t s);
+                               float* fit_final, HostPost post, hipStream_t s);
 
 hipError_t launch_generation(const GenArgs& a, int kind, int prec,
                              hipStream_t s);
@@ -79,15 +89,15 @@ hipError_t launch_copy_rot(const float* R, int ldr, int D, float* rf32,
                            hipStream_t s);
 hipError_t launch_hit_check(const GenArgs& a, unsigned long long target_key,
                             hipStream_t s);
-// Statistics restart of small populations in one launch, and posts to pinned
-// host memory ({seq, done count} in one 64-bit word).
+// Statistics restart of small populations in one launch, and the done
+// counter (with the first nhits runs' first-hit generations) to the host.
 enum { kBeginAccepted = 1, kBeginStale = 2, kBeginHits = 4 };
 constexpr long long kBeginMaxRows = 16384;
 hipError_t launch_begin(const GenArgs& a, int what,
-                        unsigned long long target_key,
-                        unsigned long long* slot, uint32_t seq, hipStream_t s);
+                        unsigned long long target_key, HostPost post,
+                        hipStream_t s);
 hipError_t launch_post(const GenArgs& a, unsigned long long* hits, int nhits,
-                       unsigned long long* slot, uint32_t seq, hipStream_t s);
+                       HostPost post, hipStream_t s);
 hipError_t launch_debug_draws(const GenArgs& a, int* idx4, uint32_t* mask,
                               hipStream_t s);
 

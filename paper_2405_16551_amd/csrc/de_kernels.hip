@@ -376,6 +376,13 @@ __global__ void k_hit_check(GenArgs a, unsigned long long target_key) {
   }
 }
 
+// The word the host waits for: post number and done counter.
+__device__ __forceinline__ void post_done(unsigned long long* slot,
+                                          uint32_t seq, uint32_t done) {
+  __hip_atomic_store(slot, ((unsigned long long)seq << 32) | done,
+                     __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // Restart of the statistics in one workgroup, for populations of at most
 // kBeginMaxRows rows: best and hit of every run from the current values (one
 // wave per run in turn), and as `what` says accepted counts and stale flags.
@@ -383,16 +390,9 @@ __global__ void k_hit_check(GenArgs a, unsigned long long target_key) {
 // of such runs goes to *done, and with the number `seq` to the host's `slot`
 // (null: nowhere).  A call on a small problem is launches and round trips
 // more than work: one launch here replaces three or four.
-__device__ __forceinline__ void post_done(unsigned long long* slot,
-                                          uint32_t seq, uint32_t done) {
-  __hip_atomic_store(slot, ((unsigned long long)seq << 32) | done,
-                     __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
-}
-
 __global__ __launch_bounds__(1024) void k_begin(GenArgs a, int what,
                                                 unsigned long long target_key,
-                                                unsigned long long* slot,
-                                                uint32_t seq) {
+                                                HostPost post) {
   __shared__ unsigned int s_done;
   const int wave = (int)threadIdx.x / 64, lane = (int)threadIdx.x % 64;
   if (threadIdx.x == 0) s_done = 0u;
@@ -423,7 +423,10 @@ __global__ __launch_bounds__(1024) void k_begin(GenArgs a, int what,
   __syncthreads();
   if (threadIdx.x == 0) {
     *a.done = s_done;
-    if (slot) post_done(slot, seq, s_done);
+    if (post.slot) {
+      *post.finished = 0u;
+      post_done(post.slot, post.seq, s_done);
+    }
   }
 }
 
@@ -431,13 +434,11 @@ __global__ __launch_bounds__(1024) void k_begin(GenArgs a, int what,
 // to the host (pinned memory).
 __global__ __launch_bounds__(256) void k_post(GenArgs a,
                                               unsigned long long* hits,
-                                              int nhits,
-                                              unsigned long long* slot,
-                                              uint32_t seq) {
+                                              int nhits, HostPost post) {
   for (int r = (int)threadIdx.x; r < nhits; r += 256) hits[r] = a.hit_gen[r];
   __threadfence_system();
   __syncthreads();
-  if (threadIdx.x == 0) post_done(slot, seq, *a.done);
+  if (threadIdx.x == 0) post_done(post.slot, post.seq, *a.done);
 }
 
 // Draws of generation a.gen: idx4 [runs][NP][4], mask [runs][NP][ceil(D/32)].
@@ -537,7 +538,8 @@ __device__ __forceinline__ ResidentDraws resident_draws(const GenArgs& a,
 template <int LPI>
 __global__ __launch_bounds__(1024) void k_sep_resident(GenArgs a, int n_gens,
                                                        float* pop_final,
-                                                       float* fit_final) {
+                                                       float* fit_final,
+                                                       HostPost post) {
   extern __shared__ __align__(16) float rs[];
   __shared__ unsigned int s_accepted, s_hit;
   __shared__ unsigned long long s_best;
@@ -650,6 +652,14 @@ __global__ __launch_bounds__(1024) void k_sep_resident(GenArgs a, int n_gens,
       const unsigned long long old = atomicMin(
           &a.hit_gen[run], (unsigned long long)a.gen + s_hit + 1ull);
       if (old == kNoHit) atomicAdd(a.done, 1u);
+    }
+    if (post.slot) {
+      // the last workgroup hands the done counter to the host
+      __threadfence();
+      if (atomicAdd(post.finished, 1u) == gridDim.x - 1) {
+        atomicExch(post.finished, 0u);
+        post_done(post.slot, post.seq, atomicAdd(a.done, 0u));
+      }
     }
   }
 }
@@ -850,7 +860,7 @@ hipError_t launch_sep_e(const GenArgs& a, hipStream_t s) {
 
 template <int LPI>
 hipError_t launch_resident_t(const GenArgs& a, int n_gens, float* pop_final,
-                             float* fit_final, hipStream_t s) {
+                             float* fit_final, HostPost post, hipStream_t s) {
   const void* fn = reinterpret_cast<const void*>(&k_sep_resident<LPI>);
   const hipError_t e = set_max_dynamic_lds(fn);
   if (e != hipSuccess) return e;
@@ -858,7 +868,7 @@ hipError_t launch_resident_t(const GenArgs& a, int n_gens, float* pop_final,
   threads = std::min(std::max(threads, 64), 1024);
   hipLaunchKernelGGL((k_sep_resident<LPI>), dim3(a.runs), dim3(threads),
                      sep_resident_lds_bytes(a.NP, a.ldx, a.D), s, a, n_gens,
-                     pop_final, fit_final);
+                     pop_final, fit_final, post);
   return hipGetLastError();
 }
 
@@ -974,16 +984,17 @@ bool sep_resident_fits(int NP, int ldx, int D) {
 }
 
 hipError_t launch_sep_resident(const GenArgs& a, int n_gens, float* pop_final,
-                               float* fit_final, hipStream_t s) {
+                               float* fit_final, HostPost post,
+                               hipStream_t s) {
   const int nq = (a.D + 3) / 4;
-  if (nq <= 4) return launch_resident_t<4>(a, n_gens, pop_final, fit_final, s);
-  if (nq <= 8) return launch_resident_t<8>(a, n_gens, pop_final, fit_final, s);
+  if (nq <= 4) return launch_resident_t<4>(a, n_gens, pop_final, fit_final, post, s);
+  if (nq <= 8) return launch_resident_t<8>(a, n_gens, pop_final, fit_final, post, s);
   if (nq <= 16)
-    return launch_resident_t<16>(a, n_gens, pop_final, fit_final, s);
+    return launch_resident_t<16>(a, n_gens, pop_final, fit_final, post, s);
   if (nq <= 32)
-    return launch_resident_t<32>(a, n_gens, pop_final, fit_final, s);
+    return launch_resident_t<32>(a, n_gens, pop_final, fit_final, post, s);
   if (nq <= 64)
-    return launch_resident_t<64>(a, n_gens, pop_final, fit_final, s);
+    return launch_resident_t<64>(a, n_gens, pop_final, fit_final, post, s);
   return hipErrorInvalidValue;
 }
 
@@ -1120,17 +1131,16 @@ hipError_t launch_hit_check(const GenArgs& a, unsigned long long target_key,
 }
 
 hipError_t launch_begin(const GenArgs& a, int what,
-                        unsigned long long target_key,
-                        unsigned long long* slot, uint32_t seq, hipStream_t s) {
+                        unsigned long long target_key, HostPost post,
+                        hipStream_t s) {
   hipLaunchKernelGGL(k_begin, dim3(1), dim3(1024), 0, s, a, what, target_key,
-                     slot, seq);
+                     post);
   return hipGetLastError();
 }
 
 hipError_t launch_post(const GenArgs& a, unsigned long long* hits, int nhits,
-                       unsigned long long* slot, uint32_t seq, hipStream_t s) {
-  hipLaunchKernelGGL(k_post, dim3(1), dim3(256), 0, s, a, hits, nhits, slot,
-                     seq);
+                       HostPost post, hipStream_t s) {
+  hipLaunchKernelGGL(k_post, dim3(1), dim3(256), 0, s, a, hits, nhits, post);
   return hipGetLastError();
 }
 

@@ -15,6 +15,7 @@
 #include <limits>
 #include <mutex>
 #include <new>
+#include <thread>
 #include <unordered_set>
 #include <vector>
 
@@ -321,25 +322,35 @@ constexpr int kPollSlots = 2, kPollHits = 4096;
 
 // Waits for post number seq in slot: polls the pinned word for a while (a
 // chunk of a small problem takes some tens of microseconds, less than the
-// wake-up from an event), then waits for the event recorded behind the post.
+// wake-up from an event), then waits for the event recorded behind the post,
+// or, where none is (an event is a packet of its own between two launches),
+// keeps polling and looks whether the stream has ended or failed.
 de_status wait_post(const unsigned long long* slot, uint32_t seq,
-                    hipEvent_t ev, uint32_t* done) {
+                    hipEvent_t ev, hipStream_t st, uint32_t* done) {
+  auto posted = [&] {
+    const unsigned long long v = __atomic_load_n(slot, __ATOMIC_ACQUIRE);
+    *done = (uint32_t)v;
+    return (uint32_t)(v >> 32) == seq;
+  };
   const auto t0 = std::chrono::steady_clock::now();
   for (int spin = 0;; ++spin) {
-    const unsigned long long v = __atomic_load_n(slot, __ATOMIC_ACQUIRE);
-    if ((uint32_t)(v >> 32) == seq) {
-      *done = (uint32_t)v;
-      return DE_OK;
-    }
+    if (posted()) return DE_OK;
     if (spin % 64 == 63 && std::chrono::steady_clock::now() - t0 >
                                std::chrono::microseconds(200))
       break;
   }
-  const de_status rc = FROM_HIP(hipEventSynchronize(ev));
-  if (rc != DE_OK) return rc;
-  const unsigned long long v = __atomic_load_n(slot, __ATOMIC_ACQUIRE);
-  *done = (uint32_t)v;
-  return (uint32_t)(v >> 32) == seq ? DE_OK : DE_E_DEVICE;
+  if (ev) {
+    const de_status rc = FROM_HIP(hipEventSynchronize(ev));
+    if (rc != DE_OK) return rc;
+    return posted() ? DE_OK : DE_E_DEVICE;
+  }
+  for (;;) {
+    const hipError_t e = hipStreamQuery(st);
+    if (posted()) return DE_OK;
+    if (e != hipErrorNotReady) return DE_E_DEVICE;
+    (void)hipGetLastError();
+    std::this_thread::sleep_for(std::chrono::microseconds(20));
+  }
 }
 
 // Fewest generations per call that take the split: the second group's
@@ -800,9 +811,14 @@ DE_API de_status de_evolve(de_state* state, int64_t max_gens, double target,
     if (rc == DE_OK)
       rc = FROM_HIP(de::launch_post(a, nullptr, 0, first, st));
   }
-  if (rc == DE_OK) rc = FROM_HIP(hipEventRecord(state->poll_ev[0], st));
+  // events behind the posts, null where a small problem's launch posts
+  hipEvent_t ev[kPollSlots] = {};
+  if (rc == DE_OK && !small_rows(state)) {
+    ev[0] = state->poll_ev[0];
+    rc = FROM_HIP(hipEventRecord(ev[0], st));
+  }
   uint32_t done = 0;
-  if (rc == DE_OK) rc = wait_post(&slot[0], posted[0], state->poll_ev[0], &done);
+  if (rc == DE_OK) rc = wait_post(&slot[0], posted[0], ev[0], st, &done);
   state->target = t32;
   int64_t done_gens = 0;
   if (rc == DE_OK && (int)done < state->p.runs) {
@@ -826,13 +842,15 @@ DE_API de_status de_evolve(de_state* state, int64_t max_gens, double target,
         state->pending = {};
         if (rc != DE_OK) break;
         done_gens += n;
+        ev[tail] = taken ? nullptr : state->poll_ev[tail];
         if (!taken) rc = FROM_HIP(de::launch_post(a, nullptr, 0, post, st));
-        if (rc == DE_OK) rc = FROM_HIP(hipEventRecord(state->poll_ev[tail], st));
+        if (rc == DE_OK && ev[tail])
+          rc = FROM_HIP(hipEventRecord(ev[tail], st));
         tail ^= 1;
         ++inflight;
       }
       if (rc != DE_OK || inflight == 0) break;
-      rc = wait_post(&slot[head], posted[head], state->poll_ev[head], &done);
+      rc = wait_post(&slot[head], posted[head], ev[head], st, &done);
       if (rc != DE_OK) break;
       head ^= 1;
       --inflight;

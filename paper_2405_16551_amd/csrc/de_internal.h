@@ -20,7 +20,7 @@ struct GenArgs {
   float* fit_next;        // f of generation g+1 (EVAL: output values)
   const float* o;         // shift, zero-padded to dpad
   const void* rop;        // R in the MFMA B-operand layout (rotated only)
-  const float* rmax;      // largest |R| (FP32 product over 128 wide only)
+  const float* rmax;      // largest |R| (split FP32 product only)
   unsigned long long* best_key;  // [runs] ordered (f, index) keys
   unsigned long long* hit_gen;   // [runs] first generation with best <= target
   unsigned long long* accepted;  // [runs] accepted trials

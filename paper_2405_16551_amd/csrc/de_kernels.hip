@@ -131,12 +131,13 @@ __global__ __launch_bounds__(256) void k_sep(GenArgs a) {
   }
 }
 
-// BF16 tiles of fewer than 1024 threads: two workgroups per CU (four
-// waves per SIMD, 128 registers).
+// BF16 tiles of fewer than 1024 threads and paired split tiles: two
+// workgroups per CU (four waves per SIMD, 128 registers).
 template <class P, int BM, int NT, bool EVAL, bool JDE, bool PAIR = false>
 __global__ __launch_bounds__(NT)
 __attribute__((amdgpu_waves_per_eu(
-    (sizeof(typename P::T) == 2 && NT < 1024) ? 4 : 1)))
+    ((sizeof(typename P::T) == 2 && NT < 1024) || (P::kSplit && PAIR)) ? 4
+                                                                       : 1)))
 void k_rot(GenArgs a) {
   const int lb = xcd_logical_block((int)blockIdx.x, (int)gridDim.x);
   int run = 0, row0 = 0, nvalid = 0;
@@ -897,14 +898,19 @@ hipError_t launch_rot_e(const GenArgs& a, int prec, hipStream_t s) {
   const long long tiles = EVAL ? (a.nrows + 63) / 64
                                : (long long)a.runs * ((a.NP + 63) / 64);
   const bool narrow = rot_bf16_narrow(a.dpad, tiles, device_cus());
-  // FP32 product over 128 wide: split halves, one column block per wave as
-  // long as two would leave waves without any (256: eight blocks)
+  // FP32 product of kSplitMinD coordinates and more: split halves, one column
+  // block per wave as long as two would leave waves without any (256: eight
+  // blocks)
+  const bool split = a.D >= kSplitMinD;
   const bool split_narrow = a.dpad <= kSplitNarrowMaxDpad;
   if (!EVAL && a.jde) {
     // padded width up to 128: trials built two rows per wave instruction
     if (a.dpad <= kPairMaxDpad) {
       if (prec != kPrecBF16)
-        return launch_rot_t<PrecF32Narrow, 32, 512, false, true, true>(a, s);
+        return split ? launch_rot_t<PrecSplitNarrow, 32, 512, false, true,
+                                    true>(a, s)
+                     : launch_rot_t<PrecF32Narrow, 32, 512, false, true, true>(
+                           a, s);
       return narrow ? launch_rot_t<PrecBF16, 64, kRotBf16ThreadsNarrow, false,
                                    true, true>(a, s)
                     : launch_rot_t<PrecBF16, 64, kRotBf16Threads, false, true,
@@ -923,14 +929,17 @@ hipError_t launch_rot_e(const GenArgs& a, int prec, hipStream_t s) {
   // padded width up to 128: trials built two rows per wave instruction
   if (!EVAL && a.dpad <= kPairMaxDpad) {
     if (prec != kPrecBF16)
-      return launch_rot_t<PrecF32Narrow, 32, 512, false, false, true>(a, s);
+      return split ? launch_rot_t<PrecSplitNarrow, 32, 512, false, false,
+                                  true>(a, s)
+                   : launch_rot_t<PrecF32Narrow, 32, 512, false, false, true>(
+                         a, s);
     return narrow ? launch_rot_t<PrecBF16, 64, kRotBf16ThreadsNarrow, false,
                                  false, true>(a, s)
                   : launch_rot_t<PrecBF16, 64, kRotBf16Threads, false, false,
                                  true>(a, s);
   }
   if (prec != kPrecBF16) {
-    if (a.dpad <= kF32MaxDpad)  // evaluation: unpaired
+    if (!split)  // evaluation: unpaired
       return launch_rot_t<PrecF32Narrow, 32, 512, EVAL>(a, s);
     return split_narrow ? launch_rot_t<PrecSplitNarrow, 32, 512, EVAL>(a, s)
                         : launch_rot_t<PrecSplit, 32, 512, EVAL>(a, s);
@@ -1076,7 +1085,7 @@ hipError_t launch_prep(const float* o, const float* R, int ldr, int D,
   if (prec == kPrecBF16) {
     hipLaunchKernelGGL(k_prep_rot_bf16, dim3(grid_for(total, 256)), dim3(256),
                        0, s, R, ldr, D, dpad, reinterpret_cast<__bf16*>(rop));
-  } else if (dpad > kF32MaxDpad) {
+  } else if (D >= kSplitMinD) {
     hipLaunchKernelGGL(k_rot_max, dim3(D), dim3(256), 0, s, R, ldr, D, rmax);
     e = hipGetLastError();
     if (e != hipSuccess) return e;

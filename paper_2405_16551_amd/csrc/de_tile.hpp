@@ -97,8 +97,8 @@ struct PrecF32Narrow {
 //   - A row's scale is that of its own largest |y|, found once the row lies
 //     in LDS (a fixed scale would lose the low halves near the optimum); the
 //     row is split in place, in the space of its FP32 values.
-// Widths over 128 only: below, the tile is bound by latency and the FP32
-// product is as exact.
+// Rows of kSplitMinD coordinates and more; below, the FP32 product is as
+// exact.
 struct PrecSplit {
   using T = float;
   static constexpr int kPad = 4;
@@ -108,7 +108,7 @@ struct PrecSplit {
 struct PrecSplitNarrow : PrecSplit {
   static constexpr bool kOneBlock = true;
 };
-constexpr int kF32MaxDpad = 128;          // FP32 product: the FP32 MFMA tile
+constexpr int kSplitMinD = 32;            // below: the FP32 MFMA tile
 constexpr int kSplitNarrowMaxDpad = 256;  // one column block per wave
 
 typedef _Float16 half8 __attribute__((ext_vector_type(8)));
@@ -412,9 +412,35 @@ __device__ __forceinline__ void rot_tile(const GenArgs& a, int run, int row0,
             yb[2] = (__bf16)y.z;
             yb[3] = (__bf16)y.w;
             *reinterpret_cast<bf16x4*>(arow + j0) = yb;
-          } else {
+          } else if constexpr (!P::kSplit) {
 #pragma unroll
             for (int b = 0; b < 4; ++b) arow[lds_col<P>(j0 + b)] = get(y, b);
+          }
+        }
+        if constexpr (P::kSplit) {
+          // the row's scale from its half-wave, then the quad's halves
+          float m = fmaxf(fmaxf(fabsf(y.x), fabsf(y.y)),
+                          fmaxf(fabsf(y.z), fabsf(y.w)));
+          m = fmaxf(m, lane_xor<16>(m));
+          m = fmaxf(m, lane_xor<8>(m));
+          m = fmaxf(m, lane_xor<4>(m));
+          m = fmaxf(m, lane_xor<2>(m));
+          m = fmaxf(m, lane_xor<1>(m));
+          const RowScale rs = split_scale(m);
+          typedef _Float16 half4 __attribute__((ext_vector_type(4)));
+          half4 h, l;
+#pragma unroll
+          for (int b = 0; b < 4; ++b) {
+            const float x = get(y, b) * rs.scale;
+            h[b] = (_Float16)x;
+            l[b] = (_Float16)(x - (float)h[b]);
+          }
+          if (live) {
+            if (ql == 0) rinv[rl] = rs.inv;
+            half4* p8 = reinterpret_cast<half4*>(
+                reinterpret_cast<float*>(arow) + (j0 & ~7));
+            p8[ql & 1] = h;
+            p8[2 + (ql & 1)] = l;
           }
         }
       }
@@ -528,7 +554,11 @@ __device__ __forceinline__ void rot_tile(const GenArgs& a, int run, int row0,
       }
     }
   }
-  if constexpr (P::kSplit) {
+  if constexpr (P::kSplit && PAIR) {
+    // rows past the tile's last are zero already (as halves too)
+    if ((int)threadIdx.x >= nvalid && (int)threadIdx.x < BM)
+      rinv[threadIdx.x] = 1.f;
+  } else if constexpr (P::kSplit) {
     // each wave splits the rows it built: eight coordinates per lane and
     // step, read as FP32, written back as eight high and eight low halves
     __builtin_amdgcn_wave_barrier();
@@ -645,7 +675,8 @@ __device__ __forceinline__ void rot_tile(const GenArgs& a, int run, int row0,
           reinterpret_cast<const half8*>(a.rop) +
           (size_t)__builtin_amdgcn_readfirstlane(nb0) * (dpad / 16) * 128;
       const int kbn = dpad / 16;  // a multiple of 8
-      constexpr int kRing = NBW == 2 ? 4 : 8;
+      // (half the ring where two tiles share a CU: 128 registers)
+      constexpr int kRing = NBW == 2 || PAIR ? 4 : 8;
       const char* ar = reinterpret_cast<const char*>(At) +
                        (size_t)(lane % 32) * stride * 4 + 32 * (lane / 32);
       half8 bh[kRing][NBW], bl[kRing][NBW], ah[2], al[2];

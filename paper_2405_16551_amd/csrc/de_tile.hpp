@@ -273,6 +273,224 @@ __device__ __forceinline__ void f32_step2(const float* ar, int k8, float4 b0,
 // ballot.  Launchers refuse PAIR beyond it.
 constexpr int kPairMaxDpad = 128;
 
+// What the phases of a tile share about its rows.
+struct RotRows {
+  const float* base;             // the run's population (EVAL: the rows)
+  int* donors;                   // LDS: r1, r2, r3, j_rand per row
+  Control* ctl;                  // LDS, jDE: F', CR' per row
+  unsigned long long* planes;    // LDS: crossover lane masks [row][chunk][4]
+  uint32_t rng_run;
+  int row0, nvalid, stride, tq;
+};
+
+// Chunk t (256 coordinates) of the wave's rows rl = wave + kWaves * k, RB
+// rows at a time, into the A tile, whose column 0 is coordinate 0 of At0.
+template <class P, int RB, int kWaves, bool EVAL, bool JDE>
+__device__ __forceinline__ void build_chunk(const GenArgs& a, const RotRows& c,
+                                            int t, typename P::T* At0) {
+  using T = typename P::T;
+  const int wave = (int)threadIdx.x / 64, lane = (int)threadIdx.x % 64;
+  const int nrow_w =
+      wave < c.nvalid ? (c.nvalid - 1 - wave) / kWaves + 1 : 0;
+  const int dlast = ((a.D + 3) / 4 - 1) * 4;
+  const int q = lane + 64 * t, j0 = 4 * q, jl = min(j0, dlast);
+  const float4 ov = ld4(a.o + jl);
+  // a chunk with the row's end: its coordinates past D are zeroed
+  const bool whole = 256 * (t + 1) <= a.D;
+  XoverCol xc{0, 0, 0, 0};
+  if (!EVAL)
+    xc = xover_col(c.rng_run, a.gen, (uint32_t)q, a.key_lo, a.key_hi);
+  for (int k = 0; k < nrow_w; k += RB) {
+    float4 xv[RB], v1[RB], v2[RB], v3[RB];
+#pragma unroll
+    for (int h = 0; h < RB; ++h) {
+      // row and donor indices are wave-uniform: scalar row pointers
+      const int rl = __builtin_amdgcn_readfirstlane(
+          wave + kWaves * min(k + h, nrow_w - 1));
+      xv[h] = ld4(c.base + (size_t)(c.row0 + rl) * a.ldx + jl);
+      if (!EVAL) {
+        v1[h] = ld4(c.base + (size_t)__builtin_amdgcn_readfirstlane(
+                               c.donors[rl * 4 + 0]) * a.ldx + jl);
+        v2[h] = ld4(c.base + (size_t)__builtin_amdgcn_readfirstlane(
+                               c.donors[rl * 4 + 1]) * a.ldx + jl);
+        v3[h] = ld4(c.base + (size_t)__builtin_amdgcn_readfirstlane(
+                               c.donors[rl * 4 + 2]) * a.ldx + jl);
+      }
+    }
+    // every gather of the step is issued before any of it is used:
+    // keeps the compiler from sinking a row's loads into the guarded
+    // code that consumes them
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int h = 0; h < RB; ++h) {
+      if (k + h >= nrow_w) break;
+      const int rl =
+          __builtin_amdgcn_readfirstlane(wave + kWaves * (k + h));
+      T* arow = At0 + (size_t)rl * c.stride;
+      float4 y;
+      if constexpr (EVAL) {
+#pragma unroll
+        for (int b = 0; b < 4; ++b) set(y, b, get(xv[h], b) - get(ov, b));
+      } else {
+        const int jrand = c.donors[rl * 4 + 3];
+        float Fr = a.F;
+        uint32_t limit = xover_word_limit(a.cr_threshold);
+        if constexpr (JDE) {
+          Fr = c.ctl[rl].F;
+          limit = xover_word_limit(cr_threshold_of(c.ctl[rl].CR));
+        }
+        const XoverRow xr = xover_row(a.gen, (uint32_t)(c.row0 + rl),
+                                      a.key_lo, a.key_hi);
+        const Words4 w = xover_words(xc, xr, a.key_lo, a.key_hi);
+        unsigned long long m[4];
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+          // bitwise & and |: the tests are lane masks, no branch
+          const bool tk = (j0 + b < a.D) &
+                          ((j0 + b == jrand) | (w.w[b] <= limit));
+          const float mv = mutant_coord(get(v1[h], b), get(v2[h], b),
+                                        get(v3[h], b), Fr, a.lo, a.hi);
+          m[b] = __ballot(tk);
+          set(y, b, (tk ? mv : get(xv[h], b)) - get(ov, b));
+        }
+        // the chunk's crossover planes: the decisions' lane masks,
+        // stored by lane 0 as two 16-byte writes
+        if (lane == 0) {
+          ulonglong2* pp = reinterpret_cast<ulonglong2*>(
+              c.planes + ((size_t)rl * c.tq + t) * 4);
+          pp[0] = make_ulonglong2(m[0], m[1]);
+          pp[1] = make_ulonglong2(m[2], m[3]);
+        }
+      }
+      if (!whole) {
+#pragma unroll
+        for (int b = 0; b < 4; ++b)
+          set(y, b, j0 + b < a.D ? get(y, b) : 0.f);
+      }
+      if (j0 < a.dpad) {
+        if constexpr (sizeof(T) == 2) {
+          bf16x4 yb;
+          yb[0] = (__bf16)y.x;
+          yb[1] = (__bf16)y.y;
+          yb[2] = (__bf16)y.z;
+          yb[3] = (__bf16)y.w;
+          *reinterpret_cast<bf16x4*>(arow + j0) = yb;
+        } else if constexpr (P::kSplit) {
+          st4(arow + j0, y);
+        } else {
+#pragma unroll
+          for (int b = 0; b < 4; ++b) arow[lds_col<P>(j0 + b)] = get(y, b);
+        }
+      }
+    }
+  }
+}
+
+// The objective of two 32x32 blocks' values (kHi: hi is there) summed over
+// the 32 columns: a reduce-scatter butterfly leaves lane l with the total of
+// value l % 32 (0-15: lo's registers, 16-31: hi's).
+template <int m>
+__device__ __forceinline__ void scatter_step(float (&v)[16], int lane) {
+  const bool upper = (lane & m) != 0;
+#pragma unroll
+  for (int k = 0; k < m; ++k) {
+    const float send = upper ? v[k] : v[k + m];
+    const float keep = upper ? v[k + m] : v[k];
+    v[k] = keep + lane_xor<m>(send);
+  }
+}
+
+template <bool kFastSin, bool kHi>
+__device__ __forceinline__ float osc_rows(const floatx16& lo,
+                                          const floatx16& hi, int lane) {
+  float v[16];
+  // first exchange: values 0-15 keep lo or hi, the other half goes over
+  const bool upper = (lane & 16) != 0;
+#pragma unroll
+  for (int k = 0; k < 16; ++k) {
+    const float a = osc_term<kFastSin>(lo[k]);
+    const float b = kHi ? osc_term<kFastSin>(hi[k]) : 0.f;
+    v[k] = (upper ? b : a) + lane_xor<16>(upper ? a : b);
+  }
+  scatter_step<8>(v, lane);
+  scatter_step<4>(v, lane);
+  scatter_step<2>(v, lane);
+  scatter_step<1>(v, lane);
+  return v[0];
+}
+
+// Row totals (slots added in order), strict selection, the next generation's
+// rows (a rejected row only if the other buffer holds a stale copy) and the
+// statistics; EVAL: the values alone.
+template <int BM, int kWaves, bool EVAL, bool JDE>
+__device__ __forceinline__ void select_rows(const GenArgs& a, const RotRows& c,
+                                            int run, const float* fpart) {
+  const int wave = (int)threadIdx.x / 64, lane = (int)threadIdx.x % 64;
+  for (int rl = wave; rl < c.nvalid; rl += kWaves) {
+    float f = 0.f;
+#pragma unroll
+    for (int sl = 0; sl < kRotSlots; ++sl) f += fpart[sl * BM + rl];
+    const int i = c.row0 + rl;
+    if (EVAL) {
+      if (lane == 0) a.fit_next[i] = f;
+      continue;
+    }
+    const size_t g = (size_t)run * a.NP + i;
+    const float fx = a.fit_cur[g];
+    const bool accept = f < fx;
+    const bool refresh = !accept && a.changed[g] != 0;
+    const float Fr = JDE ? c.ctl[rl].F : a.F;
+    if (accept || refresh) {
+      const float* xrow = c.base + (size_t)i * a.ldx;
+      float* nrow = a.pop_next + g * a.ldx;
+      const float* x1 = c.base + (size_t)c.donors[rl * 4 + 0] * a.ldx;
+      const float* x2 = c.base + (size_t)c.donors[rl * 4 + 1] * a.ldx;
+      const float* x3 = c.base + (size_t)c.donors[rl * 4 + 2] * a.ldx;
+      const int dlast = ((a.D + 3) / 4 - 1) * 4;
+      for (int t0 = 0; t0 < c.tq; t0 += 4) {
+        float4 xv[4], v1[4], v2[4], v3[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const int jl = min(4 * (lane + 64 * (t0 + u)), dlast);
+          xv[u] = ld4(xrow + jl);
+          if (accept) {
+            v1[u] = ld4(x1 + jl);
+            v2[u] = ld4(x2 + jl);
+            v3[u] = ld4(x3 + jl);
+          }
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const int t = t0 + u;
+          if (t >= c.tq) break;
+          const int j0 = 4 * (lane + 64 * t);
+          float4 out = xv[u];
+          if (accept) {
+#pragma unroll
+            for (int b = 0; b < 4; ++b) {
+              const unsigned long long m = c.planes[((size_t)rl * c.tq + t) * 4 + b];
+              const float mv = mutant_coord(get(v1[u], b), get(v2[u], b),
+                                            get(v3[u], b), Fr, a.lo, a.hi);
+              set(out, b, ((m >> lane) & 1ull) ? mv : get(xv[u], b));
+            }
+          }
+          if (j0 < a.D) st4(nrow + j0, out);
+        }
+      }
+    }
+    if (lane == 0) {
+      a.fit_next[g] = accept ? f : fx;
+      a.changed[g] = accept ? 1 : 0;
+      if constexpr (JDE) {
+        // the trial's F', CR' survive only with the trial
+        a.jp_next[g] = accept ? make_float2(c.ctl[rl].F, c.ctl[rl].CR)
+                              : a.jp_cur[g];
+      }
+      if (accept) record_accept(a, run, i, f);
+    }
+  }
+}
+
 // Widest padded row of a split tile (its LDS limit).
 constexpr int kMaxSplitDpad = 1152;
 
@@ -457,102 +675,11 @@ __device__ __forceinline__ void rot_tile(const GenArgs& a, int run, int row0,
     // holds).  Loads past the end of a row go to its last chunk and rows
     // past the wave's last go to its last row (values unused), so no load
     // sits behind a per-lane branch.
-    constexpr int RB = sizeof(T) == 2 ? kBf16Rows : 8;
-    const int nrow_w = wave < nvalid ? (nvalid - 1 - wave) / kRotWaves + 1 : 0;
-    const int dlast = ((a.D + 3) / 4 - 1) * 4;
-    for (int t = 0; t < tq; ++t) {
-      const int q = lane + 64 * t, j0 = 4 * q, jl = min(j0, dlast);
-      const float4 ov = ld4(a.o + jl);
-      // a chunk with the row's end: its coordinates past D are zeroed
-      const bool whole = 256 * (t + 1) <= a.D;
-      XoverCol xc{0, 0, 0, 0};
-      if (!EVAL)
-        xc = xover_col(rng_run, a.gen, (uint32_t)q, a.key_lo, a.key_hi);
-      for (int k = 0; k < nrow_w; k += RB) {
-        float4 xv[RB], v1[RB], v2[RB], v3[RB];
-#pragma unroll
-        for (int h = 0; h < RB; ++h) {
-          // row and donor indices are wave-uniform: scalar row pointers
-          const int rl = __builtin_amdgcn_readfirstlane(
-              wave + kRotWaves * min(k + h, nrow_w - 1));
-          xv[h] = ld4(base + (size_t)(row0 + rl) * a.ldx + jl);
-          if (!EVAL) {
-            v1[h] = ld4(base + (size_t)__builtin_amdgcn_readfirstlane(
-                                   donors[rl * 4 + 0]) * a.ldx + jl);
-            v2[h] = ld4(base + (size_t)__builtin_amdgcn_readfirstlane(
-                                   donors[rl * 4 + 1]) * a.ldx + jl);
-            v3[h] = ld4(base + (size_t)__builtin_amdgcn_readfirstlane(
-                                   donors[rl * 4 + 2]) * a.ldx + jl);
-          }
-        }
-        // every gather of the step is issued before any of it is used:
-        // keeps the compiler from sinking a row's loads into the guarded
-        // code that consumes them
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int h = 0; h < RB; ++h) {
-          if (k + h >= nrow_w) break;
-          const int rl =
-              __builtin_amdgcn_readfirstlane(wave + kRotWaves * (k + h));
-          T* arow = At + (size_t)rl * stride;
-          float4 y;
-          if constexpr (EVAL) {
-#pragma unroll
-            for (int b = 0; b < 4; ++b) set(y, b, get(xv[h], b) - get(ov, b));
-          } else {
-            const int jrand = donors[rl * 4 + 3];
-            float Fr = a.F;
-            uint32_t limit = xover_word_limit(a.cr_threshold);
-            if constexpr (JDE) {
-              Fr = ctl[rl].F;
-              limit = xover_word_limit(cr_threshold_of(ctl[rl].CR));
-            }
-            const XoverRow xr = xover_row(a.gen, (uint32_t)(row0 + rl),
-                                          a.key_lo, a.key_hi);
-            const Words4 w = xover_words(xc, xr, a.key_lo, a.key_hi);
-            unsigned long long m[4];
-#pragma unroll
-            for (int b = 0; b < 4; ++b) {
-              // bitwise & and |: the tests are lane masks, no branch
-              const bool tk = (j0 + b < a.D) &
-                              ((j0 + b == jrand) | (w.w[b] <= limit));
-              const float mv = mutant_coord(get(v1[h], b), get(v2[h], b),
-                                            get(v3[h], b), Fr, a.lo, a.hi);
-              m[b] = __ballot(tk);
-              set(y, b, (tk ? mv : get(xv[h], b)) - get(ov, b));
-            }
-            // the chunk's crossover planes: the decisions' lane masks,
-            // stored by lane 0 as two 16-byte writes
-            if (lane == 0) {
-              ulonglong2* pp = reinterpret_cast<ulonglong2*>(
-                  planes + ((size_t)rl * tq + t) * 4);
-              pp[0] = make_ulonglong2(m[0], m[1]);
-              pp[1] = make_ulonglong2(m[2], m[3]);
-            }
-          }
-          if (!whole) {
-#pragma unroll
-            for (int b = 0; b < 4; ++b)
-              set(y, b, j0 + b < a.D ? get(y, b) : 0.f);
-          }
-          if (j0 < dpad) {
-            if constexpr (sizeof(T) == 2) {
-              bf16x4 yb;
-              yb[0] = (__bf16)y.x;
-              yb[1] = (__bf16)y.y;
-              yb[2] = (__bf16)y.z;
-              yb[3] = (__bf16)y.w;
-              *reinterpret_cast<bf16x4*>(arow + j0) = yb;
-            } else if constexpr (P::kSplit) {
-              st4(arow + j0, y);
-            } else {
-#pragma unroll
-              for (int b = 0; b < 4; ++b) arow[lds_col<P>(j0 + b)] = get(y, b);
-            }
-          }
-        }
-      }
-    }
+    const RotRows c{base, donors, ctl, planes, rng_run, row0, nvalid, stride,
+                    tq};
+    for (int t = 0; t < tq; ++t)
+      build_chunk<P, sizeof(T) == 2 ? kBf16Rows : 8, kRotWaves, EVAL, JDE>(
+          a, c, t, At);
   }
   if constexpr (P::kSplit && PAIR) {
     // rows past the tile's last are zero already (as halves too)
@@ -776,37 +903,14 @@ __device__ __forceinline__ void rot_tile(const GenArgs& a, int run, int row0,
     // over the 32 lanes of each half-wave leaves lane l with the total of
     // value l % 32 (31 exchanges instead of 5 per value).
     constexpr bool kFastSin = sizeof(T) == 2;
-    floatx16& lo = c00;
-    floatx16& hi = MB == 2 ? c10 : c01;
+    const floatx16& lo = c00;
+    const floatx16& hi = MB == 2 ? c10 : c01;
     // FP32 one-block tiles: values 16-31 (a second block) are empty
     constexpr bool kHi = MB == 2 || NBW == 2;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      lo[r] = osc_term<kFastSin>(lo[r]);
-      hi[r] = kHi ? osc_term<kFastSin>(hi[r]) : 0.f;
-    }
-    {  // first exchange: values 0-15 keep lo or hi, the other half goes over
-      const bool upper = (lane & 16) != 0;
-#pragma unroll
-      for (int k = 0; k < 16; ++k) {
-        const float send = upper ? lo[k] : hi[k];
-        const float keep = upper ? hi[k] : lo[k];
-        lo[k] = keep + __shfl_xor(send, 16, 64);
-      }
-    }
-#pragma unroll
-    for (int m = 8, n = 16; m >= 1; m >>= 1, n >>= 1) {
-      const bool upper = (lane & m) != 0;
-#pragma unroll
-      for (int k = 0; k < n / 2; ++k) {
-        const float send = upper ? lo[k] : lo[k + n / 2];
-        const float keep = upper ? lo[k + n / 2] : lo[k];
-        lo[k] = keep + __shfl_xor(send, m, 64);
-      }
-    }
+    const float total = osc_rows<kFastSin, kHi>(lo, hi, lane);
 #pragma unroll
     for (int q = 0; q < SPW; ++q)
-      if (pass % SPW == q) sacc[q] += lo[0];
+      if (pass % SPW == q) sacc[q] += total;
   }
   // lane l holds value l % 32: BF16 row (l % 32 / 16) * 32 + rin of the
   // wave's blocks; FP32 row rin of block nb0 + (l % 32) / 16 (one-block
@@ -867,69 +971,8 @@ __device__ __forceinline__ void rot_tile(const GenArgs& a, int run, int row0,
     }
     return;
   }
-  for (int rl = wave; rl < nvalid; rl += kRotWaves) {
-    float f = 0.f;
-#pragma unroll
-    for (int sl = 0; sl < kRotSlots; ++sl) f += fpart[sl * BM + rl];
-    const int i = row0 + rl;
-    if (EVAL) {
-      if (lane == 0) a.fit_next[i] = f;
-      continue;
-    }
-    const size_t g = (size_t)run * a.NP + i;
-    const float fx = a.fit_cur[g];
-    const bool accept = f < fx;
-    const bool refresh = !accept && a.changed[g] != 0;
-    const float Fr = JDE ? ctl[rl].F : a.F;
-    if (accept || refresh) {
-      const float* xrow = base + (size_t)i * a.ldx;
-      float* nrow = a.pop_next + g * a.ldx;
-      const float* x1 = base + (size_t)donors[rl * 4 + 0] * a.ldx;
-      const float* x2 = base + (size_t)donors[rl * 4 + 1] * a.ldx;
-      const float* x3 = base + (size_t)donors[rl * 4 + 2] * a.ldx;
-      const int dlast = ((a.D + 3) / 4 - 1) * 4;
-      for (int t0 = 0; t0 < tq; t0 += 4) {
-        float4 xv[4], v1[4], v2[4], v3[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const int jl = min(4 * (lane + 64 * (t0 + u)), dlast);
-          xv[u] = ld4(xrow + jl);
-          if (accept) {
-            v1[u] = ld4(x1 + jl);
-            v2[u] = ld4(x2 + jl);
-            v3[u] = ld4(x3 + jl);
-          }
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const int t = t0 + u;
-          if (t >= tq) break;
-          const int j0 = 4 * (lane + 64 * t);
-          float4 out = xv[u];
-          if (accept) {
-#pragma unroll
-            for (int b = 0; b < 4; ++b) {
-              const unsigned long long m = planes[((size_t)rl * tq + t) * 4 + b];
-              const float mv = mutant_coord(get(v1[u], b), get(v2[u], b),
-                                            get(v3[u], b), Fr, a.lo, a.hi);
-              set(out, b, ((m >> lane) & 1ull) ? mv : get(xv[u], b));
-            }
-          }
-          if (j0 < a.D) st4(nrow + j0, out);
-        }
-      }
-    }
-    if (lane == 0) {
-      a.fit_next[g] = accept ? f : fx;
-      a.changed[g] = accept ? 1 : 0;
-      if constexpr (JDE) {
-        // the trial's F', CR' survive only with the trial
-        a.jp_next[g] = accept ? make_float2(ctl[rl].F, ctl[rl].CR)
-                              : a.jp_cur[g];
-      }
-      if (accept) record_accept(a, run, i, f);
-    }
-  }
+  const RotRows c{base, donors, ctl, planes, rng_run, row0, nvalid, stride, tq};
+  select_rows<BM, kRotWaves, EVAL, JDE>(a, c, run, fpart);
 }
 
 }  // namespace de

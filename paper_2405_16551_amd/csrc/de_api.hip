@@ -219,6 +219,8 @@ GenArgs base_args(const de_state* s) {
   a.D = s->p.D;
   a.ldx = s->ldx;
   a.dpad = s->dpad;
+  a.tall = s->kind == de::kObjRotOsc &&
+           de::rot_tall(s->prec, s->dpad, s->p.runs, s->p.NP);
   a.nrows = s->p.runs * s->p.NP;
   a.F = s->p.F;
   a.lo = s->p.lo;

@@ -989,7 +989,7 @@ __device__ __forceinline__ void rot_tile(const GenArgs& a, int run, int row0,
 // (then the accumulators would have to grow); where a later part needs a
 // smaller scale they are scaled down by the same power of two.
 // One workgroup of 8 waves (256 registers) per CU, so it pays from more than
-// one 32-row tile per CU on: 16 x 1024 x 1000 TALL_US us per generation
+// one 32-row tile per CU on: 16 x 1024 x 1000 124 us per generation
 // against 141.
 constexpr int kTallPart = 512;
 constexpr int kTallMinDpad = 640, kTallMaxDpad = 1024;

@@ -419,75 +419,138 @@ __device__ __forceinline__ float osc_rows(const floatx16& lo,
   return v[0];
 }
 
-// Row totals (slots added in order), strict selection, the next generation's
-// rows (a rejected row only if the other buffer holds a stale copy) and the
-// statistics; EVAL: the values alone.
-template <int BM, int kWaves, bool EVAL, bool JDE>
-__device__ __forceinline__ void select_rows(const GenArgs& a, const RotRows& c,
-                                            int run, const float* fpart) {
+// The wave's rows in the selection: lane r < count has row wave + kWaves r,
+// with its target's value and stale flag, read before the product so that
+// the selection does not wait for them.
+struct SelectRow {
+  int rl;
+  bool in;
+  float fx;
+  bool stale;
+};
+
+template <int kWaves, bool EVAL>
+__device__ __forceinline__ SelectRow select_row(const GenArgs& a, int run,
+                                                int row0, int nvalid) {
   const int wave = (int)threadIdx.x / 64, lane = (int)threadIdx.x % 64;
-  for (int rl = wave; rl < c.nvalid; rl += kWaves) {
-    float f = 0.f;
+  SelectRow s;
+  s.rl = wave + kWaves * lane;
+  s.in = s.rl < nvalid;
+  s.rl = s.in ? s.rl : wave;
+  s.fx = 0.f;
+  s.stale = false;
+  if (!EVAL && s.in) {
+    const size_t g = (size_t)run * a.NP + row0 + s.rl;
+    s.fx = a.fit_cur[g];
+    s.stale = a.changed[g] != 0;
+  }
+  return s;
+}
+
+// Writes the rows of `need` (bit r: row wave + kWaves r) into the next
+// generation: trials (rebuilt from the crossover masks and the donors) where
+// bit r of `accept` is set, else the target.  R rows at a time, so that the
+// rows' reads share one round trip (four 256-coordinate pieces in flight).
+template <int R, int kWaves, bool JDE>
+__device__ __forceinline__ void write_rows(const GenArgs& a, const RotRows& c,
+                                           int run, uint32_t need,
+                                           uint32_t accept) {
+  constexpr int C = 4 / R;  // chunks of a row in flight
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / 64);
+  const int lane = (int)threadIdx.x % 64;
+  const int dlast = ((a.D + 3) / 4 - 1) * 4;
+  while (need) {
+    int rl[R];
+    const float *x0[R], *x1[R], *x2[R], *x3[R];  // scalar row pointers
+    bool on[R], acc[R];
 #pragma unroll
-    for (int sl = 0; sl < kRotSlots; ++sl) f += fpart[sl * BM + rl];
-    const int i = c.row0 + rl;
-    if (EVAL) {
-      if (lane == 0) a.fit_next[i] = f;
-      continue;
+    for (int h = 0; h < R; ++h) {
+      on[h] = need != 0;
+      const int r = on[h] ? __builtin_ctz(need) : 0;
+      acc[h] = on[h] && ((accept >> r) & 1u);
+      rl[h] = wave + kWaves * r;
+      need &= need - 1;
+      const int* d = c.donors + rl[h] * 4;
+      x0[h] = c.base + (size_t)(c.row0 + rl[h]) * a.ldx;
+      x1[h] = c.base + (size_t)__builtin_amdgcn_readfirstlane(d[0]) * a.ldx;
+      x2[h] = c.base + (size_t)__builtin_amdgcn_readfirstlane(d[1]) * a.ldx;
+      x3[h] = c.base + (size_t)__builtin_amdgcn_readfirstlane(d[2]) * a.ldx;
     }
-    const size_t g = (size_t)run * a.NP + i;
-    const float fx = a.fit_cur[g];
-    const bool accept = f < fx;
-    const bool refresh = !accept && a.changed[g] != 0;
-    const float Fr = JDE ? c.ctl[rl].F : a.F;
-    if (accept || refresh) {
-      const float* xrow = c.base + (size_t)i * a.ldx;
-      float* nrow = a.pop_next + g * a.ldx;
-      const float* x1 = c.base + (size_t)c.donors[rl * 4 + 0] * a.ldx;
-      const float* x2 = c.base + (size_t)c.donors[rl * 4 + 1] * a.ldx;
-      const float* x3 = c.base + (size_t)c.donors[rl * 4 + 2] * a.ldx;
-      const int dlast = ((a.D + 3) / 4 - 1) * 4;
-      for (int t0 = 0; t0 < c.tq; t0 += 4) {
-        float4 xv[4], v1[4], v2[4], v3[4];
+    for (int t0 = 0; t0 < c.tq; t0 += C) {
+      float4 xv[4], v1[4], v2[4], v3[4];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const int jl = min(4 * (lane + 64 * (t0 + u)), dlast);
-          xv[u] = ld4(xrow + jl);
-          if (accept) {
-            v1[u] = ld4(x1 + jl);
-            v2[u] = ld4(x2 + jl);
-            v3[u] = ld4(x3 + jl);
-          }
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const int t = t0 + u;
-          if (t >= c.tq) break;
-          const int j0 = 4 * (lane + 64 * t);
-          float4 out = xv[u];
-          if (accept) {
-#pragma unroll
-            for (int b = 0; b < 4; ++b) {
-              const unsigned long long m = c.planes[((size_t)rl * c.tq + t) * 4 + b];
-              const float mv = mutant_coord(get(v1[u], b), get(v2[u], b),
-                                            get(v3[u], b), Fr, a.lo, a.hi);
-              set(out, b, ((m >> lane) & 1ull) ? mv : get(xv[u], b));
-            }
-          }
-          if (j0 < a.D) st4(nrow + j0, out);
+      for (int s = 0; s < 4; ++s) {
+        const int h = s / C, t = t0 + s % C;
+        // (past the row's end its last piece, past the last row row 0)
+        const int jl = min(4 * (lane + 64 * t), dlast);
+        if (on[h]) xv[s] = ld4(x0[h] + jl);
+        if (acc[h]) {
+          v1[s] = ld4(x1[h] + jl);
+          v2[s] = ld4(x2[h] + jl);
+          v3[s] = ld4(x3[h] + jl);
         }
       }
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        const int h = s / C, t = t0 + s % C;
+        const int j0 = 4 * (lane + 64 * t);
+        if (!on[h] || t >= c.tq) continue;
+        float4 out = xv[s];
+        if (acc[h]) {
+          const float Fr = JDE ? c.ctl[rl[h]].F : a.F;
+#pragma unroll
+          for (int b = 0; b < 4; ++b) {
+            const unsigned long long m =
+                c.planes[((size_t)rl[h] * c.tq + t) * 4 + b];
+            const float mv = mutant_coord(get(v1[s], b), get(v2[s], b),
+                                          get(v3[s], b), Fr, a.lo, a.hi);
+            set(out, b, ((m >> lane) & 1ull) ? mv : get(xv[s], b));
+          }
+        }
+        if (j0 < a.D)
+          st4(a.pop_next +
+                  ((size_t)run * a.NP + c.row0 + rl[h]) * a.ldx + j0,
+              out);
+      }
     }
-    if (lane == 0) {
-      a.fit_next[g] = accept ? f : fx;
+  }
+}
+
+// Row totals (slots added in order), strict selection, the next generation's
+// rows (a rejected row only if the other buffer holds a stale copy) and the
+// statistics; EVAL: the values alone.  All of the wave's rows are decided at
+// once, one per lane.
+template <int BM, int kWaves, bool EVAL, bool JDE>
+__device__ __forceinline__ void select_rows(const GenArgs& a, const RotRows& c,
+                                            int run, const float* fpart,
+                                            const SelectRow& s) {
+  float f = 0.f;
+#pragma unroll
+  for (int sl = 0; sl < kRotSlots; ++sl) f += fpart[sl * BM + s.rl];
+  const int i = c.row0 + s.rl;
+  if constexpr (EVAL) {
+    if (s.in) a.fit_next[i] = f;
+  } else {
+    const bool accept = s.in && f < s.fx;
+    if (s.in) {
+      const size_t g = (size_t)run * a.NP + i;
+      a.fit_next[g] = accept ? f : s.fx;
       a.changed[g] = accept ? 1 : 0;
       if constexpr (JDE) {
         // the trial's F', CR' survive only with the trial
-        a.jp_next[g] = accept ? make_float2(c.ctl[rl].F, c.ctl[rl].CR)
+        a.jp_next[g] = accept ? make_float2(c.ctl[s.rl].F, c.ctl[s.rl].CR)
                               : a.jp_cur[g];
       }
-      if (accept) record_accept(a, run, i, f);
     }
+    const uint32_t acc = (uint32_t)__ballot(accept);
+    const uint32_t need = acc | (uint32_t)__ballot(s.in && s.stale);
+    if (c.tq == 1)
+      write_rows<4, kWaves, JDE>(a, c, run, need, acc);
+    else if (c.tq == 2)
+      write_rows<2, kWaves, JDE>(a, c, run, need, acc);
+    else
+      write_rows<1, kWaves, JDE>(a, c, run, need, acc);
+    if (accept) record_accept(a, run, i, f);
   }
 }
 
@@ -726,6 +789,10 @@ __device__ __forceinline__ void rot_tile(const GenArgs& a, int run, int row0,
     }
   }
   __syncthreads();
+
+  SelectRow sr{0, false, 0.f, false};
+  if constexpr (!PAIR)
+    sr = select_row<kRotWaves, EVAL>(a, run, row0, nvalid);
 
   // ---- phase 2: Z = Y R^T with the objective fused into the epilogue
   // Accumulators c{m}{n}: 32x32 block (row block m, column block nb0 + n),
@@ -972,7 +1039,7 @@ __device__ __forceinline__ void rot_tile(const GenArgs& a, int run, int row0,
     return;
   }
   const RotRows c{base, donors, ctl, planes, rng_run, row0, nvalid, stride, tq};
-  select_rows<BM, kRotWaves, EVAL, JDE>(a, c, run, fpart);
+  select_rows<BM, kRotWaves, EVAL, JDE>(a, c, run, fpart, sr);
 }
 
 // ---------------------------------------------------------------------------
@@ -1050,6 +1117,7 @@ __device__ __forceinline__ void rot_tile_tall(const GenArgs& a, int run,
   }
   if (threadIdx.x < BM) rexp[threadIdx.x] = 127;
   __syncthreads();
+  const SelectRow sr = select_row<kWaves, EVAL>(a, run, row0, nvalid);
   const int nblk = dpad / 32, kbn = dpad / 16;
   floatx16 acc[NB][2];
 #pragma unroll
@@ -1220,7 +1288,7 @@ __device__ __forceinline__ void rot_tile_tall(const GenArgs& a, int run,
     fpart[(size_t)(wave + 8) * BM + hb * 32 + rin] = sacc[1];
   }
   __syncthreads();
-  select_rows<BM, kWaves, EVAL, JDE>(a, c, run, fpart);
+  select_rows<BM, kWaves, EVAL, JDE>(a, c, run, fpart, sr);
 }
 
 }  // namespace de

@@ -95,6 +95,19 @@ __host__ __device__ constexpr size_t bt_lds_bytes(int dpad) {
          + (size_t)BM * (dpad / 4);         // crossover bits, 4 per byte
 }
 
+// Reduce-scatter step over lanes l, l ^ m: 16 lanes' worth of m values to
+// m / 2.
+template <int m>
+__device__ __forceinline__ void rows16_step(float (&v)[16], int lane) {
+  const bool upper = (lane & m) != 0;
+#pragma unroll
+  for (int k = 0; k < m / 2; ++k) {
+    const float send = upper ? v[k] : v[k + m / 2];
+    const float keep = upper ? v[k + m / 2] : v[k];
+    v[k] = keep + lane_xor<m>(send);
+  }
+}
+
 // ---------------------------------------------------------------------------
 // Generic tile kernel.
 //   phase 1: items (row, 4-coordinate group) over all threads, two per step
@@ -158,13 +171,16 @@ void k_bt_rot(BatchArgs b) {
     // and the row's last 4-group, so the loads carry no per-lane branch.
     const int dlast = ((rn.D + 3) / 4 - 1) * 4;
     const int items = BM * nq4;
+    // it / nq4 by one product: (it + 1/2) / nq4 is at least 1 / (2 nq4) away
+    // from an integer, far more than its rounding for it < 2^16
+    const float inv_nq4 = 1.0f / (float)nq4;
     for (int it0 = tid; it0 < items; it0 += 2 * NT) {
       int rl[2], q[2];
       float4 xv[2], ov[2], v1[2], v2[2], v3[2];
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
         const int it = min(it0 + h * NT, items - 1);
-        rl[h] = it / nq4;
+        rl[h] = (int)(((float)it + 0.5f) * inv_nq4);
         q[h] = it - rl[h] * nq4;
         const int r = min(rl[h], nvalid - 1);
         const int jl = min(4 * q[h], dlast);
@@ -246,17 +262,11 @@ void k_bt_rot(BatchArgs b) {
       float v[16];
 #pragma unroll
       for (int r = 0; r < 16; ++r) v[r] = part[r];
-#pragma unroll
-      for (int m = 16; m >= 2; m >>= 1) {
-        const bool upper = (lane & m) != 0;
-#pragma unroll
-        for (int k = 0; k < m / 2; ++k) {
-          const float send = upper ? v[k] : v[k + m / 2];
-          const float keep = upper ? v[k + m / 2] : v[k];
-          v[k] = keep + __shfl_xor(send, m, 64);
-        }
-      }
-      v[0] += __shfl_xor(v[0], 1, 64);
+      rows16_step<16>(v, lane);
+      rows16_step<8>(v, lane);
+      rows16_step<4>(v, lane);
+      rows16_step<2>(v, lane);
+      v[0] += lane_xor<1>(v[0]);
       if ((lane & 1) == 0) {
         const int r = (lane % 32) >> 1;
         const int row = mb * 32 + 8 * (r / 4) + 4 * (lane / 32) + (r % 4);
@@ -295,8 +305,9 @@ void k_bt_rot(BatchArgs b) {
     if (!EVAL) {
       __syncthreads();
       const int nqd = (rn.D + 3) / 4;
+      const float inv_nqd = 1.0f / (float)nqd;  // as inv_nq4
       for (int it = tid; it < nvalid * nqd; it += NT) {
-        const int rl = it / nqd, q = it - rl * nqd;
+        const int rl = (int)(((float)it + 0.5f) * inv_nqd), q = it - rl * nqd;
         const int action = act[rl];
         if (action == 0) continue;
         const int i = tile.row0 + rl, j0 = 4 * q;

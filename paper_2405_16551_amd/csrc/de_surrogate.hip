@@ -367,49 +367,91 @@ void k_comp_eval(SurArgs a, const float* X, int n, int ldx, float* f) {
 }
 
 // ---------------------------------------------------------------------------
-// Candidates: one wave per candidate row (i, c), or one half-wave when a
-// row has at most 32 4-groups; lanes over 4-groups.
-__host__ __device__ constexpr int cand_rows_per_wave(int D) {
-  return (D + 3) / 4 <= 32 ? 2 : 1;
-}
+// Candidates (i, c): a wave takes kCandRows rows, LPR lanes a row (32 for rows
+// of at most 32 4-groups, so that two rows share an instruction), lanes over
+// 4-groups, two rows of a lane group requested at a time.
+// Bound: vector issue.  The donors and what the crossover words owe to the
+// row alone are drawn once per row, eight rows in eight lanes, and handed
+// through LDS; what they owe to the 4-group stays in registers over the rows.
+// A wave that drew both for its own pair of rows issued about three times the
+// instructions: 17.5 us for 30 x 2048 rows of D = 100 (24.6 MB stored, 4.7 us
+// at the copy rate), 11.6 us so; 16 rows a wave: 11.1, but half the waves
+// where rows are few; four rows requested at a time: 11.9.
+constexpr int kCandRows = 8;
 
+struct alignas(16) CandRow {
+  size_t x, x1, x2, x3, out;  // first elements of the rows
+  XoverRow xr;
+  int jrand;
+};
+
+template <int LPR>
 __global__ __launch_bounds__(256) void k_sur_cand(SurArgs a) {
+  constexpr int kGroups = 64 / LPR, kSteps = kCandRows / kGroups;
+  constexpr int kStep = 2;  // rows of a lane group in flight
+  __shared__ CandRow rows[4 * kCandRows];
   const RunUnit wu = run_unit();
-  const int run = wu.run;
-  const int wave = (int)threadIdx.x / 64;
-  const int rpw = cand_rows_per_wave(a.D), lpr = 64 / rpw;
-  const int lane = (int)threadIdx.x % lpr;
-  const int cr = (wu.x * 4 + wave) * rpw + ((int)threadIdx.x % 64) / lpr;
-  if (cr >= a.NP * a.k) return;  // whole row groups leave together
-  const int i = cr / a.k, c = cr - i * a.k;
-  const uint32_t ctr_i = (uint32_t)i | ((uint32_t)c << 24);
-  const Donors d = pick_donors_ctr((uint32_t)run, a.gen, ctr_i, i, a.NP, a.D,
-                                   a.key_lo, a.key_hi);
-  const float* base = a.pop_cur + (size_t)run * a.NP * a.ldx;
-  const float* x = base + (size_t)i * a.ldx;
-  const float* x1 = base + (size_t)d.r1 * a.ldx;
-  const float* x2 = base + (size_t)d.r2 * a.ldx;
-  const float* x3 = base + (size_t)d.r3 * a.ldx;
-  float* out = a.cand + ((size_t)run * a.NP * a.k + cr) * a.ldx;
-  // predictions read 0 for a generation the model does not screen
-  if (!a.use_model && lane == 0) a.pred[(size_t)run * a.NP * a.k + cr] = 0.f;
+  const int run = wu.run, nrows = a.NP * a.k;
+  const int wave = (int)threadIdx.x / 64, wl = (int)threadIdx.x % 64;
+  const int lane = wl % LPR, grp = wl / LPR;
+  const int cr0 = (wu.x * 4 + wave) * kCandRows;
+  if (cr0 >= nrows) return;  // whole waves leave; no barrier below
+  CandRow* mine = rows + wave * kCandRows;
+  if (wl < kCandRows) {
+    const int cr = min(cr0 + wl, nrows - 1);
+    const int i = cr / a.k, c = cr - i * a.k;
+    const uint32_t ctr_i = (uint32_t)i | ((uint32_t)c << 24);
+    const Donors d = pick_donors_ctr((uint32_t)run, a.gen, ctr_i, i, a.NP, a.D,
+                                     a.key_lo, a.key_hi);
+    const size_t row0 = (size_t)run * a.NP, ldx = a.ldx;
+    mine[wl] = {(row0 + i) * ldx,
+                (row0 + d.r1) * ldx,
+                (row0 + d.r2) * ldx,
+                (row0 + d.r3) * ldx,
+                ((size_t)run * nrows + cr) * ldx,
+                xover_row(a.gen, ctr_i, a.key_lo, a.key_hi),
+                d.jrand};
+    // predictions read 0 for a generation the model does not screen
+    if (!a.use_model && cr0 + wl < nrows)
+      a.pred[(size_t)run * nrows + cr0 + wl] = 0.f;
+  }
+  // the wave's own LDS words: written before they are read by its lanes
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
   const int nq = (a.D + 3) / 4;
-  for (int q = lane; q < nq; q += lpr) {
+  for (int q = lane; q < nq; q += LPR) {
     const int j0 = 4 * q;
-    const float4 xv = ld4(x + j0), v1 = ld4(x1 + j0), v2 = ld4(x2 + j0),
-                 v3 = ld4(x3 + j0);
-    const Words4 w = draw_block(kTagXover, (uint32_t)run, a.gen, ctr_i,
-                                (uint32_t)q, a.key_lo, a.key_hi);
-    float4 u = xv;
+    const XoverCol col =
+        xover_col((uint32_t)run, a.gen, (uint32_t)q, a.key_lo, a.key_hi);
 #pragma unroll
-    for (int b = 0; b < 4; ++b) {
-      const bool tk = (j0 + b < a.D) &&
-                      take_mutant(w.w[b], j0 + b, d.jrand, a.cr_threshold);
-      const float mv = mutant_coord(get(v1, b), get(v2, b), get(v3, b), a.F,
-                                    a.lo, a.hi);
-      set(u, b, tk ? mv : get(xv, b));
+    for (int s0 = 0; s0 < kSteps; s0 += kStep) {
+      float4 xv[kStep], v1[kStep], v2[kStep], v3[kStep];
+#pragma unroll
+      for (int t = 0; t < kStep; ++t) {
+        const CandRow& d = mine[(s0 + t) * kGroups + grp];
+        xv[t] = ld4(a.pop_cur + d.x + j0);
+        v1[t] = ld4(a.pop_cur + d.x1 + j0);
+        v2[t] = ld4(a.pop_cur + d.x2 + j0);
+        v3[t] = ld4(a.pop_cur + d.x3 + j0);
+      }
+      __builtin_amdgcn_sched_barrier(0);  // all requested before any draw
+#pragma unroll
+      for (int t = 0; t < kStep; ++t) {
+        const CandRow& d = mine[(s0 + t) * kGroups + grp];
+        const Words4 w = xover_words(col, d.xr, a.key_lo, a.key_hi);
+        float4 u = xv[t];
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+          const bool tk = (j0 + b < a.D) & take_mutant(w.w[b], j0 + b, d.jrand,
+                                                       a.cr_threshold);
+          const float mv = mutant_coord(get(v1[t], b), get(v2[t], b),
+                                        get(v3[t], b), a.F, a.lo, a.hi);
+          set(u, b, tk ? mv : get(xv[t], b));
+        }
+        // rows past the last one repeat it: the same values at its place
+        st4(a.cand + d.out + j0, u);
+      }
     }
-    st4(out + j0, u);
   }
 }
 
@@ -1770,10 +1812,12 @@ de_status one_generation(de_sur* s, hipStream_t st) {
   SurArgs a = args_of(s);
   a.use_model = (s->sp.k > 1 && s->gen >= s->sp.warmup_gens) ? 1 : 0;
   s->last_use_model = a.use_model;
-  const int per_wg = 4 * de::cand_rows_per_wave(a.D);
-  hipLaunchKernelGGL(de::k_sur_cand,
-                     dim3((a.NP * a.k + per_wg - 1) / per_wg, a.runs),
-                     dim3(256), 0, st, a);
+  constexpr int per_wg = 4 * de::kCandRows;
+  const dim3 cand_grid((a.NP * a.k + per_wg - 1) / per_wg, a.runs);
+  if ((a.D + 3) / 4 <= 32)
+    hipLaunchKernelGGL((de::k_sur_cand<32>), cand_grid, dim3(256), 0, st, a);
+  else
+    hipLaunchKernelGGL((de::k_sur_cand<64>), cand_grid, dim3(256), 0, st, a);
   de_status rc = FROM_HIP(hipGetLastError());
   if (rc != DE_OK) return rc;
   if (a.use_model) {

@@ -243,3 +243,29 @@ def test_inference_edges(D, H, n):
                                    (97, 128, 96), (128, 256, 160)])
 def test_training_edges(D, H, B):
     sur.test_adam_step_matches_oracle(D, H, B)
+
+
+# candidates: two rows or one row per wave instruction (up to 32 4-groups, or
+# more), rows of one to three passes, last waves with rows left over
+@pytest.mark.parametrize("NP,D,k", [(5, 1, 1), (9, 127, 3), (11, 128, 4),
+                                    (7, 129, 1), (13, 257, 2), (6, 600, 3)])
+def test_candidate_edges(NP, D, k):
+    s, comp = sur.make_sur(runs=2, NP=NP, D=D, n=1, hidden=32, k=k, F=0.6,
+                           CR=0.8, seed=3, warmup_gens=100, steps=0, batch=32,
+                           archive=64)
+    s.generation(1)
+    g = s.gen
+    pop32, fit32 = host(s.population()).copy(), host(s.fitness()).copy()
+    theta, _, _, _ = s.get_model()
+    s.generation(1)
+    cand, pred, choice = s.last()
+    O, R, bias, sigma = comp
+    out = oracle.sur_generation(pop32, fit32, theta, k=k, F=0.6, CR=0.8, lo=LO,
+                                hi=HI, seed=3, gen=g, use_model=False, H=32,
+                                O=O, R=R, bias=bias, sigma=sigma, nthreads=8)
+    assert (pred == 0).all() and (choice == 0).all()
+    # one rounding of the difference and one of the fused result, every
+    # operand within the box
+    tol = 2.0 ** -22 * HI * (1 + 2 * 0.6)
+    assert (np.abs(cand - out["cand"]) <= tol).all()
+    s.close()

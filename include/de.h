@@ -161,9 +161,9 @@ DE_API de_status de_init_population(const de_params* params,
  * generations: every donor comes from generation g.  Asynchronous.
  * Calls of at least 32 generations on rotated problems with the BF16
  * product, more than 896 coordinates, two or more runs and at least one
- * 64-row tile per compute unit run as two run groups on two streams that such handles create at initialisation (ordered after,
- * and waited for by, hip_stream through events; released by de_destroy),
- * the second group offset by half the time per generation measured on an
+ * 64-row tile per compute unit run as two run groups on two streams that
+ * such handles create at initialisation (ordered after, and waited for by,
+ * hip_stream through events; released by de_destroy), the second group offset by half the time per generation measured on an
  * earlier call, so that one group's trial build overlaps the other's
  * rotation product.  The results are identical to one launch per
  * generation; the environment variable DE_STAGGER=0 turns the split off,
@@ -173,8 +173,8 @@ DE_API de_status de_generation(de_state* state, int32_t n_gens, void* hip_stream
 /* Run until every run's best value is <= target or max_gens further
  * generations have run (Section 7.3.4: budget or error threshold).  The
  * generations are queued in chunks of check_every (>= 1); behind each
- * chunk the device's count of runs at the target is copied to pinned host
- * memory (the solution-found flag of Section 8, copied asynchronously), and
+ * chunk a kernel writes the count of runs at the target to pinned host
+ * memory (the solution-found flag of Section 8, posted asynchronously), and
  * the next chunk is queued before the host reads the previous chunk's
  * count, so the device does not wait on the host between chunks.  The call
  * therefore stops at most one chunk after the chunk in which the last run
@@ -184,9 +184,9 @@ DE_API de_status de_generation(de_state* state, int32_t n_gens, void* hip_stream
  * first-hit generation is recorded on the device and is exact whatever
  * check_every is.  *gens_done receives the number of generations run by
  * this call; hit_gen (nullable, runs entries) receives per run the first
- * generation at which the best was <= target, or -1.  The handle keeps two
- * pinned host words and two events for the polling from its first
- * de_evolve call until de_destroy.  Synchronises hip_stream.               */
+ * generation at which the best was <= target, or -1.  The handle keeps a
+ * small block of pinned host memory and two events for the polling from its
+ * first de_evolve call until de_destroy.  Synchronises hip_stream.         */
 DE_API de_status de_evolve(de_state* state, int64_t max_gens, double target,
                     int32_t check_every, void* hip_stream, int64_t* gens_done,
                     int64_t* hit_gen);

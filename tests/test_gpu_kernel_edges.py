@@ -269,3 +269,24 @@ def test_candidate_edges(NP, D, k):
     tol = 2.0 ** -22 * HI * (1 + 2 * 0.6)
     assert (np.abs(cand - out["cand"]) <= tol).all()
     s.close()
+
+
+# run groups: calls of 32 generations and more on BF16 rows of more than 896
+# coordinates, the second call with a measured offset; 17 runs: groups of 8
+# and 9; a shorter call between them goes unsplit
+@pytest.mark.parametrize("jde", [None, True])
+def test_long_calls_equal_single_steps(jde):
+    kw = dict(runs=17, NP=1000, D=900, seed=3, kind="rot_osc",
+              gemm_prec="bf16", jde=jde)
+    a, _, _ = make_de(**kw)
+    b, _, _ = make_de(**kw)
+    for n in (32, 3, 33):
+        a.generation(n)
+        host(a.fitness())
+    for _ in range(68):
+        b.generation(1)
+    np.testing.assert_array_equal(host(a.population()), host(b.population()))
+    np.testing.assert_array_equal(host(a.fitness()), host(b.fitness()))
+    assert a.stats() == b.stats()
+    a.close()
+    b.close()

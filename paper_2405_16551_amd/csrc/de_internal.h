@@ -30,6 +30,7 @@ struct GenArgs {
   float F, lo, hi, target;
   uint32_t cr_threshold, gen, key_lo, key_hi;
   int tall;           // FP32 product in 64-row tiles (rot_tall)
+  int half;           // BF16 product in 32-row tiles (rot_half)
   uint32_t run_base;  // rotated kernels: draw-counter run = run_base + run
   // jDE (jde != 0): per-individual (F, CR) of generation g and g+1, and the
   // adaptation constants (tau as floor(tau 2^24))
@@ -54,6 +55,7 @@ hipError_t set_max_dynamic_lds(const void* fn);
 // property of the problem, not of a launch: its generations and evaluations
 // sum alike, so that a value evaluated again is the same.
 bool rot_tall(int prec, int dpad, int runs, int NP);
+bool rot_half(int prec, int runs, int NP);
 size_t rot_lds_bytes_host(int prec, int dpad, bool jde = false);
 bool sep_supported(int D);
 

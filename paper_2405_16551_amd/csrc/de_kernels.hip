@@ -930,6 +930,8 @@ hipError_t launch_rot_e(const GenArgs& a, int prec, hipStream_t s) {
   const long long tiles = EVAL ? (a.nrows + 63) / 64
                                : (long long)a.runs * ((a.NP + 63) / 64);
   const bool narrow = rot_bf16_narrow(a.dpad, tiles, device_cus());
+  const bool half =
+      EVAL ? rot_bf16_half((a.nrows + 31) / 32, device_cus()) : a.half;
   // FP32 product of kSplitMinD coordinates and more: split halves, one column
   // block per wave as long as two would leave waves without any (256: eight
   // blocks)
@@ -946,6 +948,9 @@ hipError_t launch_rot_e(const GenArgs& a, int prec, hipStream_t s) {
                                     true>(a, s)
                      : launch_rot_t<PrecF32Narrow, 32, 512, false, true, true>(
                            a, s);
+      if (half)
+        return launch_rot_t<PrecBF16, 32, kRotBf16Threads, false, true, true>(
+            a, s);
       return narrow ? launch_rot_t<PrecBF16, 64, kRotBf16ThreadsNarrow, false,
                                    true, true>(a, s)
                     : launch_rot_t<PrecBF16, 64, kRotBf16Threads, false, true,
@@ -955,6 +960,8 @@ hipError_t launch_rot_e(const GenArgs& a, int prec, hipStream_t s) {
       return split_narrow
                  ? launch_rot_t<PrecSplitNarrow, 32, 512, false, true>(a, s)
                  : launch_rot_t<PrecSplit, 32, 512, false, true>(a, s);
+    if (half)
+      return launch_rot_t<PrecBF16, 32, kRotBf16Threads, false, true>(a, s);
     return narrow
                ? launch_rot_t<PrecBF16, 64, kRotBf16ThreadsNarrow, false,
                               true>(a, s)
@@ -968,6 +975,9 @@ hipError_t launch_rot_e(const GenArgs& a, int prec, hipStream_t s) {
                                   true>(a, s)
                    : launch_rot_t<PrecF32Narrow, 32, 512, false, false, true>(
                          a, s);
+    if (half)
+      return launch_rot_t<PrecBF16, 32, kRotBf16Threads, false, false, true>(
+          a, s);
     return narrow ? launch_rot_t<PrecBF16, 64, kRotBf16ThreadsNarrow, false,
                                  false, true>(a, s)
                   : launch_rot_t<PrecBF16, 64, kRotBf16Threads, false, false,
@@ -979,6 +989,7 @@ hipError_t launch_rot_e(const GenArgs& a, int prec, hipStream_t s) {
     return split_narrow ? launch_rot_t<PrecSplitNarrow, 32, 512, EVAL>(a, s)
                         : launch_rot_t<PrecSplit, 32, 512, EVAL>(a, s);
   }
+  if (half) return launch_rot_t<PrecBF16, 32, kRotBf16Threads, EVAL>(a, s);
   return narrow ? launch_rot_t<PrecBF16, 64, kRotBf16ThreadsNarrow, EVAL>(a, s)
                 : launch_rot_t<PrecBF16, 64, kRotBf16Threads, EVAL>(a, s);
 }
@@ -1010,6 +1021,11 @@ int device_cus() {
 bool rot_tall(int prec, int dpad, int runs, int NP) {
   return prec != kPrecBF16 && dpad >= kTallMinDpad && dpad <= kTallMaxDpad &&
          (long long)runs * ((NP + 31) / 32) > device_cus();
+}
+
+bool rot_half(int prec, int runs, int NP) {
+  return prec == kPrecBF16 &&
+         rot_bf16_half((long long)runs * ((NP + 31) / 32), device_cus());
 }
 
 size_t rot_lds_bytes_host(int prec, int dpad, bool jde) {

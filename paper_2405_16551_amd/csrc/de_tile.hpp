@@ -204,6 +204,17 @@ constexpr int kBf16Rows = 4;
 constexpr int kRotBf16Threads = 1024;
 constexpr int kRotBf16ThreadsNarrow = 512;
 constexpr int kRotBf16NarrowMaxDpad = 512;
+// While tiles of half the height still find a CU each, BF16 tiles have 32 rows:
+// the tile is a chain of round trips and of a wave's rows, and half the rows
+// (two a wave instead of four) make it shorter; R is then streamed by twice the
+// CUs, which would be idle otherwise.  Per generation, 64 / 32 rows: 1 x 250 x
+// 100 6.1 / 5.0 us, 30 x 256 x 100 6.4 / 5.1, 16 x 500 x 333 16.6 / 11.9,
+// 1 x 1024 x 1000 40.5 / 32.1, 8 x 1024 x 1000 (every CU) 41.4 / 36.5.  With more
+// tiles than CUs the 64-row tile, which streams R once per 64 rows.  Rows' sums
+// are formed alike, so the result does not depend on it.
+__host__ __device__ constexpr bool rot_bf16_half(long long tiles32, int cus) {
+  return tiles32 <= cus;
+}
 __host__ __device__ constexpr bool rot_bf16_narrow(int dpad, long long tiles,
                                                    int cus) {
   return dpad <= kRotBf16NarrowMaxDpad && tiles > cus;
@@ -741,8 +752,11 @@ __device__ __forceinline__ void rot_tile(const GenArgs& a, int run, int row0,
     const RotRows c{base, donors, ctl, planes, rng_run, row0, nvalid, stride,
                     tq};
     for (int t = 0; t < tq; ++t)
-      build_chunk<P, sizeof(T) == 2 ? kBf16Rows : 8, kRotWaves, EVAL, JDE>(
-          a, c, t, At);
+      build_chunk<P, sizeof(T) == 2 ? (BM / kRotWaves < kBf16Rows
+                                           ? BM / kRotWaves
+                                           : kBf16Rows)
+                                    : 8,
+                  kRotWaves, EVAL, JDE>(a, c, t, At);
   }
   if constexpr (P::kSplit && PAIR) {
     // rows past the tile's last are zero already (as halves too)

@@ -290,3 +290,31 @@ def test_long_calls_equal_single_steps(jde):
     assert a.stats() == b.stats()
     a.close()
     b.close()
+
+
+# BF16 tiles of 32 rows while they find a compute unit each, else of 64: run 0
+# of a handle of one run equals run 0 of a handle of many, at the rule's edge
+# (256 tiles of 32 rows on 256 compute units), in paired and chunked builds
+@pytest.mark.parametrize("NP,D,many,jde", [
+    (8192, 10, 2, None), (250, 100, 33, None), (33, 128, 130, True),
+    (65, 129, 90, None), (64, 333, 129, True), (33, 1000, 130, None),
+    (32, 1152, 257, None),
+])
+def test_half_height_tiles_equal_full(NP, D, many, jde):
+    kw = dict(NP=NP, D=D, seed=13, kind="rot_osc", gemm_prec="bf16", jde=jde)
+    a, _, _ = make_de(runs=1, **kw)
+    b, _, _ = make_de(runs=many, **kw)
+    a.generation(6)
+    b.generation(6)
+    np.testing.assert_array_equal(host(a.population())[0],
+                                  host(b.population())[0])
+    np.testing.assert_array_equal(host(a.fitness())[0], host(b.fitness())[0])
+    # values of given rows: 33 rows, and more rows than 32 per compute unit
+    x = host(b.population())[0]
+    few = host(a.eval(x[:33]))
+    np.testing.assert_array_equal(few, host(b.fitness())[0][:33])
+    reps = -(-8200 // len(x))
+    many_f = host(a.eval(np.tile(x, (reps, 1))))
+    np.testing.assert_array_equal(many_f[:len(few)], few)
+    a.close()
+    b.close()

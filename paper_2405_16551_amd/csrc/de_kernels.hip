@@ -931,7 +931,7 @@ hipError_t launch_rot_e(const GenArgs& a, int prec, hipStream_t s) {
                                : (long long)a.runs * ((a.NP + 63) / 64);
   const bool narrow = rot_bf16_narrow(a.dpad, tiles, device_cus());
   const bool half =
-      EVAL ? rot_bf16_half((a.nrows + 31) / 32, device_cus()) : a.half;
+      EVAL ? rot_few_tiles((a.nrows + 31) / 32, device_cus()) : a.half;
   // FP32 product of kSplitMinD coordinates and more: split halves, one column
   // block per wave as long as two would leave waves without any (256: eight
   // blocks)
@@ -940,6 +940,20 @@ hipError_t launch_rot_e(const GenArgs& a, int prec, hipStream_t s) {
   if (prec != kPrecBF16 && a.tall)
     return !EVAL && a.jde ? launch_tall<EVAL, !EVAL>(a, s)
                           : launch_tall<EVAL, false>(a, s);
+  // at most one 32-row tile per CU: 16 waves of two rows and one column block
+  if (prec != kPrecBF16 && split &&
+      rot_few_tiles(EVAL ? (a.nrows + 31) / 32
+                         : (long long)a.runs * ((a.NP + 31) / 32),
+                    device_cus())) {
+    if (!EVAL && a.dpad <= kPairMaxDpad)
+      return a.jde ? launch_rot_t<PrecSplitNarrow, 32, 1024, false, true, true>(
+                         a, s)
+                   : launch_rot_t<PrecSplitNarrow, 32, 1024, false, false,
+                                  true>(a, s);
+    return !EVAL && a.jde
+               ? launch_rot_t<PrecSplitNarrow, 32, 1024, EVAL, !EVAL>(a, s)
+               : launch_rot_t<PrecSplitNarrow, 32, 1024, EVAL>(a, s);
+  }
   if (!EVAL && a.jde) {
     // padded width up to 128: trials built two rows per wave instruction
     if (a.dpad <= kPairMaxDpad) {
@@ -1025,7 +1039,7 @@ bool rot_tall(int prec, int dpad, int runs, int NP) {
 
 bool rot_half(int prec, int runs, int NP) {
   return prec == kPrecBF16 &&
-         rot_bf16_half((long long)runs * ((NP + 31) / 32), device_cus());
+         rot_few_tiles((long long)runs * ((NP + 31) / 32), device_cus());
 }
 
 size_t rot_lds_bytes_host(int prec, int dpad, bool jde) {

@@ -210,9 +210,11 @@ constexpr int kRotBf16NarrowMaxDpad = 512;
 // CUs, which would be idle otherwise.  Per generation, 64 / 32 rows: 1 x 250 x
 // 100 6.1 / 5.0 us, 30 x 256 x 100 6.4 / 5.1, 16 x 500 x 333 16.6 / 11.9,
 // 1 x 1024 x 1000 40.5 / 32.1, 8 x 1024 x 1000 (every CU) 41.4 / 36.5.  With more
-// tiles than CUs the 64-row tile, which streams R once per 64 rows.  Rows' sums
-// are formed alike, so the result does not depend on it.
-__host__ __device__ constexpr bool rot_bf16_half(long long tiles32, int cus) {
+// tiles than CUs the 64-row tile, which streams R once per 64 rows.  Split FP32
+// tiles have 32 rows anyway; there they get 16 waves instead of 8: 1 x 1024 x
+// 1000 59.5 -> 55.1 us, 10 x 500 x 333 21.0 -> 18.1, eval of 5000 x 700 rows 46.0
+// -> 44.7.  Rows' sums are formed alike, so the result does not depend on it.
+__host__ __device__ constexpr bool rot_few_tiles(long long tiles32, int cus) {
   return tiles32 <= cus;
 }
 __host__ __device__ constexpr bool rot_bf16_narrow(int dpad, long long tiles,
@@ -755,7 +757,7 @@ __device__ __forceinline__ void rot_tile(const GenArgs& a, int run, int row0,
       build_chunk<P, sizeof(T) == 2 ? (BM / kRotWaves < kBf16Rows
                                            ? BM / kRotWaves
                                            : kBf16Rows)
-                                    : 8,
+                                    : (BM / kRotWaves < 8 ? BM / kRotWaves : 8),
                   kRotWaves, EVAL, JDE>(a, c, t, At);
   }
   if constexpr (P::kSplit && PAIR) {
@@ -883,8 +885,8 @@ __device__ __forceinline__ void rot_tile(const GenArgs& a, int run, int row0,
           reinterpret_cast<const half8*>(a.rop) +
           (size_t)__builtin_amdgcn_readfirstlane(nb0) * (dpad / 16) * 128;
       const int kbn = dpad / 16;  // a multiple of 8
-      // (half the ring where two tiles share a CU: 128 registers)
-      constexpr int kRing = NBW == 2 || PAIR ? 4 : 8;
+      // (half the ring within 128 registers: two tiles a CU, or 16 waves)
+      constexpr int kRing = NBW == 2 || PAIR || NT == 1024 ? 4 : 8;
       const char* ar = reinterpret_cast<const char*>(At) +
                        (size_t)(lane % 32) * stride * 4 + 32 * (lane / 32);
       half8 bh[kRing][NBW], bl[kRing][NBW], ah[2], al[2];

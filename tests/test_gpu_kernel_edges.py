@@ -292,16 +292,22 @@ def test_long_calls_equal_single_steps(jde):
     b.close()
 
 
-# BF16 tiles of 32 rows while they find a compute unit each, else of 64: run 0
+# BF16 tiles of 32 rows while they find a compute unit each, else of 64; split
+# FP32 tiles of 16 waves likewise, else of 8: run 0
 # of a handle of one run equals run 0 of a handle of many, at the rule's edge
 # (256 tiles of 32 rows on 256 compute units), in paired and chunked builds
-@pytest.mark.parametrize("NP,D,many,jde", [
-    (8192, 10, 2, None), (250, 100, 33, None), (33, 128, 130, True),
-    (65, 129, 90, None), (64, 333, 129, True), (33, 1000, 130, None),
-    (32, 1152, 257, None),
+@pytest.mark.parametrize("prec,NP,D,many,jde", [
+    ("bf16", 8192, 10, 2, None), ("bf16", 250, 100, 33, None),
+    ("bf16", 33, 128, 130, True), ("bf16", 65, 129, 90, None),
+    ("bf16", 64, 333, 129, True), ("bf16", 33, 1000, 130, None),
+    ("bf16", 32, 1152, 257, None),
+    ("fp32", 8192, 32, 2, None), ("fp32", 250, 100, 33, True),
+    ("fp32", 33, 128, 130, None), ("fp32", 65, 200, 90, True),
+    ("fp32", 64, 333, 129, None), ("fp32", 50, 512, 129, True),
+    ("fp32", 33, 1100, 130, None),
 ])
-def test_half_height_tiles_equal_full(NP, D, many, jde):
-    kw = dict(NP=NP, D=D, seed=13, kind="rot_osc", gemm_prec="bf16", jde=jde)
+def test_few_tiles_equal_many(prec, NP, D, many, jde):
+    kw = dict(NP=NP, D=D, seed=13, kind="rot_osc", gemm_prec=prec, jde=jde)
     a, _, _ = make_de(runs=1, **kw)
     b, _, _ = make_de(runs=many, **kw)
     a.generation(6)

@@ -514,20 +514,20 @@ __global__ __launch_bounds__(256) void k_debug_draws(GenArgs a, int* idx4,
 // leaves its last lane without coordinates, that lane draws the donor block
 // while the others draw the crossover blocks; the statistics are kept in LDS
 // (the best at the end is the least of the final values: a value is only
-// ever replaced by a smaller one).  0.95 -> 0.69 us per generation.
+// ever replaced by a smaller one).  0.95 -> 0.62 us per generation in launches of
+// 30 (64 x 10); five generations of 24 x 108 x 18: 10.8 -> 9.5 us.
 struct ResidentDraws {
   Donors d;
   Words4 w;
 };
 
-template <int LPI>
+template <int LPI, bool SPARE>
 __device__ __forceinline__ ResidentDraws resident_draws(const GenArgs& a,
                                                         int run, uint32_t gen,
-                                                        int i, int ln,
-                                                        bool spare) {
+                                                        int i, int ln) {
   ResidentDraws r;
   Words4 wd;
-  if (spare) {
+  if constexpr (SPARE) {
     const bool mine = ln == LPI - 1;
     r.w = philox4x32_10(mine ? 0u : (uint32_t)ln, (uint32_t)i, gen,
                         ((mine ? kTagIdx : kTagXover) << 24) | (uint32_t)run,
@@ -550,7 +550,9 @@ __device__ __forceinline__ ResidentDraws resident_draws(const GenArgs& a,
   return r;
 }
 
-template <int LPI>
+// SPARE: a row leaves its last lane without coordinates (a launch fetches its
+// code anew, so each form holds only its own).
+template <int LPI, bool SPARE>
 __global__ __launch_bounds__(1024) void k_sep_resident(GenArgs a, int n_gens,
                                                        float* pop_final,
                                                        float* fit_final,
@@ -574,25 +576,30 @@ __global__ __launch_bounds__(1024) void k_sep_resident(GenArgs a, int n_gens,
     s_hit = ~0u;  // generations of this launch
     s_best = ~0ull;
   }
+  const int groups = (int)blockDim.x / LPI;
+  const int slot = (int)threadIdx.x / LPI, ln = (int)threadIdx.x % LPI;
+  ResidentDraws nx;
   {
+    // every array's first piece is requested at once, and the first draws run
+    // under the loads
     const float4* src =
         reinterpret_cast<const float4*>(a.pop_cur + row0 * ldx);
-    const int n4 = NP * ldx / 4;
-    for (int t = (int)threadIdx.x; t < n4; t += (int)blockDim.x) {
-      const float4 v = src[t];
+    const int n4 = NP * ldx / 4, t0 = (int)threadIdx.x, nt = (int)blockDim.x;
+    const float4 p = src[min(t0, n4 - 1)];
+    const float f = a.fit_cur[row0 + min(t0, NP - 1)];
+    const float o = a.o[min(t0, dq - 1)];
+    __builtin_amdgcn_sched_barrier(0);
+    nx = resident_draws<LPI, SPARE>(a, run, a.gen, min(slot, NP - 1), ln);
+    __builtin_amdgcn_sched_barrier(0);
+    for (int t = t0; t < n4; t += nt) {
+      const float4 v = t == t0 ? p : src[t];
       reinterpret_cast<float4*>(P0)[t] = v;
       reinterpret_cast<float4*>(P1)[t] = v;  // padding alike in both
     }
-    for (int t = (int)threadIdx.x; t < NP; t += (int)blockDim.x)
-      F0[t] = a.fit_cur[row0 + t];
-    for (int t = (int)threadIdx.x; t < dq; t += (int)blockDim.x)
-      so[t] = a.o[t];
+    for (int t = t0; t < NP; t += nt)
+      F0[t] = t == t0 ? f : a.fit_cur[row0 + t];
+    for (int t = t0; t < dq; t += nt) so[t] = t == t0 ? o : a.o[t];
   }
-  const int groups = (int)blockDim.x / LPI;
-  const int slot = (int)threadIdx.x / LPI, ln = (int)threadIdx.x % LPI;
-  const bool spare = (D + 3) / 4 < LPI;
-  ResidentDraws nx =
-      resident_draws<LPI>(a, run, a.gen, min(slot, NP - 1), ln, spare);
   __syncthreads();
   const int dlast = ((D + 3) / 4 - 1) * 4;
   const int jl = min(4 * ln, dlast), j0 = 4 * ln;
@@ -613,8 +620,8 @@ __global__ __launch_bounds__(1024) void k_sep_resident(GenArgs a, int n_gens,
       const float fx = Fc[i];
       {
         const bool wrap = i + groups >= NP;  // next: the next generation
-        nx = resident_draws<LPI>(a, run, gen + (wrap ? 1u : 0u),
-                                 wrap ? slot : i + groups, ln, spare);
+        nx = resident_draws<LPI, SPARE>(a, run, gen + (wrap ? 1u : 0u),
+                                        wrap ? slot : i + groups, ln);
       }
       float4 uv;
       float acc = 0.f;
@@ -648,16 +655,23 @@ __global__ __launch_bounds__(1024) void k_sep_resident(GenArgs a, int n_gens,
   }
   const float* Pf = (n_gens & 1) ? P1 : P0;
   const float* Ff = (n_gens & 1) ? F1 : F0;
+  // the statistics before the rows are stored (the barrier would wait for the
+  // stores), one atomic per wave (the compiler turns one per lane into a loop
+  // over the lanes, 1.6 us)
   {
-    float4* dst = reinterpret_cast<float4*>(pop_final + row0 * ldx);
-    const int n4 = NP * ldx / 4;
-    for (int t = (int)threadIdx.x; t < n4; t += (int)blockDim.x)
-      dst[t] = reinterpret_cast<const float4*>(Pf)[t];
+    unsigned long long best = ~0ull;
     for (int t = (int)threadIdx.x; t < NP; t += (int)blockDim.x) {
-      fit_final[row0 + t] = Ff[t];
-      a.changed[row0 + t] = 1;
-      atomicMin(&s_best, fit_key(Ff[t], t));
+      const unsigned long long k = fit_key(Ff[t], t);
+      best = k < best ? k : best;
     }
+#pragma unroll
+    for (int m = 32; m >= 1; m >>= 1) {
+      const unsigned long long o =
+          ((unsigned long long)__shfl_xor((unsigned)(best >> 32), m, 64) << 32) |
+          (unsigned long long)__shfl_xor((unsigned)best, m, 64);
+      best = o < best ? o : best;
+    }
+    if (threadIdx.x % 64 == 0 && best != ~0ull) atomicMin(&s_best, best);
   }
   __syncthreads();
   if (threadIdx.x == 0) {
@@ -675,6 +689,16 @@ __global__ __launch_bounds__(1024) void k_sep_resident(GenArgs a, int n_gens,
         atomicExch(post.finished, 0u);
         post_done(post.slot, post.seq, atomicAdd(a.done, 0u));
       }
+    }
+  }
+  {
+    float4* dst = reinterpret_cast<float4*>(pop_final + row0 * ldx);
+    const int n4 = NP * ldx / 4;
+    for (int t = (int)threadIdx.x; t < n4; t += (int)blockDim.x)
+      dst[t] = reinterpret_cast<const float4*>(Pf)[t];
+    for (int t = (int)threadIdx.x; t < NP; t += (int)blockDim.x) {
+      fit_final[row0 + t] = Ff[t];
+      a.changed[row0 + t] = 1;
     }
   }
 }
@@ -873,18 +897,28 @@ hipError_t launch_sep_e(const GenArgs& a, hipStream_t s) {
   return launch_sep_j<EVAL, false>(a, s);
 }
 
-template <int LPI>
-hipError_t launch_resident_t(const GenArgs& a, int n_gens, float* pop_final,
+template <int LPI, bool SPARE>
+hipError_t launch_resident_s(const GenArgs& a, int n_gens, float* pop_final,
                              float* fit_final, HostPost post, hipStream_t s) {
-  const void* fn = reinterpret_cast<const void*>(&k_sep_resident<LPI>);
+  const void* fn = reinterpret_cast<const void*>(&k_sep_resident<LPI, SPARE>);
   const hipError_t e = set_max_dynamic_lds(fn);
   if (e != hipSuccess) return e;
   int threads = ((a.NP * LPI + 63) / 64) * 64;
   threads = std::min(std::max(threads, 64), 1024);
-  hipLaunchKernelGGL((k_sep_resident<LPI>), dim3(a.runs), dim3(threads),
+  hipLaunchKernelGGL((k_sep_resident<LPI, SPARE>), dim3(a.runs), dim3(threads),
                      sep_resident_lds_bytes(a.NP, a.ldx, a.D), s, a, n_gens,
                      pop_final, fit_final, post);
   return hipGetLastError();
+}
+
+template <int LPI>
+hipError_t launch_resident_t(const GenArgs& a, int n_gens, float* pop_final,
+                             float* fit_final, HostPost post, hipStream_t s) {
+  return (a.D + 3) / 4 < LPI
+             ? launch_resident_s<LPI, true>(a, n_gens, pop_final, fit_final,
+                                            post, s)
+             : launch_resident_s<LPI, false>(a, n_gens, pop_final, fit_final,
+                                             post, s);
 }
 
 template <class P, int BM, int NT, bool EVAL, bool JDE = false,

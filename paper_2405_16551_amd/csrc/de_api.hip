@@ -219,8 +219,6 @@ GenArgs base_args(const de_state* s) {
   a.D = s->p.D;
   a.ldx = s->ldx;
   a.dpad = s->dpad;
-  a.tall = s->kind == de::kObjRotOsc &&
-           de::rot_tall(s->prec, s->dpad, s->p.runs, s->p.NP);
   a.half = s->kind == de::kObjRotOsc &&
            de::rot_half(s->prec, s->p.runs, s->p.NP);
   a.nrows = s->p.runs * s->p.NP;

@@ -29,7 +29,6 @@ struct GenArgs {
   int runs, NP, D, ldx, dpad, nrows;
   float F, lo, hi, target;
   uint32_t cr_threshold, gen, key_lo, key_hi;
-  int tall;           // FP32 product in 64-row tiles (rot_tall)
   int half;           // BF16 product in 32-row tiles (rot_half)
   uint32_t run_base;  // rotated kernels: draw-counter run = run_base + run
   // jDE (jde != 0): per-individual (F, CR) of generation g and g+1, and the
@@ -50,11 +49,7 @@ hipError_t note_hip(hipError_t e, const char* file, int line);
 // CU's 160 KB, on the current device (once per kernel and device).
 hipError_t set_max_dynamic_lds(const void* fn);
 
-// Whether a problem's FP32 product takes the 64-row tile: rows too wide for
-// two 32-row tiles per compute unit, and more 32-row tiles than units.  A
-// property of the problem, not of a launch: its generations and evaluations
-// sum alike, so that a value evaluated again is the same.
-bool rot_tall(int prec, int dpad, int runs, int NP);
+// Whether a problem's BF16 product takes the 32-row tile.
 bool rot_half(int prec, int runs, int NP);
 size_t rot_lds_bytes_host(int prec, int dpad, bool jde = false);
 bool sep_supported(int D);

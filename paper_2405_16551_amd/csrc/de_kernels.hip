@@ -153,20 +153,6 @@ void k_rot(GenArgs a) {
   rot_tile<P, BM, NT, EVAL, JDE, PAIR>(a, run, row0, nvalid);
 }
 
-// FP32 product, 64 rows per tile.
-template <int NB, bool EVAL, bool JDE>
-__global__ __launch_bounds__(512) void k_rot_tall(GenArgs a) {
-  const int lb = xcd_logical_block((int)blockIdx.x, (int)gridDim.x);
-  int run = 0, row0 = lb * kTallRows, nvalid = min(kTallRows, a.nrows - row0);
-  if (!EVAL) {
-    const int tiles = (a.NP + kTallRows - 1) / kTallRows;
-    run = lb / tiles;
-    row0 = (lb - run * tiles) * kTallRows;
-    nvalid = min(kTallRows, a.NP - row0);
-  }
-  rot_tile_tall<NB, EVAL, JDE>(a, run, row0, nvalid);
-}
-
 // jDE: every individual starts from the same (F, CR).
 __global__ __launch_bounds__(256) void k_fill_control(float2* jp, int n,
                                                       float F, float CR) {
@@ -941,24 +927,6 @@ hipError_t launch_rot_t(const GenArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-template <int NB, bool EVAL, bool JDE>
-hipError_t launch_tall_t(const GenArgs& a, hipStream_t s) {
-  const hipError_t e = set_max_dynamic_lds(
-      reinterpret_cast<const void*>(&k_rot_tall<NB, EVAL, JDE>));
-  if (e != hipSuccess) return e;
-  const int blocks = EVAL ? (a.nrows + kTallRows - 1) / kTallRows
-                          : a.runs * ((a.NP + kTallRows - 1) / kTallRows);
-  hipLaunchKernelGGL((k_rot_tall<NB, EVAL, JDE>), dim3(blocks), dim3(512),
-                     tall_lds_bytes(a.dpad, JDE), s, a);
-  return hipGetLastError();
-}
-
-template <bool EVAL, bool JDE>
-hipError_t launch_tall(const GenArgs& a, hipStream_t s) {
-  return a.dpad <= 768 ? launch_tall_t<3, EVAL, JDE>(a, s)
-                       : launch_tall_t<4, EVAL, JDE>(a, s);
-}
-
 template <bool EVAL>
 hipError_t launch_rot_e(const GenArgs& a, int prec, hipStream_t s) {
   const long long tiles = EVAL ? (a.nrows + 63) / 64
@@ -971,9 +939,6 @@ hipError_t launch_rot_e(const GenArgs& a, int prec, hipStream_t s) {
   // blocks)
   const bool split = a.D >= kSplitMinD;
   const bool split_narrow = a.dpad <= kSplitNarrowMaxDpad;
-  if (prec != kPrecBF16 && a.tall)
-    return !EVAL && a.jde ? launch_tall<EVAL, !EVAL>(a, s)
-                          : launch_tall<EVAL, false>(a, s);
   // at most one 32-row tile per CU: 16 waves of two rows and one column block
   if (prec != kPrecBF16 && split &&
       rot_few_tiles(EVAL ? (a.nrows + 31) / 32
@@ -1064,18 +1029,13 @@ int device_cus() {
   return n;
 }
 
-// LDS bytes of the rotated kernel: BF16 tiles of 64 rows, FP32 tiles of 32
-// rows (independent of the number of threads).
-bool rot_tall(int prec, int dpad, int runs, int NP) {
-  return prec != kPrecBF16 && dpad >= kTallMinDpad && dpad <= kTallMaxDpad &&
-         (long long)runs * ((NP + 31) / 32) > device_cus();
-}
-
 bool rot_half(int prec, int runs, int NP) {
   return prec == kPrecBF16 &&
          rot_few_tiles((long long)runs * ((NP + 31) / 32), device_cus());
 }
 
+// LDS bytes of the rotated kernel's largest tile: BF16 64 rows, FP32 32 rows
+// (independent of the number of threads).
 size_t rot_lds_bytes_host(int prec, int dpad, bool jde) {
   if (prec != kPrecBF16)
     return jde ? rot_lds_bytes<PrecSplit, 32, true>(dpad)

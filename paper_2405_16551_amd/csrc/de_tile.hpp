@@ -1058,253 +1058,4 @@ __device__ __forceinline__ void rot_tile(const GenArgs& a, int run, int row0,
   select_rows<BM, kRotWaves, EVAL, JDE>(a, c, run, fpart, sr);
 }
 
-// ---------------------------------------------------------------------------
-// Tall split tile: 64 rows for rows of 513 to 1024 coordinates.  The 32-row
-// tile streams all of R (4 bytes per element) from L2 for 32 rows and is
-// bound by that stream (16 x 1024 x 1000: 2.1 GB per generation, 17 TB/s).
-// Here 64 rows share it: the A tile holds kTallPart coordinates at a time,
-// the next part is built when the product of the last is done, and every
-// wave keeps the accumulators of its NB column blocks (both row blocks, 32
-// NB registers) over the parts.  One accumulator per block takes all three
-// half products (measured error of z against 64 bits relative to its rms at
-// K = 512 / 1008: 2.5e-7 / 3.7e-7; FP32 MFMA 3.9e-7 / 5.8e-7).  A part's rows
-// are scaled by their own largest |y|, but never more than the parts before
-// (then the accumulators would have to grow); where a later part needs a
-// smaller scale they are scaled down by the same power of two.
-// One workgroup of 8 waves (256 registers) per CU, so it pays from more than
-// one 32-row tile per CU on: 16 x 1024 x 1000 124 us per generation
-// against 141.
-constexpr int kTallPart = 512;
-constexpr int kTallMinDpad = 640, kTallMaxDpad = 1024;
-constexpr int kTallRows = 64;
-
-__host__ __device__ constexpr size_t tall_lds_bytes(int dpad, bool jde) {
-  const int tq = (dpad / 4 + 63) / 64;
-  return (size_t)kTallRows * (kTallPart + PrecSplit::kPad) * sizeof(float)
-         + (size_t)kTallRows * tq * 4 * sizeof(unsigned long long)  // planes
-         + (size_t)kTallRows * 4 * sizeof(int)                      // donors
-         + (size_t)kRotSlots * kTallRows * sizeof(float)            // slot sums
-         + (size_t)kTallRows * 2 * sizeof(int)  // scale exponents, ratios
-         + (jde ? (size_t)kTallRows * sizeof(Control) : 0);
-}
-
-// Exponent of the power of two that brings a row's largest magnitude m to
-// [2^14, 2^15): 127 for zero rows, 0 where m is not finite.
-__device__ __forceinline__ int split_exponent(float m) {
-  const int E = (int)(__builtin_bit_cast(uint32_t, m) >> 23);
-  if (m == 0.f) return 127;
-  return E >= 255 ? 0 : 141 - max(E, 15);
-}
-
-template <int NB, bool EVAL, bool JDE>
-__device__ __forceinline__ void rot_tile_tall(const GenArgs& a, int run,
-                                              int row0, int nvalid) {
-  constexpr int kWaves = 8, BM = kTallRows;
-  extern __shared__ __align__(16) char smem[];
-  const int dpad = a.dpad, stride = kTallPart + PrecSplit::kPad;
-  const int tq = (dpad / 4 + 63) / 64;
-  float* At = reinterpret_cast<float*>(smem);
-  unsigned long long* planes =
-      reinterpret_cast<unsigned long long*>(At + (size_t)BM * stride);
-  int* donors = reinterpret_cast<int*>(planes + (size_t)BM * tq * 4);
-  float* fpart = reinterpret_cast<float*>(donors + BM * 4);
-  int* rexp = reinterpret_cast<int*>(fpart + kRotSlots * BM);
-  float* ratio = reinterpret_cast<float*>(rexp + BM);
-  Control* ctl = reinterpret_cast<Control*>(ratio + BM);
-  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / 64);
-  const int lane = (int)threadIdx.x % 64;
-  const uint32_t rng_run = a.run_base + (uint32_t)run;
-  const RotRows c{a.pop_cur + (EVAL ? 0 : (size_t)run * a.NP * a.ldx),
-                  donors, ctl, planes, rng_run, row0, nvalid, stride, tq};
-  if (!EVAL && (int)threadIdx.x < nvalid) {
-    const int rl = (int)threadIdx.x;
-    const Donors d = pick_donors(rng_run, a.gen, row0 + rl, a.NP, a.D,
-                                 a.key_lo, a.key_hi);
-    donors[rl * 4 + 0] = d.r1;
-    donors[rl * 4 + 1] = d.r2;
-    donors[rl * 4 + 2] = d.r3;
-    donors[rl * 4 + 3] = d.jrand;
-    if constexpr (JDE) {
-      const float2 p = a.jp_cur[(size_t)run * a.NP + row0 + rl];
-      ctl[rl] = jde_control(rng_run, a.gen, row0 + rl, a.key_lo, a.key_hi,
-                            a.jF_lo, a.jF_span, a.jtau_F, a.jtau_CR,
-                            Control{p.x, p.y});
-    }
-  }
-  if (threadIdx.x < BM) rexp[threadIdx.x] = 127;
-  __syncthreads();
-  const SelectRow sr = select_row<kWaves, EVAL>(a, run, row0, nvalid);
-  const int nblk = dpad / 32, kbn = dpad / 16;
-  floatx16 acc[NB][2];
-#pragma unroll
-  for (int n = 0; n < NB; ++n) acc[n][0] = acc[n][1] = floatx16{};
-  // the wave's column blocks wave + 8 n (past the last: the last again,
-  // their values unused)
-  const half8* rb[NB];
-#pragma unroll
-  for (int n = 0; n < NB; ++n)
-    rb[n] = reinterpret_cast<const half8*>(a.rop) +
-            (size_t)min(wave + kWaves * n, nblk - 1) * kbn * 128;
-  const char* ar = reinterpret_cast<const char*>(At) +
-                   (size_t)(lane % 32) * stride * 4 + 32 * (lane / 32);
-  const char* ar1 = ar + (size_t)32 * stride * 4;
-  for (int k0 = 0; k0 < dpad; k0 += kTallPart) {
-    const int width = min(kTallPart, dpad - k0);
-    if (k0 > 0) __syncthreads();  // the last part's products are done
-    for (int t = k0 / 256; 256 * t < k0 + width; ++t)
-      build_chunk<PrecSplit, 4, kWaves, EVAL, JDE>(a, c, t, At - k0);
-    // each wave splits the rows it built, eight coordinates per lane
-    __builtin_amdgcn_wave_barrier();
-#pragma unroll 2
-    for (int k = 0; k < BM / kWaves; ++k) {
-      const int rl = wave + kWaves * k;
-      float* arow = At + (size_t)rl * stride + 8 * lane;
-      float v[8];
-      float m = 0.f;
-      const bool in = 8 * lane < width && rl < nvalid;
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const float4 p = ld4(arow + 4 * h);
-#pragma unroll
-        for (int b = 0; b < 4; ++b) {
-          v[4 * h + b] = in ? get(p, b) : 0.f;
-          m = fmaxf(m, fabsf(v[4 * h + b]));
-        }
-      }
-      m = fmaxf(m, lane_xor<32>(m));
-      m = fmaxf(m, lane_xor<16>(m));
-      m = fmaxf(m, lane_xor<8>(m));
-      m = fmaxf(m, lane_xor<4>(m));
-      m = fmaxf(m, lane_xor<2>(m));
-      m = fmaxf(m, lane_xor<1>(m));
-      const int old = rexp[rl];
-      const int e = min(old, split_exponent(m));
-      half8 h, l;
-      split_halves(v, ldexpf(1.f, e), h, l);
-      if (8 * lane < width) {
-        *reinterpret_cast<half8*>(arow) = h;
-        *reinterpret_cast<half8*>(arow + 4) = l;
-      }
-      if (lane == 0) {
-        rexp[rl] = e;
-        ratio[rl] = ldexpf(1.f, e - old);
-      }
-    }
-    __syncthreads();
-    if (k0 > 0) {
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const float4 s0 = ld4(ratio + 8 * q + 4 * (lane / 32));
-        const float4 s1 = ld4(ratio + 32 + 8 * q + 4 * (lane / 32));
-#pragma unroll
-        for (int n = 0; n < NB; ++n)
-#pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            acc[n][0][4 * q + r] *= get(s0, r);
-            acc[n][1][4 * q + r] *= get(s1, r);
-          }
-      }
-    }
-    // products of the part: a ring of two K-steps of fragments, reloaded
-    // after their last use (no branch, in the loop's order, so that the
-    // loads in flight can be counted)
-    const int steps = width / 16, kb0 = k0 / 16;  // multiples of 8
-    half8 bh[2][NB], bl[2][NB], ah[2][2], al[2][2];
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-#pragma unroll
-      for (int n = 0; n < NB; ++n) {
-        bh[u][n] = rb[n][(kb0 + u) * 128 + lane];
-        __builtin_amdgcn_sched_barrier(0);
-      }
-#pragma unroll
-      for (int n = 0; n < NB; ++n) {
-        bl[u][n] = rb[n][(kb0 + u) * 128 + 64 + lane];
-        __builtin_amdgcn_sched_barrier(0);
-      }
-    }
-    ah[0][0] = *reinterpret_cast<const half8*>(ar);
-    al[0][0] = *reinterpret_cast<const half8*>(ar + 16);
-    ah[0][1] = *reinterpret_cast<const half8*>(ar1);
-    al[0][1] = *reinterpret_cast<const half8*>(ar1 + 16);
-    for (int kb = 0; kb < steps; kb += 2) {
-      const int kn = kb + 2 < steps ? kb + 2 : kb;
-#pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        const int nxt = u ^ 1;
-        const int ka = u == 0 ? kb + 1 : kn;
-        al[nxt][0] = *reinterpret_cast<const half8*>(ar + ka * 64 + 16);
-        al[nxt][1] = *reinterpret_cast<const half8*>(ar1 + ka * 64 + 16);
-        ah[nxt][0] = *reinterpret_cast<const half8*>(ar + ka * 64);
-        ah[nxt][1] = *reinterpret_cast<const half8*>(ar1 + ka * 64);
-#pragma unroll
-        for (int n = 0; n < NB; ++n)
-#pragma unroll
-          for (int m = 0; m < 2; ++m)
-            acc[n][m] = __builtin_amdgcn_mfma_f32_32x32x16_f16(
-                al[u][m], bh[u][n], acc[n][m], 0, 0, 0);
-#pragma unroll
-        for (int n = 0; n < NB; ++n)
-#pragma unroll
-          for (int m = 0; m < 2; ++m)
-            acc[n][m] = __builtin_amdgcn_mfma_f32_32x32x16_f16(
-                ah[u][m], bh[u][n], acc[n][m], 0, 0, 0);
-#pragma unroll
-        for (int n = 0; n < NB; ++n)
-#pragma unroll
-          for (int m = 0; m < 2; ++m)
-            acc[n][m] = __builtin_amdgcn_mfma_f32_32x32x16_f16(
-                ah[u][m], bl[u][n], acc[n][m], 0, 0, 0);
-#pragma unroll
-        for (int n = 0; n < NB; ++n)
-          bh[u][n] = rb[n][(kb0 + kn + u) * 128 + lane];
-#pragma unroll
-        for (int n = 0; n < NB; ++n)
-          bl[u][n] = rb[n][(kb0 + kn + u) * 128 + 64 + lane];
-        // the first MFMAs with the next step's A reads, then the fragments
-        // as their last use is done
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          __builtin_amdgcn_sched_group_barrier(0x008, NB / 2, 0);  // MFMA
-          __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);       // DS read
-        }
-        __builtin_amdgcn_sched_group_barrier(0x008, 2 * NB - 4 * (NB / 2), 0);
-#pragma unroll
-        for (int k = 0; k < 2 * NB; ++k) {
-          __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
-          __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);  // VMEM read
-        }
-        __builtin_amdgcn_sched_barrier(0);
-      }
-    }
-  }
-  // objective: z in the rows' and R's scales, row sums per column block;
-  // blocks s and s + 16 of slot s are the wave's, in order
-  const float rs0 = split_scale(*a.rmax).inv;
-  float sacc[2] = {0.f, 0.f};
-#pragma unroll
-  for (int n = 0; n < NB; ++n) {
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int rl = 8 * q + 4 * (lane / 32) + r;
-        acc[n][0][4 * q + r] =
-            ldexpf(acc[n][0][4 * q + r], -rexp[rl]) * rs0;
-        acc[n][1][4 * q + r] =
-            ldexpf(acc[n][1][4 * q + r], -rexp[32 + rl]) * rs0;
-      }
-    const float total = osc_rows<false, true>(acc[n][0], acc[n][1], lane);
-    if (wave + kWaves * n < nblk) sacc[n & 1] += total;
-  }
-  {
-    const int idx = lane % 32, hb = idx / 16, r = idx % 16;
-    const int rin = 8 * (r / 4) + 4 * (lane / 32) + (r % 4);
-    fpart[(size_t)wave * BM + hb * 32 + rin] = sacc[0];
-    fpart[(size_t)(wave + 8) * BM + hb * 32 + rin] = sacc[1];
-  }
-  __syncthreads();
-  select_rows<BM, kWaves, EVAL, JDE>(a, c, run, fpart, sr);
-}
-
 }  // namespace de

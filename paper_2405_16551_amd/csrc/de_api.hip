@@ -38,14 +38,13 @@ constexpr uint64_t kMagic = 0x4445'6d69'3335'3578ull;
 constexpr int64_t kGenLimit = int64_t(1) << 32;  // counter field is 32-bit
 
 struct Layout {
-  // done: the counter, at kRmaxAt the largest |R|, at kFinishedAt the count
-  // of finished workgroups
+  // done: the counter, and at kFinishedAt the count of finished workgroups
   size_t best, hit, acc, done, changed, opad, rop, rf32, f64, idx, jp[2],
       total;
 };
 
 // within the done counter's 256 bytes
-constexpr size_t kRmaxAt = 16, kFinishedAt = 32;
+constexpr size_t kFinishedAt = 32;
 
 size_t round_up(size_t v, size_t m) { return (v + m - 1) / m * m; }
 
@@ -186,7 +185,8 @@ de_status check_problem(const de_params* p, const de_objective* o) {
       return DE_E_INVAL;
     if (!o->R || !aligned(o->R, 4) || o->ldr < p->D) return DE_E_INVAL;
     const int dpad = dpad_for(p->D);
-    if (de::rot_lds_bytes_host(o->gemm_prec, dpad) > (size_t)de::kMaxLdsBytes)
+    if (dpad > de::kMaxRotDpad ||
+        de::rot_lds_bytes_host(o->gemm_prec, dpad) > (size_t)de::kMaxLdsBytes)
       return DE_E_UNSUPPORTED;
   } else {
     if (!de::sep_supported(p->D)) return DE_E_UNSUPPORTED;
@@ -208,7 +208,6 @@ GenArgs base_args(const de_state* s) {
   GenArgs a{};
   a.o = reinterpret_cast<const float*>(s->work + s->L.opad);
   a.rop = s->L.rop ? s->work + s->L.rop : nullptr;
-  a.rmax = reinterpret_cast<const float*>(s->work + s->L.done + kRmaxAt);
   a.best_key = reinterpret_cast<unsigned long long*>(s->work + s->L.best);
   a.hit_gen = reinterpret_cast<unsigned long long*>(s->work + s->L.hit);
   a.accepted = reinterpret_cast<unsigned long long*>(s->work + s->L.acc);
@@ -647,8 +646,6 @@ de_status init_common(const de_params* params, const de_objective* objective,
                                 p.D, s->dpad, s->kind, s->prec,
                                 reinterpret_cast<float*>(s->work + L.opad),
                                 L.rop ? s->work + L.rop : nullptr,
-                                reinterpret_cast<float*>(s->work + L.done +
-                                                         kRmaxAt),
                                 st));
   if (rc == DE_OK && L.rf32)
     rc = FROM_HIP(de::launch_copy_rot(objective->R, objective->ldr, p.D,
@@ -1093,8 +1090,6 @@ DE_API de_status de_generation_noalloc(const de_params* params,
                                 p.D, s.dpad, s.kind, s.prec,
                                 reinterpret_cast<float*>(s.work + L.opad),
                                 L.rop ? s.work + L.rop : nullptr,
-                                reinterpret_cast<float*>(s.work + L.done +
-                                                         kRmaxAt),
                                 st));
   const GenArgs a = base_args(&s);
   if (rc == DE_OK) rc = FROM_HIP(de::launch_stats_reset(a, true, st));

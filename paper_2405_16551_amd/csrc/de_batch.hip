@@ -1151,11 +1151,11 @@ DE_API de_status de_batch_create(const de_batch_params* params, float* pop0,
     float* opad = reinterpret_cast<float*>(b->work + L.opad_at[k]);
     rc = FROM_HIP(de::launch_prep(in.o, in.R, in.ldr, in.D, dpad_generic(in.D),
                                   de::kObjRotOsc, de::kPrecBF16, opad,
-                                  b->work + L.ropg_at[k], nullptr, st));
+                                  b->work + L.ropg_at[k], st));
     if (rc == DE_OK && L.ropw_at[k] != L.ropg_at[k])
       rc = FROM_HIP(de::launch_prep(in.o, in.R, in.ldr, in.D, dpad_wide(in.D),
                                     de::kObjRotOsc, de::kPrecBF16, opad,
-                                    b->work + L.ropw_at[k], nullptr, st));
+                                    b->work + L.ropw_at[k], st));
   }
   if (rc != DE_OK) return fail(rc);
 

@@ -11,6 +11,9 @@ enum { kObjSphere = 0, kObjRotOsc = 1 };
 enum { kPrecF32 = 0, kPrecBF16 = 1 };
 
 constexpr int kMaxLdsBytes = 160 * 1024;  // gfx950 LDS per workgroup
+// Widest padded row of the rotated objective: a BF16 tile's rows then fill the
+// LDS, and an FP32 tile's 16 waves have three column blocks each.
+constexpr int kMaxRotDpad = 1152;
 
 // Everything one generation launch needs, passed by value.
 struct GenArgs {
@@ -20,7 +23,6 @@ struct GenArgs {
   float* fit_next;        // f of generation g+1 (EVAL: output values)
   const float* o;         // shift, zero-padded to dpad
   const void* rop;        // R in the MFMA B-operand layout (rotated only)
-  const float* rmax;      // largest |R| (split FP32 product only)
   unsigned long long* best_key;  // [runs] ordered (f, index) keys
   unsigned long long* hit_gen;   // [runs] first generation with best <= target
   unsigned long long* accepted;  // [runs] accepted trials
@@ -81,7 +83,7 @@ hipError_t launch_fill_control(float2* jp, int n, float F, float CR,
                                hipStream_t s);
 hipError_t launch_prep(const float* o, const float* R, int ldr, int D,
                        int dpad, int kind, int prec, float* o_pad, void* rop,
-                       float* rmax, hipStream_t s);
+                       hipStream_t s);
 hipError_t launch_stats_reset(const GenArgs& a, bool reset_accepted,
                               hipStream_t s);
 hipError_t launch_best_from_fit(const GenArgs& a, hipStream_t s);

@@ -131,13 +131,12 @@ __global__ __launch_bounds__(256) void k_sep(GenArgs a) {
   }
 }
 
-// BF16 tiles of fewer than 1024 threads and paired split tiles: two
-// workgroups per CU (four waves per SIMD, 128 registers).
+// BF16 operands in fewer than 1024 threads: two workgroups per CU (four waves
+// per SIMD, 128 registers).
 template <class P, int BM, int NT, bool EVAL, bool JDE, bool PAIR = false>
 __global__ __launch_bounds__(NT)
 __attribute__((amdgpu_waves_per_eu(
-    ((sizeof(typename P::T) == 2 && NT < 1024) || (P::kSplit && PAIR)) ? 4
-                                                                       : 1)))
+    (sizeof(typename P::T) == 2 && NT < 1024) ? 4 : 1)))
 void k_rot(GenArgs a) {
   const int lb = xcd_logical_block((int)blockIdx.x, (int)gridDim.x);
   int run = 0, row0 = 0, nvalid = 0;
@@ -151,6 +150,23 @@ void k_rot(GenArgs a) {
     nvalid = min(BM, a.NP - row0);
   }
   rot_tile<P, BM, NT, EVAL, JDE, PAIR>(a, run, row0, nvalid);
+}
+
+// FP32 product in three-part operands.  32-row tiles: four waves per SIMD.
+template <int MB, int NB, int NW, bool EVAL, bool JDE>
+__global__ __launch_bounds__(64 * NW)
+__attribute__((amdgpu_waves_per_eu(MB == 1 && NB <= 2 ? 4 : 2)))
+void k_rot_x3(GenArgs a) {
+  constexpr int BM = 32 * MB;
+  const int lb = xcd_logical_block((int)blockIdx.x, (int)gridDim.x);
+  int run = 0, row0 = lb * BM, nvalid = min(BM, a.nrows - row0);
+  if (!EVAL) {
+    const int tiles = (a.NP + BM - 1) / BM;
+    run = lb / tiles;
+    row0 = (lb - run * tiles) * BM;
+    nvalid = min(BM, a.NP - row0);
+  }
+  rot_tile_x3<MB, NB, NW, EVAL, JDE>(a, run, row0, nvalid);
 }
 
 // jDE: every individual starts from the same (F, CR).
@@ -197,11 +213,8 @@ __global__ __launch_bounds__(64) void k_delay(uint64_t ticks) {
     __builtin_amdgcn_s_sleep(2);
 }
 
-// *rmax (null: none) is cleared for k_rot_max.
 __global__ __launch_bounds__(256) void k_prep_shift(const float* o, int D,
-                                                    int dpad, float* o_pad,
-                                                    float* rmax) {
-  if (rmax && blockIdx.x == 0 && threadIdx.x == 0) *rmax = 0.f;
+                                                    int dpad, float* o_pad) {
   for (int k = blockIdx.x * 256 + threadIdx.x; k < dpad; k += gridDim.x * 256)
     o_pad[k] = k < D ? o[k] : 0.f;
 }
@@ -239,41 +252,21 @@ __global__ __launch_bounds__(256) void k_prep_rot_f32(const float* R, int ldr,
   }
 }
 
-// Largest |R| (*rmax starts at zero; non-negative floats order as integers).
-__global__ __launch_bounds__(256) void k_rot_max(const float* R, int ldr, int D,
-                                                 float* rmax) {
-  const int n = (int)blockIdx.x;
-  float m = 0.f;
-  for (int k = (int)threadIdx.x; k < D; k += 256)
-    m = fmaxf(m, fabsf(R[(size_t)n * ldr + k]));
-  for (int x = 32; x >= 1; x >>= 1) m = fmaxf(m, __shfl_xor(m, x, 64));
-  if (threadIdx.x % 64 == 0)
-    atomicMax(reinterpret_cast<int*>(rmax), __builtin_bit_cast(int, m));
-}
-
-// Split layout (PrecSplit): R scaled by one power of two (from *rmax), as
-// halves: element (n, k) of half p goes to block nb = n / 32, K-step kb =
-// k / 16, lane (n % 32) + 32 ((k % 16) / 8), slot k % 8 of fragment
-// ((nb * dpad / 16 + kb) * 2 + p) * 64 + lane.  One workgroup per row.
-__global__ __launch_bounds__(256) void k_prep_rot_split(const float* R, int ldr,
-                                                        int D, int dpad,
-                                                        const float* rmax,
-                                                        half8* rop) {
-  const int n = (int)blockIdx.x;
-  const RowScale rs = split_scale(*rmax);
-  for (int g8 = (int)threadIdx.x; g8 < dpad / 8; g8 += 256) {
-    float v[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int k = 8 * g8 + u;
-      v[u] = n < D && k < D ? R[(size_t)n * ldr + k] : 0.f;
-    }
-    half8 h, l;
-    split_halves(v, rs.scale, h, l);
-    const size_t f = ((size_t)(n / 32) * (dpad / 16) + g8 / 2) * 128 +
-                     (n % 32) + 32 * (g8 % 2);
-    rop[f] = h;
-    rop[f + 64] = l;
+// Three-part layout (PrecX3), FP32: block nb = n / 32, K-step kb = k / 16, half
+// p of the lane's eight coordinates, lane (n % 32) + 32 ((k % 16) / 8), slot
+// k % 4 of float4 ((nb * dpad / 16 + kb) * 2 + p) * 64 + lane.
+__global__ __launch_bounds__(256) void k_prep_rot_x3(const float* R, int ldr,
+                                                     int D, int dpad,
+                                                     float* rop) {
+  const size_t total = (size_t)dpad * dpad;
+  for (size_t t = (size_t)blockIdx.x * 256 + threadIdx.x; t < total;
+       t += (size_t)gridDim.x * 256) {
+    const int e = (int)(t % 4), lane = (int)(t / 4 % 64);
+    const int p = (int)(t / 256 % 2), kb = (int)(t / 512 % (dpad / 16));
+    const int nb = (int)(t / 512 / (dpad / 16));
+    const int n = nb * 32 + lane % 32;
+    const int k = kb * 16 + 8 * (lane / 32) + 4 * p + e;
+    rop[t] = n < D && k < D ? R[(size_t)n * ldr + k] : 0.f;
   }
 }
 
@@ -927,6 +920,49 @@ hipError_t launch_rot_t(const GenArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
+template <int MB, int NB, int NW, bool EVAL, bool JDE>
+hipError_t launch_x3_t(const GenArgs& a, hipStream_t s) {
+  constexpr int BM = 32 * MB;
+  const hipError_t e = set_max_dynamic_lds(
+      reinterpret_cast<const void*>(&k_rot_x3<MB, NB, NW, EVAL, JDE>));
+  if (e != hipSuccess) return e;
+  const int blocks = EVAL ? (a.nrows + BM - 1) / BM
+                          : a.runs * ((a.NP + BM - 1) / BM);
+  hipLaunchKernelGGL((k_rot_x3<MB, NB, NW, EVAL, JDE>), dim3(blocks),
+                     dim3(64 * NW), x3_lds_bytes(BM, a.dpad, JDE), s, a);
+  return hipGetLastError();
+}
+
+// The FP32 product of kX3MinD coordinates and more.  Rows of up to 128 in
+// generation steps: the paired build.  While 32-row tiles find a CU each, 16
+// waves (four per SIMD) against 8: 1 x 1024 x 1000 108 us per generation / 197,
+// 10 x 500 x 333 28.8 / 31.5, evaluation of 5000 x 700 rows 70 / 102.  With more
+// tiles: up to 512 coordinates 8 waves and two workgroups per CU (40 x 500 x
+// 200 33.7 us, with 16 waves 41.1; 40 x 500 x 333 74.8 / 78.5); from 769 to
+// 1024 tiles of 64 rows, which stream R once for both row blocks (16 x 1024 x
+// 1000 250 us, 32 rows 276); between, 32 rows (20 x 1024 x 700 238 us, 64 rows
+// 248; 24 x 1000 x 600 219 / 209).  Beyond 1024 coordinates 8 waves hold z of
+// five column blocks each, which 16 waves have no registers for.
+template <bool EVAL, bool JDE>
+hipError_t launch_x3(const GenArgs& a, hipStream_t s) {
+  const bool few =
+      rot_few_tiles(EVAL ? (a.nrows + 31) / 32
+                         : (long long)a.runs * ((a.NP + 31) / 32),
+                    device_cus());
+  if constexpr (!EVAL)
+    if (a.dpad <= kPairMaxDpad)
+      return few ? launch_rot_t<PrecX3, 32, 1024, false, JDE, true>(a, s)
+                 : launch_rot_t<PrecX3, 32, 512, false, JDE, true>(a, s);
+  const int nblk = (a.D + 31) / 32;
+  if (nblk > 32) return launch_x3_t<1, 5, 8, EVAL, JDE>(a, s);
+  if (!few && nblk > kX3TallMinBlocks)
+    return launch_x3_t<2, 4, 8, EVAL, JDE>(a, s);
+  if (nblk > 16) return launch_x3_t<1, 2, 16, EVAL, JDE>(a, s);
+  if (few) return launch_x3_t<1, 1, 16, EVAL, JDE>(a, s);
+  return nblk <= 8 ? launch_x3_t<1, 1, 8, EVAL, JDE>(a, s)
+                   : launch_x3_t<1, 2, 8, EVAL, JDE>(a, s);
+}
+
 template <bool EVAL>
 hipError_t launch_rot_e(const GenArgs& a, int prec, hipStream_t s) {
   const long long tiles = EVAL ? (a.nrows + 63) / 64
@@ -934,33 +970,14 @@ hipError_t launch_rot_e(const GenArgs& a, int prec, hipStream_t s) {
   const bool narrow = rot_bf16_narrow(a.dpad, tiles, device_cus());
   const bool half =
       EVAL ? rot_few_tiles((a.nrows + 31) / 32, device_cus()) : a.half;
-  // FP32 product of kSplitMinD coordinates and more: split halves, one column
-  // block per wave as long as two would leave waves without any (256: eight
-  // blocks)
-  const bool split = a.D >= kSplitMinD;
-  const bool split_narrow = a.dpad <= kSplitNarrowMaxDpad;
-  // at most one 32-row tile per CU: 16 waves of two rows and one column block
-  if (prec != kPrecBF16 && split &&
-      rot_few_tiles(EVAL ? (a.nrows + 31) / 32
-                         : (long long)a.runs * ((a.NP + 31) / 32),
-                    device_cus())) {
-    if (!EVAL && a.dpad <= kPairMaxDpad)
-      return a.jde ? launch_rot_t<PrecSplitNarrow, 32, 1024, false, true, true>(
-                         a, s)
-                   : launch_rot_t<PrecSplitNarrow, 32, 1024, false, false,
-                                  true>(a, s);
-    return !EVAL && a.jde
-               ? launch_rot_t<PrecSplitNarrow, 32, 1024, EVAL, !EVAL>(a, s)
-               : launch_rot_t<PrecSplitNarrow, 32, 1024, EVAL>(a, s);
-  }
+  if (prec != kPrecBF16 && a.D >= kX3MinD)
+    return !EVAL && a.jde ? launch_x3<EVAL, !EVAL>(a, s)
+                          : launch_x3<EVAL, false>(a, s);
   if (!EVAL && a.jde) {
     // padded width up to 128: trials built two rows per wave instruction
+    if (prec != kPrecBF16)
+      return launch_rot_t<PrecF32, 32, 512, false, true, true>(a, s);
     if (a.dpad <= kPairMaxDpad) {
-      if (prec != kPrecBF16)
-        return split ? launch_rot_t<PrecSplitNarrow, 32, 512, false, true,
-                                    true>(a, s)
-                     : launch_rot_t<PrecF32Narrow, 32, 512, false, true, true>(
-                           a, s);
       if (half)
         return launch_rot_t<PrecBF16, 32, kRotBf16Threads, false, true, true>(
             a, s);
@@ -969,10 +986,6 @@ hipError_t launch_rot_e(const GenArgs& a, int prec, hipStream_t s) {
                     : launch_rot_t<PrecBF16, 64, kRotBf16Threads, false, true,
                                    true>(a, s);
     }
-    if (prec != kPrecBF16)
-      return split_narrow
-                 ? launch_rot_t<PrecSplitNarrow, 32, 512, false, true>(a, s)
-                 : launch_rot_t<PrecSplit, 32, 512, false, true>(a, s);
     if (half)
       return launch_rot_t<PrecBF16, 32, kRotBf16Threads, false, true>(a, s);
     return narrow
@@ -981,13 +994,11 @@ hipError_t launch_rot_e(const GenArgs& a, int prec, hipStream_t s) {
                : launch_rot_t<PrecBF16, 64, kRotBf16Threads, false, true>(a,
                                                                           s);
   }
+  if (prec != kPrecBF16)  // evaluation: unpaired
+    return EVAL ? launch_rot_t<PrecF32, 32, 512, EVAL>(a, s)
+                : launch_rot_t<PrecF32, 32, 512, false, false, true>(a, s);
   // padded width up to 128: trials built two rows per wave instruction
   if (!EVAL && a.dpad <= kPairMaxDpad) {
-    if (prec != kPrecBF16)
-      return split ? launch_rot_t<PrecSplitNarrow, 32, 512, false, false,
-                                  true>(a, s)
-                   : launch_rot_t<PrecF32Narrow, 32, 512, false, false, true>(
-                         a, s);
     if (half)
       return launch_rot_t<PrecBF16, 32, kRotBf16Threads, false, false, true>(
           a, s);
@@ -995,12 +1006,6 @@ hipError_t launch_rot_e(const GenArgs& a, int prec, hipStream_t s) {
                                  false, true>(a, s)
                   : launch_rot_t<PrecBF16, 64, kRotBf16Threads, false, false,
                                  true>(a, s);
-  }
-  if (prec != kPrecBF16) {
-    if (!split)  // evaluation: unpaired
-      return launch_rot_t<PrecF32Narrow, 32, 512, EVAL>(a, s);
-    return split_narrow ? launch_rot_t<PrecSplitNarrow, 32, 512, EVAL>(a, s)
-                        : launch_rot_t<PrecSplit, 32, 512, EVAL>(a, s);
   }
   if (half) return launch_rot_t<PrecBF16, 32, kRotBf16Threads, EVAL>(a, s);
   return narrow ? launch_rot_t<PrecBF16, 64, kRotBf16ThreadsNarrow, EVAL>(a, s)
@@ -1034,14 +1039,20 @@ bool rot_half(int prec, int runs, int NP) {
          rot_few_tiles((long long)runs * ((NP + 31) / 32), device_cus());
 }
 
-// LDS bytes of the rotated kernel's largest tile: BF16 64 rows, FP32 32 rows
-// (independent of the number of threads).
+// LDS bytes of a problem's largest tile, whichever form a launch takes.
 size_t rot_lds_bytes_host(int prec, int dpad, bool jde) {
-  if (prec != kPrecBF16)
-    return jde ? rot_lds_bytes<PrecSplit, 32, true>(dpad)
-               : rot_lds_bytes<PrecSplit, 32>(dpad);
-  return jde ? rot_lds_bytes<PrecBF16, 64, true>(dpad)
-             : rot_lds_bytes<PrecBF16, 64>(dpad);
+  if (prec == kPrecBF16)
+    return jde ? rot_lds_bytes<PrecBF16, 64, true>(dpad)
+               : rot_lds_bytes<PrecBF16, 64>(dpad);
+  const int nblk = dpad / 32;
+  size_t b = x3_lds_bytes(nblk > kX3TallMinBlocks && nblk <= 32 ? 64 : 32, dpad,
+                          jde);
+  if (dpad <= kPairMaxDpad)
+    b = std::max(b, std::max(jde ? rot_lds_bytes<PrecX3, 32, true>(dpad)
+                                 : rot_lds_bytes<PrecX3, 32>(dpad),
+                             jde ? rot_lds_bytes<PrecF32, 32, true>(dpad)
+                                 : rot_lds_bytes<PrecF32, 32>(dpad)));
+  return b;
 }
 
 bool sep_supported(int D) { return (D + 3) / 4 <= 1024; }
@@ -1140,21 +1151,18 @@ hipError_t launch_fill_control(float2* jp, int n, float F, float CR,
 
 hipError_t launch_prep(const float* o, const float* R, int ldr, int D,
                        int dpad, int kind, int prec, float* o_pad, void* rop,
-                       float* rmax, hipStream_t s) {
+                       hipStream_t s) {
   hipLaunchKernelGGL(k_prep_shift, dim3(grid_for(dpad, 256)), dim3(256), 0, s,
-                     o, D, dpad, o_pad, rmax);
+                     o, D, dpad, o_pad);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || kind != kObjRotOsc) return e;
   const size_t total = (size_t)dpad * dpad;
   if (prec == kPrecBF16) {
     hipLaunchKernelGGL(k_prep_rot_bf16, dim3(grid_for(total, 256)), dim3(256),
                        0, s, R, ldr, D, dpad, reinterpret_cast<__bf16*>(rop));
-  } else if (D >= kSplitMinD) {
-    hipLaunchKernelGGL(k_rot_max, dim3(D), dim3(256), 0, s, R, ldr, D, rmax);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_prep_rot_split, dim3(dpad), dim3(256), 0, s, R, ldr,
-                       D, dpad, rmax, reinterpret_cast<half8*>(rop));
+  } else if (D >= kX3MinD) {
+    hipLaunchKernelGGL(k_prep_rot_x3, dim3(grid_for(total, 256)), dim3(256), 0,
+                       s, R, ldr, D, dpad, reinterpret_cast<float*>(rop));
   } else {
     hipLaunchKernelGGL(k_prep_rot_f32, dim3(grid_for(total, 256)), dim3(256),
                        0, s, R, ldr, D, dpad, reinterpret_cast<float*>(rop));

@@ -58,84 +58,75 @@ __device__ __forceinline__ void record_accept(const GenArgs& a, int run, int i,
 //            y = u - o in the GEMM precision, crossover decisions -> bit
 //            planes; padding rows and columns are zero.
 //   phase 2: Z = Y R^T in 32x32 MFMA blocks, wave tile BM rows x one
-//            32-column block per pass (two for FP32 tiles wider than 256),
-//            R fragments prefetched from L2 (BF16: eight K-steps ahead); the
+//            32-column block per pass, R fragments prefetched from L2
+//            (BF16: eight K-steps ahead); the
 //            objective z^2 + sin^2(3z) is summed per row in registers.
 //   phase 3: row totals -> selection -> next generation rows (a rejected row
 //            is rewritten only if the other buffer holds a stale copy),
 //            statistics.
-// Operand precision of the rotation product; kOneBlock: each wave owns one
-// 32-column block per pass (BF16 always; FP32 at padded widths up to 256,
-// where two blocks per wave would leave most waves without a block), else
-// two.
+// Operand precision of the rotation product: LDS element type and the parts
+// an operand is held in.
 struct PrecBF16 {
   using T = __bf16;
   static constexpr int kPad = 8;  // LDS row padding, elements
-  static constexpr bool kOneBlock = true;
-  static constexpr bool kSplit = false;
+  static constexpr int kParts = 1;
 };
-struct PrecF32Narrow {
+// FP32 operands on the FP32 matrix instruction (fewer than kX3MinD coordinates).
+struct PrecF32 {
   using T = float;
   static constexpr int kPad = 4;
-  static constexpr bool kOneBlock = true;
-  static constexpr bool kSplit = false;
+  static constexpr int kParts = 1;
 };
-// FP32 product as three half-precision products: y = yh + yl and R = Rh + Rl
-// (halves of 11 significant bits each, after scaling every row of Y and all
-// of R by a power of two into the half range), z = yh Rh + (yh Rl + yl Rh) with
-// the bracket in an accumulator of its own.
-//   - Why: an FP32 MFMA runs at 1/16 of the half-precision rate and on the
-//     vector FMA units (measured: FP32 MFMA next to FMAs of another wave
-//     takes the sum of both times, half-precision MFMA the larger), so the
-//     FP32 product held the whole tile: 64 K-coordinates cost 2048 clocks a
-//     block there, 384 here.
-//   - Accuracy: the dropped yl Rl and the halves' rounding are 2^-24 of a
-//     term, random in sign, and K / 16 additions round instead of K.
-//     Measured error of z against 64 bits, relative to its rms, FP32 MFMA /
-//     this: 1.9e-7 / 1.1e-7 at K = 112, 3.0e-7 / 1.4e-7 at 256, 5.8e-7 /
-//     2.2e-7 at 1008 (1.1e-7 / 0.9e-7 at 32, but 0.73e-7 / 0.87e-7 at 16).
-//   - A row's scale is that of its own largest |y|, found once the row lies
-//     in LDS (a fixed scale would lose the low halves near the optimum); the
-//     row is split in place, in the space of its FP32 values.
-// Rows of kSplitMinD coordinates and more; below, the FP32 product is as
-// exact.
-struct PrecSplit {
-  using T = float;
-  static constexpr int kPad = 4;
-  static constexpr bool kOneBlock = false;
-  static constexpr bool kSplit = true;
+// FP32 operands on the BF16 matrix instruction: y = yh + ym + yl and R = Rh +
+// Rm + Rl, three BF16 parts of eight significant bits each, which hold all 24
+// bits and the whole exponent range of an FP32 value (the splitting of Henry,
+// Tang & Heinecke, "Leveraging the bfloat16 artificial intelligence datatype
+// for higher-precision computations", ARITH 2019).  Per K-step of 16
+// coordinates one MFMA forms yh Rh and a chain of seven the smaller products,
+// both from zero; their sum is then added to z in FP32.
+//   - Why: an FP32 MFMA runs at 1/16 of the BF16 rate and on the vector FMA
+//     units (measured: FP32 MFMA next to FMAs of another wave takes the sum
+//     of both times, half-precision MFMA the larger): 512 clocks a block and
+//     K-step there, 256 here.  16 x 1024 x 1000: 303 us per generation there,
+//     244 here, of which the eight products take 168 (1.6 PFLOP/s).
+//   - Accuracy: of the nine products only yl Rl (2^-32 of a term) is left out,
+//     products of parts are exact, and z is rounded twice per K-step instead
+//     of 16 times.  The chain is apart because a BF16 MFMA does not round its
+//     sum to nearest: with yh Rh in it a coordinate alone in its row would be
+//     off by up to 1.1 half-ulps, where it is the rounded product so, as a
+//     fused multiply-add's.  Error of f against 64 bits, root mean square in
+//     2^-24, FP32 MFMA / here: dense R 0.95 / 0.81 (32 coordinates), 0.91 /
+//     0.79 (100), 1.04 / 0.92 (256), 1.50 / 1.22 (700), 1.42 / 1.14 (1000);
+//     diagonal R over three decades 0.89 / 0.89; permutations 0.42 / 0.42.
+//     Six products would be faster (215 us) and worse for sparse R (0.94 ->
+//     0.97), two half-precision parts (three products, 123 us) two bits short.
+// Problems of kX3MinD coordinates and more; below, the FP32 instruction's
+// chain is as short.
+struct PrecX3 {
+  using T = __bf16;
+  static constexpr int kPad = 8;
+  static constexpr int kParts = 3;
 };
-struct PrecSplitNarrow : PrecSplit {
-  static constexpr bool kOneBlock = true;
-};
-constexpr int kSplitMinD = 32;            // below: the FP32 MFMA tile
-constexpr int kSplitNarrowMaxDpad = 256;  // one column block per wave
+constexpr int kX3MinD = 32;
+constexpr int kX3TallMinBlocks = 24;  // column blocks; beyond: 64-row tiles
 
-typedef _Float16 half8 __attribute__((ext_vector_type(8)));
-
-// Power-of-two scale of a row whose largest magnitude is m: m * scale lies
-// in [2^14, 2^15) (below 2^15 for m under 2^-112; 1 for rows that are zero
-// or not finite), and its exact inverse.
-struct RowScale {
-  float scale, inv;
-};
-
-__host__ __device__ __forceinline__ RowScale split_scale(float m) {
-  const uint32_t E = __builtin_bit_cast(uint32_t, m) >> 23;  // m >= 0
-  if (m == 0.f || E >= 255u) return {1.f, 1.f};
-  const uint32_t e = E < 15u ? 15u : E;
-  return {__builtin_bit_cast(float, (268u - e) << 23),
-          __builtin_bit_cast(float, (e - 14u) << 23)};
-}
-
-// The two halves of eight scaled values.
-__device__ __forceinline__ void split_halves(const float (&v)[8], float scale,
-                                             half8& h, half8& l) {
+// The three BF16 parts of N values, a pair per conversion.
+template <int N, class V>
+__device__ __forceinline__ void x3_split(const float (&v)[N], V (&p)[3]) {
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+  typedef float floatx2 __attribute__((ext_vector_type(2)));
 #pragma unroll
-  for (int u = 0; u < 8; ++u) {
-    const float x = v[u] * scale;
-    h[u] = (_Float16)x;
-    l[u] = (_Float16)(x - (float)h[u]);
+  for (int u = 0; u < N; u += 2) {
+    float r0 = v[u], r1 = v[u + 1];
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      const bf16x2 h = __builtin_convertvector((floatx2{r0, r1}), bf16x2);
+      p[q][u] = h[0];
+      p[q][u + 1] = h[1];
+      const uint32_t w = __builtin_bit_cast(uint32_t, h);
+      r0 -= __builtin_bit_cast(float, w << 16);
+      r1 -= __builtin_bit_cast(float, w & 0xFFFF0000u);
+    }
   }
 }
 
@@ -145,24 +136,41 @@ constexpr int kRotSlots = 16;
 template <class P, int BM, bool JDE = false>
 __host__ __device__ constexpr size_t rot_lds_bytes(int dpad) {
   const int tq = (dpad / 4 + 63) / 64;
-  return (size_t)BM * (dpad + P::kPad) * sizeof(typename P::T)  // A tile
+  return (size_t)BM * (P::kParts * dpad + P::kPad) * sizeof(typename P::T)  // A
          + (size_t)BM * tq * 4 * sizeof(unsigned long long)     // planes
          + (size_t)BM * 4 * sizeof(int)                         // donors
          + (size_t)kRotSlots * BM * sizeof(float)               // slot sums
-         + (P::kSplit ? (size_t)BM * sizeof(float) : 0)         // row scales
          + (JDE ? (size_t)BM * sizeof(Control) : 0);            // F', CR'
 }
 
-// Position of coordinate k inside an LDS row.  BF16 and split: natural
-// order.  FP32: within each group of 8, k = 2s + h is stored at 4h + s so that one lane's
+// Coordinates j0 .. j0 + 3 of an LDS row.  BF16: natural order.  Three parts:
+// each group of 8 coordinates as its 8 high, 8 middle and 8 low parts.  FP32:
+// within each group of 8, k = 2s + h is stored at 4h + s so that one lane's
 // four K-steps of the 32x32x2 MFMA are one 16-byte read.
 template <class P>
-__device__ __forceinline__ int lds_col(int k) {
-  if constexpr (sizeof(typename P::T) == 2 || P::kSplit) {
-    return k;
+__device__ __forceinline__ void put_quad(typename P::T* arow, int j0,
+                                         float4 y) {
+  if constexpr (P::kParts == 3) {
+    const float v[4] = {y.x, y.y, y.z, y.w};
+    bf16x4 p[3];
+    x3_split(v, p);
+    bf16x4* d = reinterpret_cast<bf16x4*>(arow + 3 * (j0 & ~7) + (j0 & 7));
+    d[0] = p[0];
+    d[2] = p[1];
+    d[4] = p[2];
+  } else if constexpr (sizeof(typename P::T) == 2) {
+    bf16x4 yb;
+    yb[0] = (__bf16)y.x;
+    yb[1] = (__bf16)y.y;
+    yb[2] = (__bf16)y.z;
+    yb[3] = (__bf16)y.w;
+    *reinterpret_cast<bf16x4*>(arow + j0) = yb;
   } else {
-    const int g = k & ~7, r = k & 7;
-    return g + (r & 1) * 4 + (r >> 1);
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+      const int k = j0 + b;
+      arow[(k & ~7) + (k & 1) * 4 + ((k & 7) >> 1)] = get(y, b);
+    }
   }
 }
 
@@ -210,10 +218,8 @@ constexpr int kRotBf16NarrowMaxDpad = 512;
 // CUs, which would be idle otherwise.  Per generation, 64 / 32 rows: 1 x 250 x
 // 100 6.1 / 5.0 us, 30 x 256 x 100 6.4 / 5.1, 16 x 500 x 333 16.6 / 11.9,
 // 1 x 1024 x 1000 40.5 / 32.1, 8 x 1024 x 1000 (every CU) 41.4 / 36.5.  With more
-// tiles than CUs the 64-row tile, which streams R once per 64 rows.  Split FP32
-// tiles have 32 rows anyway; there they get 16 waves instead of 8: 1 x 1024 x
-// 1000 59.5 -> 55.1 us, 10 x 500 x 333 21.0 -> 18.1, eval of 5000 x 700 rows 46.0
-// -> 44.7.  Rows' sums are formed alike, so the result does not depend on it.
+// tiles than CUs the 64-row tile, which streams R once per 64 rows.  Rows' sums
+// are formed alike, so the result does not depend on it.
 __host__ __device__ constexpr bool rot_few_tiles(long long tiles32, int cus) {
   return tiles32 <= cus;
 }
@@ -234,33 +240,6 @@ __device__ __forceinline__ void interleave_step() {
     __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
   }
   __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);  // VMEM read
-  __builtin_amdgcn_sched_barrier(0);
-}
-
-// The same for a split step: each MFMA is followed by one read, the next
-// step's two A reads first, then the fragments whose last use is done.
-template <int NBW>
-__device__ __forceinline__ void interleave_split() {
-  if constexpr (NBW == 2) {
-#pragma unroll
-    for (int k = 0; k < 2; ++k) {
-      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // MFMA
-      __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);  // DS read
-    }
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // MFMA
-      __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);  // VMEM read
-    }
-  } else {
-    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-    __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-#pragma unroll
-    for (int k = 0; k < 2; ++k) {
-      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-      __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
-    }
-  }
   __builtin_amdgcn_sched_barrier(0);
 }
 
@@ -380,21 +359,7 @@ __device__ __forceinline__ void build_chunk(const GenArgs& a, const RotRows& c,
         for (int b = 0; b < 4; ++b)
           set(y, b, j0 + b < a.D ? get(y, b) : 0.f);
       }
-      if (j0 < a.dpad) {
-        if constexpr (sizeof(T) == 2) {
-          bf16x4 yb;
-          yb[0] = (__bf16)y.x;
-          yb[1] = (__bf16)y.y;
-          yb[2] = (__bf16)y.z;
-          yb[3] = (__bf16)y.w;
-          *reinterpret_cast<bf16x4*>(arow + j0) = yb;
-        } else if constexpr (P::kSplit) {
-          st4(arow + j0, y);
-        } else {
-#pragma unroll
-          for (int b = 0; b < 4; ++b) arow[lds_col<P>(j0 + b)] = get(y, b);
-        }
-      }
+      if (j0 < a.dpad) put_quad<P>(arow, j0, y);
     }
   }
 }
@@ -567,8 +532,84 @@ __device__ __forceinline__ void select_rows(const GenArgs& a, const RotRows& c,
   }
 }
 
-// Widest padded row of a split tile (its LDS limit).
-constexpr int kMaxSplitDpad = 1152;
+// z += Y R^T over `steps` K-steps for NB column blocks of R and MB row blocks
+// (three-part operands).  ar: the lane's first fragment of the A rows (row l %
+// 32, coordinates 8 (l / 32) on), row32 elements to the next row block.  rb:
+// the first block's fragments, FP32, [K-step][half][64 lanes] of four
+// coordinates each, bstep float4s to the next block.  R stays FP32 in memory
+// (four bytes an element to stream instead of six) and is split by the one
+// wave of the tile that multiplies by it.
+// A block's R registers are loaded for the next step once all of them are
+// split, without a branch and in the loop's order, so that the loads in
+// flight can be counted.  Only the first `mine` blocks (NB or NB - 1) are
+// multiplied; the loads of a missing last one repeat the one
+// before it.
+// (pin: the compiler otherwise puts the parts off until after the loads and
+// the sums until the end of the step, and moves or spills what they hold.)
+template <class V>
+__device__ __forceinline__ void pin(V& v) {
+  asm volatile("" : "+v"(v));
+}
+
+template <int MB, int NB>
+__device__ __forceinline__ void x3_product(floatx16 (&acc)[NB][MB],
+                                           const __bf16* ar, int row32,
+                                           const float4* rb, size_t bstep,
+                                           int steps, int lane, int mine) {
+  // scalar row addresses, the lane's part in one register
+  const uint32_t lofs = (uint32_t)lane * 16u;
+  auto frag = [&](const float4* p) {
+    return *reinterpret_cast<const float4*>(reinterpret_cast<const char*>(p) +
+                                            lofs);
+  };
+  const size_t last = (size_t)(mine - 1) * bstep;
+  float4 r[NB][2];
+#pragma unroll
+  for (int n = 0; n < NB; ++n)
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+      r[n][p] = frag(rb + (n < mine ? n * bstep : last) + 64 * p);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  for (int s = 0; s < steps; ++s) {
+    bf16x8 x[MB][3];
+#pragma unroll
+    for (int m = 0; m < MB; ++m)
+#pragma unroll
+      for (int p = 0; p < 3; ++p)
+        x[m][p] =
+            *reinterpret_cast<const bf16x8*>(ar + m * row32 + 48 * s + 8 * p);
+    const float4* rn = rb + (size_t)(s + 1 < steps ? s + 1 : s) * 128;
+#pragma unroll
+    for (int n = 0; n < NB; ++n) {
+      const float v[8] = {r[n][0].x, r[n][0].y, r[n][0].z, r[n][0].w,
+                          r[n][1].x, r[n][1].y, r[n][1].z, r[n][1].w};
+      bf16x8 b[3];
+      x3_split(v, b);
+#pragma unroll
+      for (int p = 0; p < 3; ++p) pin(b[p]);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int p = 0; p < 2; ++p)
+        r[n][p] = frag(rn + (n < mine ? n * bstep : last) + 64 * p);
+      if (NB > 1 && n == NB - 1 && n >= mine) break;
+      constexpr int kA[7] = {1, 2, 2, 0, 1, 1, 0};
+      constexpr int kB[7] = {2, 1, 0, 2, 1, 0, 1};
+#pragma unroll
+      for (int m = 0; m < MB; ++m) {
+        floatx16 t = {};
+#pragma unroll
+        for (int q = 0; q < 7; ++q)
+          t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[m][kA[q]], b[kB[q]], t,
+                                                      0, 0, 0);
+        const floatx16 h = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+            x[m][0], b[0], floatx16{}, 0, 0, 0);
+        acc[n][m] += h + t;
+        pin(acc[n][m]);
+      }
+    }
+  }
+}
 
 // One tile: rows row0 .. row0 + nvalid - 1 of run `run` (EVAL: of the
 // flattened row range).  Ends with every LDS access of the tile complete
@@ -583,24 +624,19 @@ __device__ __forceinline__ void rot_tile(const GenArgs& a, int run, int row0,
   constexpr int MB = BM / 32;
   constexpr int kRotThreads = NT;
   constexpr int kRotWaves = NT / 64;
-  // BF16 tiles: one column block per wave and pass, four producer rows per
-  // step (128 registers); FP32 tiles: one or two column blocks (P),
-  // eight rows
-  constexpr int NBW = P::kOneBlock ? 1 : 2;
+  static_assert(P::kParts == 1 || PAIR, "three parts: rot_tile_x3");
   static_assert(MB == 1 || (MB == 2 && sizeof(T) == 2), "tile shape");
   extern __shared__ __align__(16) char smem[];
   const int dpad = a.dpad;
-  const int stride = dpad + P::kPad;
+  const int stride = P::kParts * dpad + P::kPad;
   const int tq = (dpad / 4 + 63) / 64;
   T* At = reinterpret_cast<T*>(smem);
   unsigned long long* planes = reinterpret_cast<unsigned long long*>(
       smem + (size_t)BM * stride * sizeof(T));
   int* donors = reinterpret_cast<int*>(planes + (size_t)BM * tq * 4);
   float* fpart = reinterpret_cast<float*>(donors + BM * 4);
-  // split tiles: inverse scale of every row
-  float* rinv = fpart + kRotSlots * BM;
   // jDE: the F' and CR' of every row of the tile
-  Control* ctl = reinterpret_cast<Control*>(rinv + (P::kSplit ? BM : 0));
+  Control* ctl = reinterpret_cast<Control*>(fpart + kRotSlots * BM);
 
   const int wave = (int)threadIdx.x / 64, lane = (int)threadIdx.x % 64;
   const uint32_t rng_run = a.run_base + (uint32_t)run;
@@ -629,7 +665,7 @@ __device__ __forceinline__ void rot_tile(const GenArgs& a, int run, int row0,
                              kRotWaves;
        rl < BM; rl += kRotWaves) {
     T* arow = At + (size_t)rl * stride;
-    for (int k = lane; k < dpad; k += 64) arow[k] = (T)0.0f;
+    for (int k = lane; k < P::kParts * dpad; k += 64) arow[k] = (T)0.0f;
   }
   // PAIR: each wave keeps its rows' targets and trials (lane 32 h + q: quad
   // q of the h-th row of a pair), their values and stale flags in registers
@@ -698,45 +734,7 @@ __device__ __forceinline__ void rot_tile(const GenArgs& a, int run, int row0,
           set(y, b, (j0 + b < a.D) ? u - get(ov, b) : 0.f);
         }
         T* arow = At + (size_t)rl * stride;
-        if (live && j0 < dpad) {
-          if constexpr (sizeof(T) == 2) {
-            bf16x4 yb;
-            yb[0] = (__bf16)y.x;
-            yb[1] = (__bf16)y.y;
-            yb[2] = (__bf16)y.z;
-            yb[3] = (__bf16)y.w;
-            *reinterpret_cast<bf16x4*>(arow + j0) = yb;
-          } else if constexpr (!P::kSplit) {
-#pragma unroll
-            for (int b = 0; b < 4; ++b) arow[lds_col<P>(j0 + b)] = get(y, b);
-          }
-        }
-        if constexpr (P::kSplit) {
-          // the row's scale from its half-wave, then the quad's halves
-          float m = fmaxf(fmaxf(fabsf(y.x), fabsf(y.y)),
-                          fmaxf(fabsf(y.z), fabsf(y.w)));
-          m = fmaxf(m, lane_xor<16>(m));
-          m = fmaxf(m, lane_xor<8>(m));
-          m = fmaxf(m, lane_xor<4>(m));
-          m = fmaxf(m, lane_xor<2>(m));
-          m = fmaxf(m, lane_xor<1>(m));
-          const RowScale rs = split_scale(m);
-          typedef _Float16 half4 __attribute__((ext_vector_type(4)));
-          half4 h, l;
-#pragma unroll
-          for (int b = 0; b < 4; ++b) {
-            const float x = get(y, b) * rs.scale;
-            h[b] = (_Float16)x;
-            l[b] = (_Float16)(x - (float)h[b]);
-          }
-          if (live) {
-            if (ql == 0) rinv[rl] = rs.inv;
-            half4* p8 = reinterpret_cast<half4*>(
-                reinterpret_cast<float*>(arow) + (j0 & ~7));
-            p8[ql & 1] = h;
-            p8[2 + (ql & 1)] = l;
-          }
-        }
+        if (live && j0 < dpad) put_quad<P>(arow, j0, y);
       }
     }
   } else
@@ -760,50 +758,6 @@ __device__ __forceinline__ void rot_tile(const GenArgs& a, int run, int row0,
                                     : (BM / kRotWaves < 8 ? BM / kRotWaves : 8),
                   kRotWaves, EVAL, JDE>(a, c, t, At);
   }
-  if constexpr (P::kSplit && PAIR) {
-    // rows past the tile's last are zero already (as halves too)
-    if ((int)threadIdx.x >= nvalid && (int)threadIdx.x < BM)
-      rinv[threadIdx.x] = 1.f;
-  } else if constexpr (P::kSplit) {
-    // each wave splits the rows it built: eight coordinates per lane and
-    // step, read as FP32, written back as eight high and eight low halves
-    __builtin_amdgcn_wave_barrier();
-    constexpr int kSteps = (kMaxSplitDpad / 8 + 63) / 64;
-#pragma unroll
-    for (int k = 0; k < BM / kRotWaves; ++k) {
-      const int rl = wave + kRotWaves * k;
-      float* arow = reinterpret_cast<float*>(At) + (size_t)rl * stride;
-      float v[kSteps][8];
-      float m = 0.f;
-#pragma unroll
-      for (int t = 0; t < kSteps; ++t) {
-        const int g8 = lane + 64 * t;
-        if (64 * 8 * t >= dpad) break;
-        const float4 p = ld4(arow + 8 * min(g8, dpad / 8 - 1));
-        const float4 q = ld4(arow + 8 * min(g8, dpad / 8 - 1) + 4);
-#pragma unroll
-        for (int b = 0; b < 4; ++b) {
-          v[t][b] = get(p, b);
-          v[t][4 + b] = get(q, b);
-          m = fmaxf(m, fmaxf(fabsf(get(p, b)), fabsf(get(q, b))));
-        }
-      }
-#pragma unroll
-      for (int x = 32; x >= 1; x >>= 1) m = fmaxf(m, __shfl_xor(m, x, 64));
-      const RowScale rs = split_scale(m);
-      if (lane == 0) rinv[rl] = rs.inv;
-#pragma unroll
-      for (int t = 0; t < kSteps; ++t) {
-        const int g8 = lane + 64 * t;
-        if (8 * g8 < dpad) {
-          half8 h, l;
-          split_halves(v[t], rs.scale, h, l);
-          *reinterpret_cast<half8*>(arow + 8 * g8) = h;
-          *reinterpret_cast<half8*>(arow + 8 * g8 + 4) = l;
-        }
-      }
-    }
-  }
   __syncthreads();
 
   SelectRow sr{0, false, 0.f, false};
@@ -820,20 +774,25 @@ __device__ __forceinline__ void rot_tile(const GenArgs& a, int run, int row0,
   // blocks s, s + 16, s + 32, ... in increasing order, so the result does
   // not depend on how blocks are dealt to waves (the number of threads).
   // A wave's blocks fall into SPW slots, its pass p into sacc[p % SPW].
-  constexpr int SPW = kRotSlots / (kRotWaves * NBW) > 1
-                          ? kRotSlots / (kRotWaves * NBW)
-                          : 1;
-  static_assert(kRotSlots % (kRotWaves * NBW) == 0 ||
-                    (kRotWaves * NBW) % kRotSlots == 0,
-                "slots and waves");
+  constexpr int SPW = kRotSlots / kRotWaves > 1 ? kRotSlots / kRotWaves : 1;
+  static_assert(kRotSlots % kRotWaves == 0, "slots and waves");
   float sacc[SPW];
 #pragma unroll
   for (int q = 0; q < SPW; ++q) sacc[q] = 0.f;
   int pass = 0;
-  for (int nb0 = wave * NBW; nb0 < nblk;
-       nb0 += kRotWaves * NBW, ++pass) {
+  for (int nb0 = wave; nb0 < nblk; nb0 += kRotWaves, ++pass) {
     floatx16 c00 = {}, c01 = {}, c10 = {};
-    if constexpr (sizeof(T) == 2) {
+    if constexpr (P::kParts == 3) {
+      floatx16 acc[1][1] = {{c00}};
+      const int kbn = dpad / 16;
+      x3_product<1, 1>(acc,
+                       At + (size_t)(lane % 32) * stride + 24 * (lane / 32), 0,
+                       reinterpret_cast<const float4*>(a.rop) +
+                           (size_t)__builtin_amdgcn_readfirstlane(nb0) * kbn *
+                               128,
+                       0, (a.D + 15) / 16, lane, 1);
+      c00 = acc[0][0];
+    } else if constexpr (sizeof(T) == 2) {
       // R as [nblk][dpad/16][64 lanes][8]: one 16-byte load per lane per
       // block and K-step; dpad / 16 is a multiple of 8.
       // Software pipeline at K-step granularity: the A fragments of step
@@ -876,84 +835,6 @@ __device__ __forceinline__ void rot_tile(const GenArgs& a, int run, int row0,
           interleave_step<MB>();
         }
       }
-    } else if constexpr (P::kSplit) {
-      // R as [nblk][dpad/16][half][64 lanes][8].  A ring of kRing K-steps of fragments: a step's
-      // registers are loaded for kRing steps later once its MFMAs are
-      // issued.  The stream from L2 (4 bytes per element of R per 32 rows)
-      // bounds the loop: 2 KB per block and step against 96 clocks of MFMA.
-      const half8* rop =
-          reinterpret_cast<const half8*>(a.rop) +
-          (size_t)__builtin_amdgcn_readfirstlane(nb0) * (dpad / 16) * 128;
-      const int kbn = dpad / 16;  // a multiple of 8
-      // (half the ring within 128 registers: two tiles a CU, or 16 waves)
-      constexpr int kRing = NBW == 2 || PAIR || NT == 1024 ? 4 : 8;
-      const char* ar = reinterpret_cast<const char*>(At) +
-                       (size_t)(lane % 32) * stride * 4 + 32 * (lane / 32);
-      half8 bh[kRing][NBW], bl[kRing][NBW], ah[2], al[2];
-      floatx16 x00 = {}, x01 = {};
-#pragma unroll
-      for (int u = 0; u < kRing; ++u) {
-        // in the loop's order, or the loop's head waits for all of them
-#pragma unroll
-        for (int n = 0; n < NBW; ++n) {
-          bh[u][n] = rop[(size_t)n * kbn * 128 + u * 128 + lane];
-          __builtin_amdgcn_sched_barrier(0);
-        }
-#pragma unroll
-        for (int n = 0; n < NBW; ++n) {
-          bl[u][n] = rop[(size_t)n * kbn * 128 + u * 128 + 64 + lane];
-          __builtin_amdgcn_sched_barrier(0);
-        }
-      }
-      ah[0] = *reinterpret_cast<const half8*>(ar);
-      al[0] = *reinterpret_cast<const half8*>(ar + 16);
-      for (int kb = 0; kb < kbn; kb += kRing) {
-        const int kn = kb + kRing < kbn ? kb + kRing : kb;
-#pragma unroll
-        for (int u = 0; u < kRing; ++u) {
-          const int cur = u & 1, nxt = cur ^ 1;
-          const int ka = u < kRing - 1 ? kb + u + 1 : kn;
-          ah[nxt] = *reinterpret_cast<const half8*>(ar + ka * 64);
-          al[nxt] = *reinterpret_cast<const half8*>(ar + ka * 64 + 16);
-          x00 = __builtin_amdgcn_mfma_f32_32x32x16_f16(al[cur], bh[u][0], x00,
-                                                       0, 0, 0);
-          if constexpr (NBW == 2)
-            x01 = __builtin_amdgcn_mfma_f32_32x32x16_f16(al[cur], bh[u][NBW - 1],
-                                                         x01, 0, 0, 0);
-          c00 = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah[cur], bh[u][0], c00,
-                                                       0, 0, 0);
-          if constexpr (NBW == 2)
-            c01 = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah[cur], bh[u][NBW - 1],
-                                                         c01, 0, 0, 0);
-          x00 = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah[cur], bl[u][0], x00,
-                                                       0, 0, 0);
-          if constexpr (NBW == 2)
-            x01 = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah[cur], bl[u][NBW - 1],
-                                                         x01, 0, 0, 0);
-          // the step's fragments for kRing steps later, in order of their
-          // last use
-          const half8* r = rop + (size_t)kn * 128;
-          bh[u][0] = r[u * 128 + lane];
-          if constexpr (NBW == 2)
-            bh[u][NBW - 1] = r[(size_t)kbn * 128 + u * 128 + lane];
-          bl[u][0] = r[u * 128 + 64 + lane];
-          if constexpr (NBW == 2)
-            bl[u][NBW - 1] = r[(size_t)kbn * 128 + u * 128 + 64 + lane];
-          interleave_split<NBW>();
-        }
-      }
-      const float rs0 = split_scale(*a.rmax).inv;
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const float4 rs = ld4(rinv + 8 * q + 4 * (lane / 32));
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          c00[4 * q + r] = (c00[4 * q + r] + x00[4 * q + r]) * get(rs, r) * rs0;
-          if constexpr (NBW == 2)
-            c01[4 * q + r] =
-                (c01[4 * q + r] + x01[4 * q + r]) * get(rs, r) * rs0;
-        }
-      }
     } else {
       // R as [nblk][dpad/8][64 lanes][4]: one float4 = four K-steps; dpad / 8
       // is a multiple of 2.  Even and odd four-step groups accumulate apart
@@ -981,37 +862,29 @@ __device__ __forceinline__ void rot_tile(const GenArgs& a, int run, int row0,
     // result does not depend on how blocks are dealt to waves (the number
     // of threads).  32x32 accumulator layout: register r of lane l holds
     // row 8 (r / 4) + 4 (l / 32) + r % 4 and column l % 32 of the block.
-    // Each lane has 32 values (BF16: rows of row blocks 0 and 1; FP32: one
-    // row block, column blocks nb0 and nb0 + 1); a reduce-scatter butterfly
-    // over the 32 lanes of each half-wave leaves lane l with the total of
-    // value l % 32 (31 exchanges instead of 5 per value).
-    constexpr bool kFastSin = sizeof(T) == 2;
+    // Each lane has 16 values of one row block, or 32 of two; a
+    // reduce-scatter butterfly over the 32 lanes of each half-wave leaves
+    // lane l with the total of value l % 32 (31 exchanges instead of 5 per
+    // value).
+    constexpr bool kFastSin = sizeof(T) == 2 && P::kParts == 1;
+    constexpr bool kHi = MB == 2;
     const floatx16& lo = c00;
     const floatx16& hi = MB == 2 ? c10 : c01;
-    // FP32 one-block tiles: values 16-31 (a second block) are empty
-    constexpr bool kHi = MB == 2 || NBW == 2;
     const float total = osc_rows<kFastSin, kHi>(lo, hi, lane);
 #pragma unroll
     for (int q = 0; q < SPW; ++q)
       if (pass % SPW == q) sacc[q] += total;
   }
-  // lane l holds value l % 32: BF16 row (l % 32 / 16) * 32 + rin of the
-  // wave's blocks; FP32 row rin of block nb0 + (l % 32) / 16 (one-block
-  // tiles: block nb0 in lanes with l % 32 < 16)
+  // lane l holds value l % 32: row (l % 32 / 16) * 32 + rin of the wave's
+  // blocks (one row block: the lanes with l % 32 < 16)
   {
     const int idx = lane % 32, hb = idx / 16, r = idx % 16;
     const int rin = 8 * (r / 4) + 4 * (lane / 32) + (r % 4);
 #pragma unroll
     for (int q = 0; q < SPW; ++q) {
-      const int b0 = wave * NBW + q * kRotWaves * NBW;  // first block of q
-      if constexpr (MB == 2) {
-        if (b0 < kRotSlots) fpart[(size_t)b0 * BM + hb * 32 + rin] = sacc[q];
-      } else if constexpr (NBW == 1) {
-        if (hb == 0 && b0 < kRotSlots) fpart[(size_t)b0 * BM + rin] = sacc[q];
-      } else {
-        if (b0 + hb < kRotSlots)
-          fpart[(size_t)(b0 + hb) * BM + rin] = sacc[q];
-      }
+      const int b0 = wave + q * kRotWaves;  // first block of q
+      if ((MB == 2 || hb == 0) && b0 < kRotSlots)
+        fpart[(size_t)b0 * BM + hb * 32 + rin] = sacc[q];
     }
   }
   __syncthreads();
@@ -1056,6 +929,106 @@ __device__ __forceinline__ void rot_tile(const GenArgs& a, int run, int row0,
   }
   const RotRows c{base, donors, ctl, planes, rng_run, row0, nvalid, stride, tq};
   select_rows<BM, kRotWaves, EVAL, JDE>(a, c, run, fpart, sr);
+}
+
+// ---------------------------------------------------------------------------
+// FP32 tile of three-part operands for rows of more than 128 coordinates, and
+// for evaluations: 32 MB rows, NW waves.  The A tile holds kX3Part coordinates
+// at a time (six bytes each: whole rows of 1000 would not fit); the next part
+// is built when the product of the last is done, and every wave keeps z of its
+// column blocks wave, wave + NW, ... (at most NB) over the parts.  Every form
+// adds the same numbers in the same order, so a value does not depend on which
+// one computed it.
+constexpr int kX3Part = 256;
+
+__host__ __device__ constexpr size_t x3_lds_bytes(int bm, int dpad, bool jde) {
+  const int tq = (dpad / 4 + 63) / 64;
+  return (size_t)bm * (3 * kX3Part + PrecX3::kPad) * sizeof(__bf16)  // A tile
+         + (size_t)bm * tq * 4 * sizeof(unsigned long long)          // planes
+         + (size_t)bm * 4 * sizeof(int)                              // donors
+         + (size_t)kRotSlots * bm * sizeof(float)                    // slot sums
+         + (jde ? (size_t)bm * sizeof(Control) : 0);                 // F', CR'
+}
+
+template <int MB, int NB, int NW, bool EVAL, bool JDE>
+__device__ __forceinline__ void rot_tile_x3(const GenArgs& a, int run, int row0,
+                                            int nvalid) {
+  constexpr int BM = 32 * MB;
+  static_assert(NW == 8 || NW == 16, "slots and waves");
+  extern __shared__ __align__(16) char smem[];
+  const int stride = 3 * kX3Part + PrecX3::kPad;
+  const int tq = (a.dpad / 4 + 63) / 64;
+  __bf16* At = reinterpret_cast<__bf16*>(smem);
+  unsigned long long* planes =
+      reinterpret_cast<unsigned long long*>(At + (size_t)BM * stride);
+  int* donors = reinterpret_cast<int*>(planes + (size_t)BM * tq * 4);
+  float* fpart = reinterpret_cast<float*>(donors + BM * 4);
+  Control* ctl = reinterpret_cast<Control*>(fpart + kRotSlots * BM);
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / 64);
+  const int lane = (int)threadIdx.x % 64;
+  const uint32_t rng_run = a.run_base + (uint32_t)run;
+  const RotRows c{a.pop_cur + (EVAL ? 0 : (size_t)run * a.NP * a.ldx),
+                  donors, ctl, planes, rng_run, row0, nvalid, stride, tq};
+  if (!EVAL) {
+    if ((int)threadIdx.x < nvalid) {
+      const int rl = (int)threadIdx.x;
+      const Donors d = pick_donors(rng_run, a.gen, row0 + rl, a.NP, a.D,
+                                   a.key_lo, a.key_hi);
+      donors[rl * 4 + 0] = d.r1;
+      donors[rl * 4 + 1] = d.r2;
+      donors[rl * 4 + 2] = d.r3;
+      donors[rl * 4 + 3] = d.jrand;
+      if constexpr (JDE) {
+        const float2 p = a.jp_cur[(size_t)run * a.NP + row0 + rl];
+        ctl[rl] = jde_control(rng_run, a.gen, row0 + rl, a.key_lo, a.key_hi,
+                              a.jF_lo, a.jF_span, a.jtau_F, a.jtau_CR,
+                              Control{p.x, p.y});
+      }
+    }
+    __syncthreads();
+  }
+  const SelectRow sr = select_row<NW, EVAL>(a, run, row0, nvalid);
+  // column blocks past D hold zeros: left out, like the K-steps past D
+  const int nblk = (a.D + 31) / 32, kbn = a.dpad / 16;
+  const int mine = wave < nblk ? (nblk - 1 - wave) / NW + 1 : 0;
+  floatx16 acc[NB][MB];
+#pragma unroll
+  for (int n = 0; n < NB; ++n)
+#pragma unroll
+    for (int m = 0; m < MB; ++m) acc[n][m] = floatx16{};
+  const float4* rb = reinterpret_cast<const float4*>(a.rop) +
+                     (size_t)(wave < nblk ? wave : 0) * kbn * 128;
+  const size_t bstep = (size_t)NW * kbn * 128;
+  const __bf16* ar = At + (size_t)(lane % 32) * stride + 24 * (lane / 32);
+  for (int t = 0; t < tq; ++t) {
+    if (t > 0) __syncthreads();  // the last part's products are done
+    // rows past the tile's last keep what the LDS held: their sums are unused
+    build_chunk<PrecX3, (MB == 2 ? 2 : BM / NW), NW, EVAL, JDE>(
+        a, c, t, At - 3 * kX3Part * t);
+    __syncthreads();
+    const int steps = (min(kX3Part, a.D - kX3Part * t) + 15) / 16;
+    const float4* rt = rb + (size_t)t * (kX3Part / 16) * 128;
+    if (mine > 0)
+      x3_product<MB, NB>(acc, ar, 32 * stride, rt, bstep, steps, lane, mine);
+  }
+  // row sums of the objective: block b goes to slot b mod 16, a slot's blocks
+  // in order
+  float sacc[2] = {0.f, 0.f};
+#pragma unroll
+  for (int n = 0; n < NB; ++n) {
+    const float total = osc_rows<false, MB == 2>(acc[n][0], acc[n][MB - 1], lane);
+    if (n < mine) sacc[NW == 8 ? n & 1 : 0] += total;
+  }
+  {
+    const int idx = lane % 32, hb = idx / 16, r = idx % 16;
+    const int rin = 8 * (r / 4) + 4 * (lane / 32) + (r % 4);
+    if (MB == 2 || hb == 0) {
+      fpart[(size_t)wave * BM + hb * 32 + rin] = sacc[0];
+      if (NW == 8) fpart[(size_t)(wave + 8) * BM + hb * 32 + rin] = sacc[1];
+    }
+  }
+  __syncthreads();
+  select_rows<BM, NW, EVAL, JDE>(a, c, run, fpart, sr);
 }
 
 }  // namespace de

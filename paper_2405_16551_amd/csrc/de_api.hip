@@ -298,7 +298,8 @@ float f_of_key(unsigned long long key) {
 constexpr int64_t kResidentChunk = 1024;
 
 // Staggered run groups, for rotated-objective problems that fill the GPU
-// (at least as many tiles as compute units) with two or more runs.  Every
+// (at least as many tiles as compute units) with two or more runs (which of
+// them: rot_group_min_gens).  Every
 // CU of one launch goes through the same phases at the same time: the
 // trial build (Philox draws, gathers of population rows from HBM), then
 // the rotation product (MFMA, R fragments from L2), then selection.  Here
@@ -354,28 +355,14 @@ de_status wait_post(const unsigned long long* slot, uint32_t seq,
   }
 }
 
-// Fewest generations per call that take the split: the second group's
-// offset leaves half a generation of it after the first group's last
-// kernel.  16 x 1024 x 1000, BF16, one handle, split / plain: 20 generations
-// 1115 / 1108 us, 400 generations late in a run 51.0 / 55.1 us each; several
-// handles in turn share the hardware queues, and the split of 20
-// generations then costs 1354 us.
-constexpr int64_t kStaggerMinGens = 32;
-
-// Padded widths that take the split (BF16 product): at 700 coordinates both
-// forms take 37.5 us per generation, and the FP32 product, whose tiles
-// outnumber the compute units two to one, is slower split (145 / 140 us).
-constexpr int kStaggerMinDpad = 1024;
-
-// Problems that take the split: rotated objective, BF16 product of wide
-// rows, two or more runs, at least one 64-row tile per compute unit.  Their
-// handles create the two streams at initialisation.
-bool stagger_shape(const de_state* s) {
-  if (s->kind != de::kObjRotOsc || s->prec != de::kPrecBF16 ||
-      s->dpad < kStaggerMinDpad || s->p.runs < 2 || !stagger_enabled())
-    return false;
-  const long long tiles = (long long)s->p.runs * ((s->p.NP + 63) / 64);
-  return tiles >= de::device_cus();
+// Fewest generations of a call that takes the split (0: none does).  Handles
+// whose calls may take it create the two streams at initialisation.  Several
+// handles in turn share the hardware queues, which cost calls of three handles
+// of 16 x 1024 x 1000 between nothing and a fifth (54.6 -> 52.3 us per generation
+// in one process, 53 -> 63 in another).
+int64_t stagger_min_gens(const de_state* s) {
+  if (s->kind != de::kObjRotOsc || !stagger_enabled()) return 0;
+  return de::rot_group_min_gens(s->prec, s->p.D, s->dpad, s->p.runs, s->p.NP);
 }
 
 // A stream being captured into a graph gets the plain launches (event
@@ -478,7 +465,7 @@ de_status run_plain(de_state* s, int64_t n, hipStream_t st);
 de_status run_generations(de_state* s, int64_t n, hipStream_t st) {
   if (n > 0 && s->grp[0] && !s->grp_failed && !capturing(st)) {
     read_gen_time(s);
-    if (n >= kStaggerMinGens) return run_staggered(s, n, st);
+    if (n >= stagger_min_gens(s)) return run_staggered(s, n, st);
     // a short call: one launch per generation, timed for later offsets
     const bool time_it = s->grp_timed == 0;
     de_status rc = time_it ? FROM_HIP(hipEventRecord(s->grp_t0, st)) : DE_OK;
@@ -668,7 +655,7 @@ de_status init_common(const de_params* params, const de_objective* objective,
   }
   // the run-group streams of problems that take the split (a failure
   // leaves the handle on plain launches)
-  if (stagger_shape(s)) (void)stagger_setup(s);
+  if (stagger_min_gens(s) > 0) (void)stagger_setup(s);
   {
     std::lock_guard<std::mutex> lk(g_live_mu);
     g_live.insert(s);

@@ -53,6 +53,8 @@ hipError_t set_max_dynamic_lds(const void* fn);
 
 // Whether a problem's BF16 product takes the 32-row tile.
 bool rot_half(int prec, int runs, int NP);
+// Fewest generations of a call that runs as two run groups; 0: never.
+int rot_group_min_gens(int prec, int D, int dpad, int runs, int NP);
 size_t rot_lds_bytes_host(int prec, int dpad, bool jde = false);
 bool sep_supported(int D);
 

@@ -1034,6 +1034,44 @@ int device_cus() {
   return n;
 }
 
+// A generation in two launches of half the runs, one offset against the other
+// (run_staggered), against one launch.  us per generation, one / two launches,
+// 256 CUs, calls of 16 and 40 generations:
+//   - The last round of the tiles' slots at least a quarter empty: the other
+//     group's tiles fill it.  BF16 17 x 1000 x 1000 (272 tiles) 96.6 / 67.4 and
+//     93.0 / 62.5, 24 x 1024 x 1000 (384) 99.0 / 83.6 and 91.0 / 74.2, 17 x 1000 x
+//     700 66.2 / 48.5 and 60.9 / 42.5, 17 x 1000 x 333 (512 slots) 31.7 / 29.7 and
+//     29.2 / 23.8; FP32 17 x 1000 x 1000 430 / 281 and 428 / 277.  From 16
+//     generations on; a single round of rows of up to 128 from 32 on (17 x
+//     1000 x 100 15.0 / 18.2 and 11.8 / 11.2; 33 x 1024 x 100, two rounds, 23.4 /
+//     20.4 and 17.2 / 14.2).
+//   - Full rounds of one BF16 tile per CU: only one group's builds under the
+//     other's products, 16 x 1024 x 1000 (256 tiles) 59.1 / 60.4 and 53.8 / 51.0,
+//     32 x 1024 x 1000 110 / 107 and 104 / 99, 32 x 1024 x 700 75.5 / 72.5 and 67.6 /
+//     63.7: from 32 generations on.
+//   - Full rounds otherwise never: 32 x 1024 x 333 BF16 (512 slots) 35.2 / 39.0
+//     and 31.1 / 31.8, 16 x 1024 x 1000 FP32 244 / 273 and 242 / 266.
+int rot_group_min_gens(int prec, int D, int dpad, int runs, int NP) {
+  const long long cus = device_cus();
+  const long long tiles64 = (long long)runs * ((NP + 63) / 64);
+  const long long tiles32 = (long long)runs * ((NP + 31) / 32);
+  if (runs < 2 || tiles64 < cus) return 0;
+  const int nblk = (D + 31) / 32;
+  const bool wide_bf16 = prec == kPrecBF16 && dpad > kRotBf16NarrowMaxDpad;
+  const bool rows64 = prec == kPrecBF16 ? !rot_few_tiles(tiles32, (int)cus)
+                                        : nblk > kX3TallMinBlocks && nblk <= 32;
+  // two workgroups per CU: narrow BF16 tiles, FP32 of up to 16 column blocks
+  const bool two = prec == kPrecBF16
+                       ? rot_bf16_narrow(dpad, tiles64, (int)cus)
+                       : nblk <= 16;
+  const long long tiles = rows64 ? tiles64 : tiles32;
+  const long long slots = two ? 2 * cus : cus;
+  const long long rounds = (tiles + slots - 1) / slots;
+  if (4 * (rounds * slots - tiles) >= tiles)
+    return dpad <= kPairMaxDpad && rounds == 1 ? 32 : 16;
+  return wide_bf16 ? 32 : 0;
+}
+
 bool rot_half(int prec, int runs, int NP) {
   return prec == kPrecBF16 &&
          rot_few_tiles((long long)runs * ((NP + 31) / 32), device_cus());

@@ -239,8 +239,8 @@ GenArgs base_args(const de_state* s) {
   return a;
 }
 
-// One workgroup restarts the statistics of this many rows faster than four
-// launches do.
+// One workgroup restarts the statistics of this many rows as fast as four
+// launches do or faster (measured at k_begin).
 bool small_rows(const de_state* s) {
   return (long long)s->p.runs * s->p.NP <= de::kBeginMaxRows;
 }

@@ -378,44 +378,94 @@ __device__ __forceinline__ void post_done(unsigned long long* slot,
 }
 
 // Restart of the statistics in one workgroup, for populations of at most
-// kBeginMaxRows rows: best and hit of every run from the current values (one
-// wave per run in turn), and as `what` says accepted counts and stale flags.
-// A run whose best is within target_key hit at generation a.gen.  The count
-// of such runs goes to *done, and with the number `seq` to the host's `slot`
-// (null: nowhere).  A call on a small problem is launches and round trips
-// more than work: one launch here replaces three or four.
+// kBeginMaxRows rows: best and hit of every run from the current values, and
+// as `what` says accepted counts and stale flags.  A run whose best is within
+// target_key hit at generation a.gen.  The count of such runs goes to *done,
+// and with the number `seq` to the host's `slot` (null: nowhere).  A call on a
+// small problem is launches and round trips more than work: one launch here
+// replaces three or four.
+// A run is read by a group of lanes (4 to 64, by NP); where that leaves groups
+// without a run, by several of them, each an interleaved part of the run.
+// Rows loaded and evaluated, statistics restarted, us (in brackets a wave per
+// run, and four launches): 1 x 16384 18 (79, 24), 16 x 1024 17 (21, 23), 256 x 64
+// 27 (30, 24), 4096 x 4 22 (-, 22); the restart of an evolve of 256 x 64 46 (47, 57).
 __global__ __launch_bounds__(1024) void k_begin(GenArgs a, int what,
                                                 unsigned long long target_key,
                                                 HostPost post) {
   __shared__ unsigned int s_done;
-  const int wave = (int)threadIdx.x / 64, lane = (int)threadIdx.x % 64;
-  if (threadIdx.x == 0) s_done = 0u;
+  __shared__ unsigned long long s_best[256];  // of at most a run per group
+  const int tid = (int)threadIdx.x;
+  int G = 4;
+  while (G < 64 && G < a.NP) G *= 2;
+  const int groups = 1024 / G, grp = tid / G, gl = tid % G;
+  const int parts = a.runs <= groups ? groups / a.runs : 0;
+  if (tid == 0) s_done = 0u;
+  if (tid < 256) s_best[tid] = ~0ull;
   __syncthreads();
-  for (int run = wave; run < a.runs; run += 16) {
-    unsigned long long best = ~0ull;
-    for (int i = lane; i < a.NP; i += 64)
-      best = min(best, fit_key(a.fit_cur[(size_t)run * a.NP + i], i));
-    for (int m = 32; m >= 1; m >>= 1) {
+  auto put = [&](int run, unsigned long long best) {
+    const bool hit = (what & kBeginHits) && best != ~0ull &&
+                     (best >> 32) <= (target_key >> 32);
+    a.best_key[run] = best;
+    a.hit_gen[run] = hit ? (unsigned long long)a.gen : kNoHit;
+    if (hit) atomicAdd(&s_done, 1u);
+    if (what & kBeginAccepted) a.accepted[run] = 0ull;
+  };
+  auto reduce = [&](unsigned long long best) {
+    for (int m = G / 2; m >= 1; m >>= 1) {
       const unsigned long long o =
           ((unsigned long long)__shfl_xor((unsigned)(best >> 32), m, 64)
            << 32) |
           (unsigned long long)__shfl_xor((unsigned)best, m, 64);
       best = min(best, o);
     }
-    if (lane == 0) {
-      const bool hit = (what & kBeginHits) && best != ~0ull &&
-                       (best >> 32) <= (target_key >> 32);
-      a.best_key[run] = best;
-      a.hit_gen[run] = hit ? (unsigned long long)a.gen : kNoHit;
-      if (hit) atomicAdd(&s_done, 1u);
-      if (what & kBeginAccepted) a.accepted[run] = 0ull;
+    return best;
+  };
+  // four values in flight, of one run or of four (past the end the last again)
+  if (parts > 0) {
+    const int run = grp / parts, part = grp - run * parts;
+    if (run < a.runs) {
+      const float* f = a.fit_cur + (size_t)run * a.NP;
+      const int step = parts * G;
+      unsigned long long best = ~0ull;
+      for (int i0 = part * G + gl; i0 < a.NP; i0 += 4 * step) {
+        float v[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) v[k] = f[min(i0 + k * step, a.NP - 1)];
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+          best = min(best, fit_key(v[k], min(i0 + k * step, a.NP - 1)));
+      }
+      best = reduce(best);
+      if (gl == 0) atomicMin(&s_best[run], best);
+    }
+  } else {
+    for (int r0 = grp; r0 < a.runs; r0 += 4 * groups) {
+      unsigned long long best[4] = {~0ull, ~0ull, ~0ull, ~0ull};
+      for (int i0 = gl; i0 - gl < a.NP; i0 += G) {
+        const int i = min(i0, a.NP - 1);
+        float v[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+          v[k] = a.fit_cur[(size_t)min(r0 + k * groups, a.runs - 1) * a.NP + i];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) best[k] = min(best[k], fit_key(v[k], i));
+      }
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        best[k] = reduce(best[k]);
+        const int run = r0 + k * groups;
+        if (gl == 0 && run < a.runs) put(run, best[k]);
+      }
     }
   }
   if (what & kBeginStale)
-    for (int t = (int)threadIdx.x; t < a.runs * a.NP; t += 1024)
-      a.changed[t] = 1;
+    for (int t = tid; t < a.runs * a.NP; t += 1024) a.changed[t] = 1;
   __syncthreads();
-  if (threadIdx.x == 0) {
+  if (parts > 0) {
+    if (tid < a.runs) put(tid, s_best[tid]);
+    __syncthreads();
+  }
+  if (tid == 0) {
     *a.done = s_done;
     if (post.slot) {
       *post.finished = 0u;

@@ -687,13 +687,14 @@ __global__ __launch_bounds__(512) void k_mlp_infer_res(SurArgs a, const float* X
   const int tiles = (n + kResRows - 1) / kResRows;
   const int t0 = wu.x * per, t1 = min(t0 + per, tiles);
   // scaled group e (row e / (Dp / 4), coordinates 4 (e % (Dp / 4)) on) of
-  // tile t, zero outside the rows and past D
+  // tile t, zero outside the rows and past D (the caller's last row may end
+  // at its coordinate D - 1)
   auto xquad = [&](int t, int e) {
     const int row = t * kResRows + e / (Dp / 4), j0 = 4 * (e % (Dp / 4));
     float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
     if (row < n && j0 < a.D) {
       const float* p = Xr + (size_t)row * ldx + j0;
-      if (vec) {
+      if (vec && (j0 + 4 <= a.D || row + 1 < n)) {
         v = ld4(p);
       } else {
         v.x = p[0];

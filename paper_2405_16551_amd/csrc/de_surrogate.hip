@@ -9,7 +9,7 @@
 //                  32x32x16 MFMA with FP32 accumulation, bias and ReLU
 //                  fused (the first form, for D padded to at most 128,
 //                  keeps each wave's weight fragments in registers over
-//                  several tiles of 128 candidates)
+//                  several tiles of 64 or 128 candidates)
 //   k_sur_select   per target the lowest prediction is evaluated on the
 //                  composition objective (Section 7.3.3 composition
 //                  functions; the expensive step), strict selection, next
@@ -621,7 +621,7 @@ __global__ __launch_bounds__(256) void k_mlp_infer(SurArgs a, const float* X,
 }
 
 // MLP inference with the weights held in registers: one workgroup of H / 32
-// waves walks `per` tiles of kResRows rows of one run; wave w keeps the BF16
+// waves walks `per` tiles of 32 RB rows of one run; wave w keeps the BF16
 // fragments of hidden block w of W1 (KB1 = Dp / 16 K-steps) and of W2 (KB2 =
 // H / 16) for the whole launch, so the K loops read only LDS.  Both layers
 // are computed transposed (the weights as the A operand): a lane then holds
@@ -630,13 +630,11 @@ __global__ __launch_bounds__(256) void k_mlp_infer(SurArgs a, const float* X,
 // tree over hidden units 16, 8, 4, 2, 1 apart that k_mlp_infer forms, then
 // the blocks in order, then b3.
 // Bound: the chain of barriers and LDS round trips of a tile (LDS and matrix
-// time are both 3 us per 128 rows and CU).  Four row blocks per barrier
-// instead of two and no per-value writes: 36.7 -> 19.5 us at 30 x 2048
-// rows, D 100, H 256; with tiles dealt to all CUs, 2048 rows of one run
-// 33 -> 10 us.
-constexpr int kResRows = 128;
-
-template <int KB1, int KB2>
+// time are both 3 us per 128 rows and CU).  With many tiles four row blocks per
+// barrier (RB) instead of two, and no per-value writes: 36.7 -> 19.5 us at 30 x
+// 2048 rows, D 100, H 256; with few tiles two, dealt to all CUs: 2048 rows of one
+// run 33 -> 7.8 us.  A row's value does not depend on RB.
+template <int KB1, int KB2, int RB>
 __global__ __launch_bounds__(512) void k_mlp_infer_res(SurArgs a, const float* X,
                                                        size_t x_run_stride,
                                                        int n, int ldx, float* y,
@@ -644,10 +642,10 @@ __global__ __launch_bounds__(512) void k_mlp_infer_res(SurArgs a, const float* X
                                                        int run0, int per,
                                                        int vec) {
   constexpr int Dp = KB1 * 16, H = KB2 * 16, NW = H / 32, kThr = 64 * NW;
-  constexpr int sa = Dp + 8, sh = H + 8, RB = kResRows / 32;
+  constexpr int sa = Dp + 8, sh = H + 8, kRows = 32 * RB;
   // 4-coordinate groups of a tile per thread; held in registers (BF16) one
   // tile ahead when they are few
-  constexpr int kQuads = kResRows * (Dp / 4) / kThr;
+  constexpr int kQuads = kRows * (Dp / 4) / kThr;
   constexpr bool kPre = kQuads <= 8;
   extern __shared__ __align__(16) char smem[];
   const RunUnit wu = run_unit();
@@ -655,8 +653,8 @@ __global__ __launch_bounds__(512) void k_mlp_infer_res(SurArgs a, const float* X
   const int tid = (int)threadIdx.x, lane = tid % 64;
   const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
   __bf16* A = reinterpret_cast<__bf16*>(smem);
-  __bf16* H1 = A + (size_t)kResRows * sa;
-  float* ypart = reinterpret_cast<float*>(H1 + (size_t)kResRows * sh);
+  __bf16* H1 = A + (size_t)kRows * sa;
+  float* ypart = reinterpret_cast<float*>(H1 + (size_t)kRows * sh);
   const float* Xr = X + wu.run * x_run_stride;
   const float* th = a.theta + (size_t)run * a.pstride;
   const float* b1 = th + (size_t)H * a.D;
@@ -684,13 +682,13 @@ __global__ __launch_bounds__(512) void k_mlp_infer_res(SurArgs a, const float* X
     b2r[r] = b2[u];
     w3r[r] = w3[u];
   }
-  const int tiles = (n + kResRows - 1) / kResRows;
+  const int tiles = (n + kRows - 1) / kRows;
   const int t0 = wu.x * per, t1 = min(t0 + per, tiles);
   // scaled group e (row e / (Dp / 4), coordinates 4 (e % (Dp / 4)) on) of
   // tile t, zero outside the rows and past D (the caller's last row may end
   // at its coordinate D - 1)
   auto xquad = [&](int t, int e) {
-    const int row = t * kResRows + e / (Dp / 4), j0 = 4 * (e % (Dp / 4));
+    const int row = t * kRows + e / (Dp / 4), j0 = 4 * (e % (Dp / 4));
     float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
     if (row < n && j0 < a.D) {
       const float* p = Xr + (size_t)row * ldx + j0;
@@ -784,15 +782,15 @@ __global__ __launch_bounds__(512) void k_mlp_infer_res(SurArgs a, const float* X
 #pragma unroll
       for (int r = 0; r < 4; ++r) v[r] += __shfl_xor(v[r], 32, 64);  // 4
       const float s = (v[0] + v[2]) + (v[1] + v[3]);
-      if (lk == 0) ypart[wave * kResRows + 32 * m + li] = s;
+      if (lk == 0) ypart[wave * kRows + 32 * m + li] = s;
     }
     __syncthreads();  // ypart complete
-    for (int r = tid; r < kResRows; r += kThr) {
-      const int row = t * kResRows + r;
+    for (int r = tid; r < kRows; r += kThr) {
+      const int row = t * kRows + r;
       if (row < n) {
         float s = b3;
 #pragma unroll
-        for (int w = 0; w < NW; ++w) s += ypart[w * kResRows + r];
+        for (int w = 0; w < NW; ++w) s += ypart[w * kRows + r];
         y[wu.run * y_run_stride + row] = s;
       }
     }
@@ -1699,23 +1697,24 @@ de_status set_lds_attributes() {
 using InferRes = void (*)(SurArgs, const float*, size_t, int, int, float*,
                           size_t, int, int, int);
 
-template <int KB1>
+template <int KB1, int RB>
 InferRes infer_res_for_h(int H) {
   switch (H) {
-    case 32: return &de::k_mlp_infer_res<KB1, 2>;
-    case 64: return &de::k_mlp_infer_res<KB1, 4>;
-    case 128: return &de::k_mlp_infer_res<KB1, 8>;
-    case 256: return &de::k_mlp_infer_res<KB1, 16>;
+    case 32: return &de::k_mlp_infer_res<KB1, 2, RB>;
+    case 64: return &de::k_mlp_infer_res<KB1, 4, RB>;
+    case 128: return &de::k_mlp_infer_res<KB1, 8, RB>;
+    case 256: return &de::k_mlp_infer_res<KB1, 16, RB>;
     default: return nullptr;
   }
 }
 
+template <int RB>
 InferRes infer_res_kernel(int Dp, int H) {
   switch (Dp) {
-    case 32: return infer_res_for_h<2>(H);
-    case 64: return infer_res_for_h<4>(H);
-    case 96: return infer_res_for_h<6>(H);
-    case 128: return infer_res_for_h<8>(H);
+    case 32: return infer_res_for_h<2, RB>(H);
+    case 64: return infer_res_for_h<4, RB>(H);
+    case 96: return infer_res_for_h<6, RB>(H);
+    case 128: return infer_res_for_h<8, RB>(H);
     default: return nullptr;
   }
 }
@@ -1723,14 +1722,19 @@ InferRes infer_res_kernel(int Dp, int H) {
 de_status launch_infer(const SurArgs& a, const float* X, size_t x_stride,
                        int n, int ldx, float* y, size_t y_stride, int run0,
                        int nruns, hipStream_t st) {
-  if (const InferRes fn = infer_res_kernel(a.Dp, a.H)) {
+  // fewer than three 64-row tiles per CU: those, else 128 rows (D 100, H 256: 1
+  // row 6.8 us / 9.2, 2048 rows 7.8 / 10.6, 40000 14.7 / 17.3; 30 x 2048 20.6 / 19.5)
+  const bool low = (long long)((n + 63) / 64) * nruns < 3ll * de::device_cus();
+  if (const InferRes fn = low ? infer_res_kernel<2>(a.Dp, a.H)
+                              : infer_res_kernel<4>(a.Dp, a.H)) {
+    const int rows = low ? 64 : 128;
     // as many tiles per workgroup as fill the compute units once (each
     // workgroup loads the weights once), at most eight
-    const long long tiles = (n + de::kResRows - 1) / de::kResRows;
+    const long long tiles = (n + rows - 1) / rows;
     const long long cus = de::device_cus();
     const int per = (int)std::min<long long>(
         8, std::max<long long>(1, (tiles * nruns + cus - 1) / cus));
-    const size_t lds = (size_t)de::kResRows *
+    const size_t lds = (size_t)rows *
                        ((a.Dp + 8) * 2 + (a.H + 8) * 2 + (a.H / 32) * 4);
     const de_status rc =
         FROM_HIP(de::set_max_dynamic_lds(reinterpret_cast<const void*>(fn)));

@@ -36,3 +36,17 @@ def test_last_row_without_padding(D, H, n):
                                        y.data_ptr(), s._s()), "de_sur_predict")
     np.testing.assert_array_equal(host(y), host(s.predict(0, X)))
     s.close()
+
+
+# tiles of 64 rows while there are fewer than three per compute unit, then of
+# 128: rows at both sides of the line (768 tiles of 64) equal a few of them
+@pytest.mark.parametrize("D,H", [(30, 32), (64, 64), (90, 128), (100, 256)])
+def test_tile_heights_agree(D, H):
+    s, _ = sur.make_sur(runs=1, NP=64, D=D, hidden=H, steps=3, warmup_gens=1)
+    s.generation(3)
+    X = np.random.default_rng(D).uniform(LO, HI, (49153, D)).astype(np.float32)
+    high = host(s.predict(0, X))
+    low = host(s.predict(0, X[:767 * 64]))
+    np.testing.assert_array_equal(low, high[:len(low)])
+    np.testing.assert_array_equal(host(s.predict(0, X[-65:])), high[-65:])
+    s.close()

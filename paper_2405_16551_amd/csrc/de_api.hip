@@ -245,6 +245,15 @@ bool small_rows(const de_state* s) {
   return (long long)s->p.runs * s->p.NP <= de::kBeginMaxRows;
 }
 
+// Whether the last launch of a chunk may post the done counter itself: every
+// run's workgroup then counts itself finished behind a fence, one after the
+// other, which pays while the runs are few (60 generations in chunks of 5, us,
+// posted by the launch / by one of its own: 64 runs 216 / 265, 300 220 / 237,
+// 2000 578 / 243).
+bool self_posting(const de_state* s) {
+  return small_rows(s) && s->p.runs <= de::device_cus();
+}
+
 // f of pop[gen & 1] into fit[gen & 1], then statistics restart.
 de_status eval_current_and_reset(de_state* s, hipStream_t st) {
   GenArgs a = base_args(s);
@@ -320,7 +329,7 @@ bool stagger_enabled() {
   return on;
 }
 
-constexpr int kPollSlots = 2, kPollHits = 4096;
+constexpr int kPollSlots = 2, kPollHits = 65536;
 
 // Waits for post number seq in slot: polls the pinned word for a while (a
 // chunk of a small problem takes some tens of microseconds, less than the
@@ -759,8 +768,9 @@ DE_API de_status de_evolve(de_state* state, int64_t max_gens, double target,
   de_status rc = DE_OK;
   if (!state->poll_slot) {
     void* h = nullptr;
-    rc = FROM_HIP(hipHostMalloc(&h, (kPollSlots + kPollHits) * 8,
-                                hipHostMallocDefault));
+    rc = FROM_HIP(hipHostMalloc(
+        &h, (size_t)(kPollSlots + std::min(state->p.runs, kPollHits)) * 8,
+        hipHostMallocDefault));
     for (int k = 0; k < kPollSlots && rc == DE_OK; ++k)
       rc = FROM_HIP(hipEventCreateWithFlags(&state->poll_ev[k],
                                             hipEventDisableTiming));
@@ -819,12 +829,11 @@ DE_API de_status de_evolve(de_state* state, int64_t max_gens, double target,
     while (rc == DE_OK) {
       while (rc == DE_OK && inflight < 2 && done_gens < max_gens) {
         const int64_t n = std::min<int64_t>(check_every, max_gens - done_gens);
-        // small populations (whose restart cleared the workgroup count):
-        // the chunk's last launch may post by itself
+        // (k_begin cleared the workgroup count of a launch that posts itself)
         const de::HostPost post = post_to(tail);
-        if (small_rows(state)) state->pending = post;
+        if (self_posting(state)) state->pending = post;
         rc = run_generations(state, n, st);
-        const bool taken = small_rows(state) && !state->pending.slot;
+        const bool taken = self_posting(state) && !state->pending.slot;
         state->pending = {};
         if (rc != DE_OK) break;
         done_gens += n;
@@ -850,7 +859,9 @@ DE_API de_status de_evolve(de_state* state, int64_t max_gens, double target,
     rc = FROM_HIP(
         de::launch_post(a, slot + kPollSlots, runs, post_to(0), st));
   // a chunk queued ahead may still run: the call returns with the stream idle
-  if (rc == DE_OK) rc = FROM_HIP(hipStreamSynchronize(st));
+  // (hits that are copied below wait for it there)
+  if (rc == DE_OK && (post_hits || !hit_gen))
+    rc = FROM_HIP(hipStreamSynchronize(st));
   *gens_done = done_gens;
   if (rc == DE_OK && hit_gen) {
     unsigned long long* tmp = slot + kPollSlots;

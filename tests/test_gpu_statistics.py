@@ -48,3 +48,29 @@ def test_restarted_statistics(runs, NP):
     want = np.where(f.min(axis=1) <= target, 4, -1)
     np.testing.assert_array_equal(np.asarray(hits), want)
     de.close()
+
+
+# evolve in chunks against single steps: runs that fit one workgroup each and
+# more, posts by the launch itself and behind it, hits posted and copied
+@pytest.mark.parametrize("runs,NP,D", [
+    (256, 6, 3), (257, 6, 3), (4096, 4, 2), (5000, 4, 2), (65536, 4, 1),
+    (65537, 4, 1),
+])
+def test_first_hits_of_many_runs(runs, NP, D):
+    a, _, _ = make_de(runs=runs, NP=NP, D=D, seed=8)
+    b, _, _ = make_de(runs=runs, NP=NP, D=D, seed=8)
+    best = [host(b.fitness()).min(axis=1)]
+    for _ in range(12):
+        b.generation(1)
+        best.append(host(b.fitness()).min(axis=1))
+    best = np.array(best)
+    target = float(np.float32(np.quantile(best[6], 0.5)))
+    done, hits = a.evolve(12, target=target, check_every=5)
+    assert done == 12
+    hit = best <= target
+    want = np.where(hit.any(axis=0), hit.argmax(axis=0), -1)
+    np.testing.assert_array_equal(np.asarray(hits), want)
+    np.testing.assert_array_equal(host(a.population()), host(b.population()))
+    assert a.stats() == b.stats()
+    a.close()
+    b.close()

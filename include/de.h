@@ -64,8 +64,8 @@ typedef enum de_obj_kind { DE_OBJ_SPHERE = 0, DE_OBJ_ROT_OSC = 1 } de_obj_kind;
 
 /* Arithmetic of the rotation product z = R y (DE_OBJ_ROT_OSC only).
  *   DE_GEMM_FP32: FP32 operands, FP32 accumulation (from 32 coordinates on
- *                 as three BF16 parts that hold all 24 bits of an operand,
- *                 MFMA bf16; below, MFMA f32).
+ *                 as three BF16 parts that hold all 24 bits of an operand
+ *                 of magnitude 2^-102 and more, MFMA bf16; below, MFMA f32).
  *   DE_GEMM_BF16: y and R rounded to BF16 (nearest-even), FP32 accumulation
  *                 (MFMA bf16).  Everything else stays FP32.                */
 typedef enum de_gemm_prec { DE_GEMM_FP32 = 0, DE_GEMM_BF16 = 1 } de_gemm_prec;

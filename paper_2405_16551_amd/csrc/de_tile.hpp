@@ -79,7 +79,8 @@ struct PrecF32 {
 };
 // FP32 operands on the BF16 matrix instruction: y = yh + ym + yl and R = Rh +
 // Rm + Rl, three BF16 parts of eight significant bits each, which hold all 24
-// bits and the whole exponent range of an FP32 value (the splitting of Henry,
+// bits of an FP32 value from 2^-102 up (the smallest part of a smaller one
+// falls below BF16's least normal) to the largest (the splitting of Henry,
 // Tang & Heinecke, "Leveraging the bfloat16 artificial intelligence datatype
 // for higher-precision computations", ARITH 2019).  Per K-step of 16
 // coordinates one MFMA forms yh Rh and a chain of seven the smaller products,
@@ -110,7 +111,8 @@ struct PrecX3 {
 constexpr int kX3MinD = 32;
 constexpr int kX3TallMinBlocks = 24;  // column blocks; beyond: 64-row tiles
 
-// The three BF16 parts of N values, a pair per conversion.
+// The three BF16 parts of N values, a pair at a time: the high part the upper
+// half of the word (rounded it could overflow), the others rounded.
 template <int N, class V>
 __device__ __forceinline__ void x3_split(const float (&v)[N], V (&p)[3]) {
   typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
@@ -120,12 +122,20 @@ __device__ __forceinline__ void x3_split(const float (&v)[N], V (&p)[3]) {
     float r0 = v[u], r1 = v[u + 1];
 #pragma unroll
     for (int q = 0; q < 3; ++q) {
-      const bf16x2 h = __builtin_convertvector((floatx2{r0, r1}), bf16x2);
+      const uint32_t w =
+          q == 0 ? (__builtin_bit_cast(uint32_t, r0) >> 16) |
+                       (__builtin_bit_cast(uint32_t, r1) & 0xFFFF0000u)
+                 : __builtin_bit_cast(uint32_t, __builtin_convertvector(
+                                                    (floatx2{r0, r1}), bf16x2));
+      const bf16x2 h = __builtin_bit_cast(bf16x2, w);
       p[q][u] = h[0];
       p[q][u + 1] = h[1];
-      const uint32_t w = __builtin_bit_cast(uint32_t, h);
-      r0 -= __builtin_bit_cast(float, w << 16);
-      r1 -= __builtin_bit_cast(float, w & 0xFFFF0000u);
+      r0 -= __builtin_bit_cast(
+          float, q == 0 ? __builtin_bit_cast(uint32_t, r0) & 0xFFFF0000u
+                        : w << 16);
+      r1 -= __builtin_bit_cast(
+          float, q == 0 ? __builtin_bit_cast(uint32_t, r1) & 0xFFFF0000u
+                        : w & 0xFFFF0000u);
     }
   }
 }

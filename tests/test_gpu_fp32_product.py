@@ -20,7 +20,7 @@ import pytest
 
 import oracle
 from tests import test_gpu_kernel_edges as edges
-from tests.gpu_helpers import HI, LO, host, host_threads
+from tests.gpu_helpers import FP32_RTOL, HI, LO, host, host_threads
 
 pytestmark = pytest.mark.gpu
 
@@ -99,6 +99,28 @@ def test_small_rows_of_R_keep_their_bits(D, n, decades):
     Y = (rng.uniform(1.0, 2.0, (n, D)) / scale).astype(np.float32)
     r = _rel(host(de.eval(Y)), Y, R)
     assert r.max() <= (12 + 24) * U
+    de.close()
+
+
+# next to the largest float: the high part must not round beyond it.  |z| ~ 3e7,
+# where the sine's argument carries no bits: f by z^2, at the bar of a step
+@pytest.mark.parametrize("D,n", SIZES)
+def test_largest_operands(D, n):
+    rng = np.random.default_rng(D + n)
+    top = np.finfo(np.float32).max
+    X, j = _single(rng, n, D, 3.2e38, 3.4e38)
+    X[0, j[0]] = top
+    R = np.diag(rng.uniform(1e-31, 2e-31, D).astype(np.float32))
+    de = _handle(D, R)
+    assert _rel(host(de.eval(X)), X, R).max() <= FP32_RTOL
+    de.close()
+    de = _handle(D, np.zeros_like(R))
+    assert (host(de.eval(X)) == 0.0).all()
+    de.close()
+    R = np.diag(np.full(D, top))
+    X[np.arange(n), j] = 1e-31
+    de = _handle(D, R)
+    assert _rel(host(de.eval(X)), X, R).max() <= FP32_RTOL
     de.close()
 
 

@@ -208,7 +208,11 @@ __host__ __device__ __forceinline__ bool take_mutant(uint32_t word, int j, int j
 
 // Mutant coordinate of eq. 2 with clamping to the box; NaN passes through
 // (on gfx950 as v_maximum3 / v_minimum3, which hand a NaN on, instead of two
-// compares and two selects with their wait states).
+// compares and two selects with their wait states: 16 x 1024 x 1000 sphere 386
+// us per 20 generations against 401, BF16 1143 / 1168).  Of a zero and a bound
+// of zero with unlike signs maximum takes +0 and minimum -0 where the selects
+// keep the coordinate: -0, which only a loaded row can hold, becomes +0 at lo =
+// +0.  The two compare equal and give the same f.
 __host__ __device__ __forceinline__ float mutant_coord(float x1, float x2, float x3,
                                               float F, float lo, float hi) {
   float v = fmaf(F, x2 - x3, x1);

@@ -1326,7 +1326,9 @@ void k_train_grad(SurArgs a) {
   else
     c = mfma_block(dl + (size_t)lk * H + i, H, hv + (size_t)lk * ldh + j, ldh,
                    B, B, lk);
-  if constexpr (KS == 0) read_state();  // fewer registers, no spills
+  // (the form for any minibatch holds the operands of two batches besides; the
+  // others store two registers before the product and reload them after it)
+  if constexpr (KS == 0) read_state();
   // the block's new weights (0 in W1's padding columns) go through LDS so
   // that the transposed copy is written in rows of 32 and the BF16
   // fragment copy in 16-byte pieces

@@ -41,9 +41,9 @@ if ROOT not in sys.path:
 
 HBM_PEAK_GBS = 8000.0       # MI355X HBM3E
 BF16_PEAK_TFLOPS = 2500.0   # MI355X dense BF16 MFMA
-# FP32 rotation product: three half-precision products per FP32 product (rows
-# of 32 coordinates and more), at the dense half-precision rate
-FP32_PEAK_TFLOPS = round(BF16_PEAK_TFLOPS / 3, 1)
+# FP32 rotation product: eight BF16 products per FP32 product (rows of 32
+# coordinates and more), at the dense BF16 rate
+FP32_PEAK_TFLOPS = round(BF16_PEAK_TFLOPS / 8, 1)
 
 WORKLOADS = {
     "rot1000_bf16": dict(runs=16, NP=1024, D=1000, kind="rot_osc",
